@@ -73,7 +73,8 @@ struct dil_keyset {
   void *mem = nullptr;
   uint8_t *pk = nullptr, *sk = nullptr, *tr = nullptr;   // key rows (copies) and tr = H(pk)
   size_t bytes = 0;                                      // device memory held
-  int32_t *A = nullptr, *s1h = nullptr, *s2h = nullptr, *t0h = nullptr, *t1h = nullptr;
+  int32_t *A = nullptr, *t1h = nullptr;
+  int8_t *sec = nullptr;
 };
 
 namespace {
@@ -125,7 +126,7 @@ constexpr int persist_slots(int waves) {
 
 // Lay out the workspace of a call of `cap` tasks at `base` (nullptr: only
 // count) and return its size in bytes.  Every row is 256-byte aligned.  With a
-// resident key table (keyset) A-hat and the NTT-domain secrets come from the
+// resident key table (keyset) A-hat and the secret tiles come from the
 // table and are not carved; the persistent form adds its per-workgroup scratch
 // for `grid` workgroups of `waves` wavefronts.
 template <int LV>
@@ -150,9 +151,8 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.ctilde = take(staged, cap * CT_STRIDE);
   w.cpoly = (int8_t *)take(staged || form == WS_VERIFY, cap * 256);
   w.A = (int32_t *)take(!keyset, cap * K * L * 1024);
-  w.s1h = (int32_t *)take(form == WS_KEYGEN || (sign && !keyset), cap * (form == WS_KEYGEN ? L + K : L) * 1024);
-  w.s2h = (int32_t *)take(sign && !keyset, cap * K * 1024);
-  w.t0h = (int32_t *)take(sign && !keyset, cap * K * 1024);
+  w.s12 = (int32_t *)take(form == WS_KEYGEN, cap * (L + K) * 1024);
+  w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
   w.y = (int32_t *)take(staged, cap * L * 1024);
   w.w = (int32_t *)take(staged, cap * K * 1024);
   w.hmask = (uint32_t *)take(form == WS_VERIFY, cap * K * 32);
@@ -327,16 +327,14 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
   return mark_done(ctx, st);
 }
 
-// Resident key tables replace the per-task A-hat / NTT(s) arrays (no ExpandA,
-// no secret NTTs).  A caller's key_idx is read only once, by keys_check_k
+// Resident key tables replace the per-task A-hat and secret tiles (no ExpandA,
+// no unpacking).  A caller's key_idx is read only once, by keys_check_k
 // (check_keys below), which writes a copy with every index inside the table
 // to `checked`; every other kernel of the call reads that copy, which this
 // returns (nullptr when the call has no key_idx: task i uses row i).
 const uint32_t *use_keyset(Ws &ws, const dil_keyset *ks, const uint32_t *key_idx, uint32_t *checked) {
   ws.A = ks->A;
-  ws.s1h = ks->s1h;
-  ws.s2h = ks->s2h;
-  ws.t0h = ks->t0h;
+  ws.sec = ks->sec;
   ws.t1h = ks->t1h;
   ws.tr = ks->tr;
   ws.kmap = key_idx ? checked : nullptr;
@@ -350,7 +348,7 @@ void check_keys(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, uin
 
 // The setup stages are independent of each other: mu/rho' hash chains (one lane
 // per task, latency-bound for small batches), ExpandA (one lane per stream) and
-// the secret NTTs (one wave per task).  With `concurrent` they run on the
+// the secrets' unpacking (one wave per key).  With `concurrent` they run on the
 // context's side streams so the long chains overlap the bulk work.
 template <int LV>
 int sign_setup(dil_ctx *ctx, Ws &ws, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
@@ -614,7 +612,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   size_t bytes = 0;
   auto rnd = [](size_t b) { return (b + 255) & ~(size_t)255; };
   bytes += rnd(n * K * L * 1024);
-  if (sk) bytes += rnd(n * PP::SK) + rnd(n * L * 1024) + 2 * rnd(n * K * 1024);
+  if (sk) bytes += rnd(n * PP::SK) + rnd(n * sec_bytes<LV>());
   if (pk) bytes += rnd(n * PP::PK) + rnd(n * K * 1024);
   bytes += rnd(n * PP::TRB);
   hipError_t e = hipMalloc(&ks->mem, bytes);
@@ -633,9 +631,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   ks->tr = take(n * PP::TRB);
   if (sk) {
     ks->sk = take(n * PP::SK);
-    ks->s1h = (int32_t *)take(n * L * 1024);
-    ks->s2h = (int32_t *)take(n * K * 1024);
-    ks->t0h = (int32_t *)take(n * K * 1024);
+    ks->sec = (int8_t *)take(n * sec_bytes<LV>());
     HIPCHK(ctx, hipMemcpyAsync(ks->sk, sk, n * PP::SK, hipMemcpyDeviceToDevice, st));
   }
   if (pk) {
@@ -647,9 +643,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   if (sk) {
     expand_a_k<LV><<<nb, EA_WG, 0, st>>>(ks->sk, PP::SK, nullptr, ks->A, ks->nkeys);
     Ws w{};
-    w.s1h = ks->s1h;
-    w.s2h = ks->s2h;
-    w.t0h = ks->t0h;
+    w.sec = ks->sec;
     sg_secret_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->sk, nullptr, w, ks->nkeys);
   } else {
     expand_a_k<LV><<<nb, EA_WG, 0, st>>>(ks->pk, PP::PK, nullptr, ks->A, ks->nkeys);

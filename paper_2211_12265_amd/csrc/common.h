@@ -124,6 +124,12 @@ __device__ __forceinline__ int32_t mont_reduce(int64_t a) {
   return (int32_t)((a - (int64_t)t * Q) >> 32);
 }
 __device__ __forceinline__ int32_t mont_mul(int32_t a, int32_t b) { return mont_reduce((int64_t)a * b); }
-// canonical representative in [0, q) of x in (-q, q)
-__device__ __forceinline__ int32_t canon(int32_t x) { return x + ((x >> 31) & Q); }
+// canonical representative in [0, q) of x in (-q, q): as unsigned words the
+// smaller of x and x + q
+__device__ __forceinline__ int32_t canon(int32_t x) { return (int32_t)min((uint32_t)x, (uint32_t)(x + Q)); }
+// canonical representative of x in [-q, 2q)
+__device__ __forceinline__ int32_t canon_near(int32_t x) {
+  const uint32_t v = (uint32_t)canon(x);
+  return (int32_t)min(v, v - (uint32_t)Q);
+}
 }  // namespace dil

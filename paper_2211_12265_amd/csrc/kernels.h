@@ -11,6 +11,7 @@
 #include "poly.h"
 #include "sponge.h"
 #include "keccak_pair.h"
+#include "toeplitz.h"
 
 namespace dil {
 
@@ -23,9 +24,8 @@ struct Ws {
   uint8_t *ctilde;   // [cap][CT_STRIDE]
   int8_t *cpoly;     // [cap][256]  challenge c, dense
   int32_t *A;        // [cap][K][L][256]  A-hat, canonical
-  int32_t *s1h;      // [cap][L][256]  NTT(s1)   (KeyGen: s1, s2 centred, [cap][L+K][256])
-  int32_t *s2h;      // [cap][K][256]
-  int32_t *t0h;      // [cap][K][256]
+  int32_t *s12;      // KeyGen: s1, s2 centred, [cap][L+K][256]
+  int8_t *sec;       // [cap][sec_bytes] Sign: s1, s2, t0 as int8 tiles (toeplitz.h)
   int32_t *y;        // [cap][L][256]  mask, centred
   int32_t *w;        // [cap][K][256]  w = A y, canonical
   uint32_t *hmask;   // [cap][K][8]   verify: hint bits
@@ -35,7 +35,7 @@ struct Ws {
   uint32_t *counters;           // [8]: next active count, error flags, attempts
   size_t cap;
   size_t muw1_stride;
-  // Resident key tables: when kmap is set, A, s1h, s2h, t0h (and t1h, tr) are
+  // Resident key tables: when kmap is set, A, sec (and t1h, tr) are
   // indexed by key row kmap[task] instead of by task.
   const uint32_t *kmap;
   const int32_t *t1h;   // [keys][K][256] NTT(t1 2^d), slots layout (verify), or null
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size
   expand_a_squeeze_wave(s, A + (size_t)(st - lane) * N, rows[threadIdx.x >> 6], lane, valid);
 }
 
-// ExpandS: one lane per (task, r < L + K); centred coefficients to ws.s1h
+// ExpandS: one lane per (task, r < L + K); centred coefficients to ws.s12
 template <int LV>
 __global__ void __launch_bounds__(256) expand_s_k(Ws ws, uint32_t count) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256) expand_s_k(Ws ws, uint32_t count) {
   int r = (int)(st % (K + L));
   uint32_t s[50];
   absorb_seed66(s, ws.rhop + (size_t)task * 64, (uint32_t)r);
-  expand_s_squeeze<Lv<LV>::ETA>(s, ws.s1h + (size_t)st * N);
+  expand_s_squeeze<Lv<LV>::ETA>(s, ws.s12 + (size_t)st * N);
 }
 
 // LDS layout shared by the per-task polynomial kernels
@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
   int32_t *tr = lds.tr + g * NTT_LDS_GROUP;
   uint8_t *skb = (uint8_t *)lds.buf;
   uint8_t *pkb = (uint8_t *)pkbuf;
-  const int32_t *S = ws.s1h + (size_t)task * (K + L) * N;
+  const int32_t *S = ws.s12 + (size_t)task * (K + L) * N;
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
   // s1: NTT into LDS, and pack eta - s into sk
   for (int j = g; j < L; j += 4) {
@@ -449,45 +449,47 @@ __global__ void __launch_bounds__(256) sg_prep_k(const uint8_t *sk, const uint32
   }
 }
 
-// NTT of the secret vectors s1, s2, t0 unpacked from sk
+// s1, s2 and t0 unpacked from sk into the int8 tiles of toeplitz.h, one
+// wavefront per key row: lane chunk id = 64 k + lane holds coefficients
+// 16 (id & 15) .. + 15 of tile row id >> 4, so that a wavefront's 16-byte
+// stores are contiguous.  Bound by memory: 2.5 / 4 / 4.9 KB read and 4 / 8 / 8
+// KB written per key at levels 2 / 3 / 5 (the NTT-domain int32 form it
+// replaces wrote 12 / 17 / 23 KB and ran 12 / 17 / 23 transforms).
 template <int LV>
 __global__ void __launch_bounds__(64) sg_secret_k(const uint8_t *sk, const uint32_t *key_idx, Ws ws, uint32_t count) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, ETA = Lv<LV>::ETA;
-  __shared__ PolyLds<LV> lds;
+  constexpr int NW = (PP::SK - PP::OFF_S1) / 4;
+  __shared__ uint32_t buf[NW + 2];
   uint32_t task = blockIdx.x;
   if (task >= count) return;
-  int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
-  int32_t *tr = lds.tr + g * NTT_LDS_GROUP;
+  const int lane = threadIdx.x;
   size_t key = key_idx ? key_idx[task] : task;
-  const uint8_t *skr = sk + key * PP::SK;
   // stage sk bytes OFF_S1..SK into LDS (sk rows are 8-byte aligned)
-  const uint32_t *skw = (const uint32_t *)(skr + PP::OFF_S1);
-  constexpr int NW = (PP::SK - PP::OFF_S1) / 4;
-  g2l_words<NW>(skw, lds.buf, lane);
-  if (lane < 2) lds.buf[NW + lane] = 0;
+  g2l_words<NW>((const uint32_t *)(sk + key * PP::SK + PP::OFF_S1), buf, lane);
+  if (lane < 2) buf[NW + lane] = 0;
   wave_sync();
-  const Tw ftw = ntt_lane_tw(t);
-  for (int p = g; p < L + 2 * K; p += 4) {
-    uint32_t v[16];
-    int32_t x[16];
-    int32_t *dst;
-    if (p < L + K) {
-      const uint32_t *src = lds.buf + (p * PP::EB) / 4;
-      unpack_strided<PP::EBITS>(src, v, t);
+  v4i *out = (v4i *)(ws.sec + (size_t)task * sec_bytes<LV>());
+  const int part = (lane >> 4) & 3, c0 = 16 * (lane & 15);
+#pragma unroll 1
+  for (int k = 0; k < 4 * sec_tiles<LV>(); k++) {  // the wavefront's four rows: the parts of polynomial k
+    uint32_t v[4] = {0, 0, 0, 0};
+    if (part < 2) {
+      if (k < (part ? K : L)) {
+        const uint32_t *src = buf + (part ? L + k : k) * (PP::EB / 4);
 #pragma unroll
-      for (int r = 0; r < 16; r++) x[r] = ETA - (int32_t)v[r];
-      dst = p < L ? ws.s1h + ((size_t)task * L + p) * N : ws.s2h + ((size_t)task * K + (p - L)) * N;
-    } else {
-      int i = p - L - K;
-      const uint32_t *src = lds.buf + ((L + K) * PP::EB + i * PP::T0B) / 4;
-      unpack_strided<13>(src, v, t);
+        for (int r = 0; r < 16; r++)
+          v[r >> 2] |= (uint32_t)((ETA - (int32_t)field<PP::EBITS>(src, c0 + r)) & 0xFF) << (8 * (r & 3));
+      }
+    } else if (k < K) {
+      const uint32_t *src = buf + ((L + K) * PP::EB + k * PP::T0B) / 4;
 #pragma unroll
-      for (int r = 0; r < 16; r++) x[r] = (1 << (D - 1)) - (int32_t)v[r];
-      dst = ws.t0h + ((size_t)task * K + i) * N;
+      for (int r = 0; r < 16; r++) {
+        const int32_t t0 = (1 << (D - 1)) - (int32_t)field<13>(src, c0 + r), hi = (t0 + 32) >> 6;
+        v[r >> 2] |= (uint32_t)((part == 2 ? t0 - 64 * hi : hi) & 0xFF) << (8 * (r & 3));
+      }
     }
-    ntt16(x, ftw, tr, t);
-    store_slots(x, dst, t);
+    out[64 * k + lane] = v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
   }
 }
 
@@ -631,125 +633,107 @@ __device__ __forceinline__ void dev_challenge(const uint8_t *mu, const uint8_t *
 
 template <int LV>
 struct CheckLds {
-  int32_t tr[4 * NTT_LDS_GROUP];
-  uint32_t sigbuf[P<LV>::SIG / 4 + 2];
+  uint32_t ct[TOEP_WORDS];               // shifted copies of the challenge (toeplitz.h)
+  uint32_t sigbuf[P<LV>::SIG / 4 + 2];   // packed signature; holds f while the copies are built
   uint16_t hmask[Lv<LV>::K][16];
   int rowcnt[Lv<LV>::K];
 };
 
 // The rejection checks of Alg. 2 for one candidate (one wavefront):
 // z = y + c s1, r0 = LowBits(w - c s2), c t0 and the hint.  c is the dense
-// challenge (int8, natural order).  Returns true (wave-uniform) if the
-// candidate passes all four checks; the packed signature (ctilde, z, h) is
-// then in lds.sigbuf.  Polynomials whose norm already fails stop the
-// evaluation early.  EARLY (as in dev_compute_w): the group's first s1-hat
-// and y polynomials are requested before the NTT of c, the next ones before
-// the current one's INTT, and a row's w and t0-hat together with its s2-hat.
-template <int LV, bool PAD = true, bool EARLY = false, class TW>
+// challenge (int8, natural order, 4-byte aligned), sec the key's int8 tiles.
+// Returns true (wave-uniform) if the candidate passes all four checks; the
+// packed signature (ctilde, z, h) is then in lds.sigbuf.
+//
+// The products by c run on the matrix cores (toeplitz.h): 64 products per tile
+// of four polynomials, exact, instead of one NTT and twelve INTTs of four
+// polynomials each and no reductions mod q afterwards.  Group g evaluates
+// polynomial 4 T + g of tile T; a tile whose z or r0 norm fails ends the
+// evaluation before its c t0, hints and packing (about 77% of the candidates
+// at level 2).  z is packed by OR-ing each strided coefficient's bits into the
+// signature: only passing tiles pay for it, and no transpose is needed.
+// Measured against the transforms it replaces (10,000 tasks, whole Sign call,
+// four-wavefront loop kernel): level 2 1470 to 1410 us, level 5 2799 to 2680 us;
+// staged form, level 3, 1000 tasks: 6996 to 6725 us.
+template <int LV>
 __device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctilde, const int32_t *y, const int32_t *w,
-                                          const int32_t *s1h, const int32_t *s2h, const int32_t *t0h,
-                                          CheckLds<LV> &lds, const TW &ftw, const TW &itw, int lane) {
+                                          const int8_t *sec, CheckLds<LV> &lds, int lane) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, BETA = Lv<LV>::BETA, OMEGA = Lv<LV>::OMEGA;
   constexpr int32_t G1 = Lv<LV>::GAMMA1, G2 = Lv<LV>::GAMMA2;
-  int g = lane >> 4, t = lane & 15;
-  int32_t *tr = lds.tr + g * NTT_LDS_GROUP;
+  static_assert(sizeof lds.sigbuf >= 512, "the build scratch lies in the signature buffer");
+  const int g = lane >> 4, t = lane & 15;
   uint8_t *sb = (uint8_t *)lds.sigbuf;
-  // c-hat, computed by every group
-  int32_t ch[16];
-#pragma unroll
-  for (int r = 0; r < 16; r++) ch[r] = c[t + 16 * r];
-  int32_t s1n[16], yn[16];
-  if constexpr (EARLY) {
-    if (g < L) {
-      load_slots(s1n, s1h + g * N, t);
-      load_strided(yn, y + g * N, t);
-    }
-  }
-  ntt16<TW, PAD>(ch, ftw, tr, t);
-  bool bad = false;
-  // z = y + c s1
-  for (int j = g; j < L; j += 4) {
-    int32_t s1[16], x[16], yv[16];
-    if constexpr (EARLY) {
+  v4i s[4];
+  toep_load(s, sec, lane);
+  toep_build(c, lds.ct, lds.sigbuf, lane);
+  for (int q = lane; q < (int)(sizeof lds.sigbuf / 4); q += 64) lds.sigbuf[q] = 0;
+  wave_sync();
+#pragma unroll 1
+  for (int T = 0; T < sec_tiles<LV>(); T++) {
+    const int p = 4 * T + g;
+    const bool hz = p < L, hr = p < K;
+    int32_t yv[16], wv[16];
+    if (hz) load_strided(yv, y + p * N, t);
+    if (hr) load_strided(wv, w + p * N, t);
+    v4i acc[16];
+    toep_mul(acc, s, lds.ct, lane);
+    if (T + 1 < sec_tiles<LV>()) toep_load(s, sec + (T + 1) * TILE_BYTES, lane);
+    // |z| < gamma1 - beta and |r0| < gamma2 - beta, as offset maxima
+    uint32_t zm = 0, rm = 0;
+    int32_t r1v[16];
+    if (hz) {
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        s1[r] = s1n[r];
-        yv[r] = yn[r];
+        yv[r] += acc[r][0];
+        zm = max(zm, (uint32_t)(yv[r] + (G1 - BETA - 1)));
       }
-      if (j + 4 < L) {
-        load_slots(s1n, s1h + (j + 4) * N, t);
-        load_strided(yn, y + (j + 4) * N, t);
+    }
+    if (hr) {
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        wv[r] = canon_near(wv[r] - acc[r][1]);
+        int32_t r0;
+        decompose<LV>(wv[r], r1v[r], r0);
+        rm = max(rm, (uint32_t)(r0 + (G2 - BETA - 1)));
       }
-    } else {
-      load_slots(s1, s1h + j * N, t);
     }
+    if (wave_any(zm > 2u * (G1 - BETA - 1) || rm > 2u * (G2 - BETA - 1))) return false;
+    bool bad = false;
+    if (hr) {
+      int cnt = 0;
 #pragma unroll
-    for (int r = 0; r < 16; r++) x[r] = mont_mul(ch[r], s1[r]);
-    intt16<TW, PAD>(x, itw, tr, t);
-    if constexpr (!EARLY) load_strided(yv, y + j * N, t);
-    int32_t zv[16];
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      int32_t z = yv[r] + canon(x[r]);             // in [-gamma1 + 1, q + gamma1)
-      z = z > (Q - 1) / 2 ? z - Q : z;             // centred
-      bad |= (z >= G1 - BETA) || (z <= -(G1 - BETA));
-      zv[r] = G1 - z;
+      for (int r = 0; r < 16; r++) {
+        const int32_t ct0 = acc[r][2] + 64 * acc[r][3];
+        bad |= (uint32_t)(ct0 + (G2 - 1)) > 2u * (G2 - 1);
+        const bool h = highbits<LV>(canon_near(wv[r] + ct0)) != r1v[r];
+        const uint64_t m = __ballot(h);
+        const uint32_t m16 = (uint32_t)(m >> (16 * g)) & 0xFFFFu;
+        if (t == 0) lds.hmask[p][r] = (uint16_t)m16;
+        cnt += __popc(m16);
+      }
+      if (t == 0) lds.rowcnt[p] = cnt;
     }
-    uint32_t v[16];
-    to_consecutive<PAD>(zv, v, tr, t);
-    pack16_to_lds<PP::ZBITS>(v, sb + PP::OFF_Z + j * PP::ZB, t);
+    if (wave_any(bad)) return false;
+    if (hz) {
+      // coefficient t + 16 r is the B-bit field at bit B t + 16 B r of row p, and 16 B r is a whole number of words
+      constexpr int B = PP::ZBITS;
+      uint32_t *zw = lds.sigbuf + (PP::OFF_Z + p * PP::ZB) / 4 + ((B * t) >> 5);
+      const int sh = (B * t) & 31;
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const uint64_t v = (uint64_t)(uint32_t)(G1 - yv[r]) << sh;
+        atomicOr(zw + r * (B / 2), (uint32_t)v);
+        if (sh + B > 32) atomicOr(zw + r * (B / 2) + 1, (uint32_t)(v >> 32));
+      }
+    }
   }
-  if (wave_any(bad)) return false;
-  // r0 = LowBits(w - c s2), c t0 and the hint
-  for (int i = g; i < K; i += 4) {
-    int32_t s2[16], x[16], u[16], wv[16];
-    load_slots(s2, s2h + i * N, t);
-    if constexpr (EARLY) {
-      load_strided(wv, w + i * N, t);
-      load_slots(u, t0h + i * N, t);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; r++) x[r] = mont_mul(ch[r], s2[r]);
-    intt16<TW, PAD>(x, itw, tr, t);
-    if constexpr (!EARLY) load_strided(wv, w + i * N, t);
-    int32_t r1v[16];
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      x[r] = canon(wv[r] - canon(x[r]));           // w - c s2, canonical
-      int32_t r1, r0;
-      decompose<LV>(x[r], r1, r0);
-      r1v[r] = r1;
-      bad |= (r0 >= G2 - BETA) || (r0 <= -(G2 - BETA));
-    }
-    if constexpr (!EARLY) load_slots(u, t0h + i * N, t);
-#pragma unroll
-    for (int r = 0; r < 16; r++) u[r] = mont_mul(ch[r], u[r]);
-    intt16<TW, PAD>(u, itw, tr, t);
-    int cnt = 0;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      int32_t ct0 = canon(u[r]);
-      bad |= norm_ge(ct0, G2);
-      int32_t sum = x[r] + ct0;
-      sum -= (sum >= Q) ? Q : 0;                   // w - c s2 + c t0, canonical
-      bool h = highbits<LV>(sum) != r1v[r];
-      uint64_t m = __ballot(h);
-      uint32_t m16 = (uint32_t)(m >> (16 * g)) & 0xFFFFu;
-      if (t == 0) lds.hmask[i][r] = (uint16_t)m16;
-      cnt += __popc(m16);
-    }
-    if (t == 0) lds.rowcnt[i] = cnt;
-  }
-  if (wave_any(bad)) return false;
   wave_sync();
   int total = 0;
   for (int i = 0; i < K; i++) total += lds.rowcnt[i];
   if (total > OMEGA) return false;
-  // accepted: ctilde and the hint bytes
+  // accepted: ctilde and the hint bytes (the buffer is zeroed)
   if (lane < PP::CT / 4) lds.sigbuf[lane] = ctilde[lane];
-  for (int b = lane; b < OMEGA + K; b += 64) sb[PP::OFF_H + b] = 0;
-  wave_sync();
   for (int i = g; i < K; i += 4) {
     int pre = 0;
     for (int i2 = 0; i2 < i; i2++) pre += lds.rowcnt[i2];
@@ -823,14 +807,13 @@ template <int LV>
 __global__ void __launch_bounds__(64) sg_check_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,
                                                  uint32_t *next_active) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
-  __shared__ CheckLds<LV> lds;
+  __shared__ __align__(16) CheckLds<LV> lds;
   if (blockIdx.x >= nactive) return;
   uint32_t task = active[blockIdx.x];
-  int lane = threadIdx.x, t = lane & 15;
-  const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
+  const int lane = threadIdx.x;
   bool ok = dev_check<LV>(ws.cpoly + (size_t)task * N, (const uint32_t *)(ws.ctilde + (size_t)task * CT_STRIDE),
-                          ws.y + (size_t)task * L * N, ws.w + (size_t)task * K * N, ws.s1h + kix(ws, task) * L * N,
-                          ws.s2h + kix(ws, task) * K * N, ws.t0h + kix(ws, task) * K * N, lds, ftw, itw, lane);
+                          ws.y + (size_t)task * L * N, ws.w + (size_t)task * K * N,
+                          ws.sec + kix(ws, task) * sec_bytes<LV>(), lds, lane);
   if (ok) {
     l2g_bytes(lds.sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
   } else if (lane == 0) {

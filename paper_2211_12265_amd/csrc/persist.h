@@ -138,10 +138,10 @@ struct PersistLds {
 // MAX_ATTEMPTS, [6..7] sequential iterations = sum over tasks of (winning
 // index + 1) (u64).  hmax: tasks a workgroup holds at a time (1..G).
 template <int LV>
-__global__ void __launch_bounds__(64) sg_persist_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count, uint32_t hmax,
+__global__ void __launch_bounds__(64, 2) sg_persist_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count, uint32_t hmax,
                                                    uint32_t *stats) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, G = PCfg<LV>::G;
-  __shared__ PersistLds<LV> lds;
+  __shared__ __align__(16) PersistLds<LV> lds;
   const int lane = threadIdx.x, t = lane & 15;
   const size_t wg = blockIdx.x;
   const ScratchIdx si = scratch_idx<LV>(G);
@@ -207,8 +207,7 @@ __global__ void __launch_bounds__(64) sg_persist_k(Ws ws, PScr sc, uint8_t *sig,
       if (lds.h_win[h] != SCHED_NONE) continue;
       uint32_t task = lds.h_task[h];
       bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + si.y(0, s, 0), wb + si.w(0, s, 0),
-                              ws.s1h + kix(ws, task) * L * N, ws.s2h + kix(ws, task) * K * N,
-                              ws.t0h + kix(ws, task) * K * N, lds.u.ck, ftw, itw, lane);
+                              ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.u.ck, lane);
       if (ok) {
         l2g_bytes(lds.u.ck.sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
         if (lane == 0) lds.h_win[h] = lds.s_att[s];
@@ -246,9 +245,9 @@ namespace dil {
 // range sched_wave_range(ns, 4, w): it runs ExpandMask for its own slots
 // (one lane per stream, at most 16 slots x 4 streams) and goes on to their w
 // phase after a fence of its own, with no workgroup barrier between the two,
-// and its w and check phases request their operands early (EARLY in
-// dev_compute_w / dev_check).  A task's candidates then follow one another on
-// one wavefront and reuse its A-hat and secrets from cache.  The registers
+// and its w phase requests its operands early (EARLY in dev_compute_w).  A
+// task's candidates then follow one another on one wavefront and reuse its
+// A-hat and secrets from cache.  The registers
 // this takes fit two wavefronts per SIMD at l = 4 only.
 // ---------------------------------------------------------------------------
 template <int LV, int NW>
@@ -331,14 +330,17 @@ __device__ __forceinline__ void copy_sig_row(const uint32_t *src, uint8_t *dst, 
 // (sched_slots), else full batches of G slots (tail is then 0).  TAIL is a
 // template switch so that the full-batch kernel keeps its register
 // allocation (two wavefronts per SIMD with no spills at every level).
+// The bound of two wavefronts per SIMD keeps the accumulators of dev_check in
+// the same 256 registers (left alone, the compiler adds 64 AGPRs to them and
+// the kernel falls to one wavefront per SIMD); no form spills.
 template <int LV, int NW, bool PAD = true, bool TAIL = false>
-__global__ void __launch_bounds__(64 * NW) sg_persistw_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count,
+__global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count,
                                                      uint32_t sched, uint32_t *stats) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, G = PCfgW<LV, NW>::G, W = NW;
   constexpr bool CONTIG = NW == 4 && L == 4 && PAD;  // contiguous slot ranges per wavefront
   static_assert(G <= 64, "the winner search takes one slot per lane");
   static_assert(!CONTIG || PCfgW<LV, NW>::GW * L <= 64, "a wavefront's own slots take one ExpandMask lane per stream");
-  __shared__ PersistWLds<LV, NW> lds;
+  __shared__ __align__(16) PersistWLds<LV, NW> lds;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, t = lane & 15;
   const size_t wg = blockIdx.x;
   const ScratchIdx si = scratch_idx<LV>(G);
@@ -428,9 +430,8 @@ __global__ void __launch_bounds__(64 * NW) sg_persistw_k(Ws ws, PScr sc, uint8_t
       // another wave may lower h_win meanwhile: read it once, wave-uniformly
       if (__builtin_amdgcn_readfirstlane(lds.h_win[h]) < lds.s_att[s]) continue;
       uint32_t task = lds.h_task[h];
-      bool ok = dev_check<LV, PAD, CONTIG>(lds.c[s], lds.ct[s], yb + si.y(0, s, 0), wb + si.w(0, s, 0),
-                              ws.s1h + kix(ws, task) * L * N, ws.s2h + kix(ws, task) * K * N,
-                              ws.t0h + kix(ws, task) * K * N, lds.u[wave].ck, ftw, itw, lane);
+      bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + si.y(0, s, 0), wb + si.w(0, s, 0),
+                              ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.u[wave].ck, lane);
       if (ok) {
         const uint32_t *sb = lds.u[wave].ck.sigbuf;
         uint32_t *dst = (uint32_t *)(stg + si.stage(0, s));

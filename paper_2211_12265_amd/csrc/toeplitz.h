@@ -1,0 +1,93 @@
+// Products by the challenge on the matrix cores.
+//
+// The challenge c has tau coefficients of +-1 and the polynomials it multiplies
+// (s1, s2, t0, t1) are small, so c p mod (X^256 + 1) fits 32-bit integers
+// exactly and needs no transform: coefficient i is sum_j T[i][j] p[j] with the
+// negacyclic Toeplitz matrix T[i][j] = c[i - j] (i >= j), -c[256 + i - j]
+// (i < j).  One wavefront multiplies T by 16 int8 rows at a time with
+// v_mfma_i32_16x16x64_i8 (D = rows x T^t, 64 instructions per 16 rows).
+//
+// Rows: a tile holds 16 int8 rows of 256; lane l's accumulator acc[I][r] is
+// coefficient 16 I + (l & 15) of row 4 (l >> 4) + r.  With rows 4 g + r = part
+// r of polynomial g, the 16-lane group g therefore receives all the parts of
+// its own polynomial in the strided layout of ntt.h (register I = coefficient
+// t + 16 I), next to y, w and the INTT's output.
+//
+// T in LDS: every fragment is a 16-byte window of f[m] = c[255 - m] (m < 256),
+// -c[511 - m] (m >= 256): lane (i, kg) of the block (I, J) needs f from
+// 15 - i + 16 u on, u = 4 J + kg - I + 15.  Copy i of f starts at byte 15 - i,
+// so that all windows are 16-byte aligned; copies are 132 words apart, which
+// spreads the 16 lanes of a group over all 64 banks.  Only w = 4 J - I matters
+// for the address: 28 reads feed the 64 products.
+#pragma once
+#include "common.h"
+#include "poly.h"
+
+namespace dil {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int TOEP_ROW = 132;              // words of one shifted copy: 31 windows of 16 bytes, padded
+constexpr int TOEP_WORDS = 16 * TOEP_ROW;  // one wavefront's copies
+
+// Build the 16 shifted copies from the dense challenge (256 int8, 4-byte
+// aligned, LDS or global) with one wavefront.  f: 128 words of LDS scratch.
+__device__ __forceinline__ void toep_build(const int8_t *c, uint32_t *ct, uint32_t *f, int lane) {
+  const uint32_t v = ((const uint32_t *)c)[lane];
+  const uint32_t rev = __builtin_amdgcn_perm(v, v, 0x00010203u);  // bytes reversed
+  f[63 - lane] = rev;
+  // bytes of {-1, 0, 1} negated: flip the upper seven bits of the non-zero ones
+  f[127 - lane] = rev ^ ((rev & 0x01010101u) * 0xFEu);
+  wave_sync();
+  const int i = lane & 15, q = lane >> 4, sh = (15 - i) & 3;
+  const uint32_t *src = f + 32 * q + ((15 - i) >> 2);
+  v4i *dst = (v4i *)(ct + i * TOEP_ROW + 32 * q);
+  uint32_t x = src[0];
+#pragma unroll
+  for (int u = 0; u < 8; u++) {  // windows 8 q .. 8 q + 7; the last group has seven
+    if (u < 7 || q < 3) {
+      v4i o;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        const uint32_t nx = src[4 * u + k + 1];
+        o[k] = (int)__builtin_amdgcn_alignbyte(nx, x, sh);
+        x = nx;
+      }
+      dst[u] = o;
+    }
+  }
+  wave_sync();
+}
+
+// the lane's part of a tile's 16 rows (rows 256 bytes apart, 16-byte aligned)
+__device__ __forceinline__ void toep_load(v4i s[4], const int8_t *tile, int lane) {
+  const int8_t *p = tile + (lane & 15) * N + 16 * (lane >> 4);
+#pragma unroll
+  for (int J = 0; J < 4; J++) s[J] = *(const v4i *)(p + 64 * J);
+}
+
+__device__ __forceinline__ void toep_mul(v4i acc[16], const v4i s[4], const uint32_t *ct, int lane) {
+  const uint32_t *row = ct + (lane & 15) * TOEP_ROW + 4 * (lane >> 4);
+#pragma unroll
+  for (int I = 0; I < 16; I++) acc[I] = v4i{0, 0, 0, 0};
+#pragma unroll
+  for (int w = -15; w <= 12; w++) {
+    const v4i b = *(const v4i *)(row + 4 * (w + 15));
+#pragma unroll
+    for (int J = 0; J < 4; J++) {
+      const int I = 4 * J - w;
+      if (I >= 0 && I < 16) acc[I] = __builtin_amdgcn_mfma_i32_16x16x64_i8(s[J], b, acc[I], 0, 0, 0);
+    }
+  }
+}
+
+// Tiles of the Sign secrets: part 0 = s1, 1 = s2, 2 / 3 = t0 = lo + 64 hi (lo
+// in [-32, 31], hi in [-64, 64]) of the tile's polynomials 4 T + g; absent
+// rows are zero.
+template <int LV>
+constexpr int sec_tiles() { return ((Lv<LV>::K > Lv<LV>::L ? Lv<LV>::K : Lv<LV>::L) + 3) / 4; }
+constexpr int TILE_BYTES = 16 * N;
+template <int LV>
+constexpr size_t sec_bytes() { return (size_t)sec_tiles<LV>() * TILE_BYTES; }
+
+}  // namespace dil
