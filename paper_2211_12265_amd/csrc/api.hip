@@ -11,7 +11,7 @@
 #include "errwords.h"
 #include "ntt_ablation.h"
 #include "t0_ablation.h"
-#include "persist.h"
+#include "rounds.h"
 #include "probe.h"
 
 using namespace dil;
@@ -59,8 +59,9 @@ struct dil_ctx {
   uint64_t clock = 0;
   int graph_hits = 0, graph_builds = 0;
   // side streams for independent setup stages (fork/join through events)
-  hipStream_t side[2] = {nullptr, nullptr};
-  hipEvent_t fork_ev = nullptr, join_ev[2] = {nullptr, nullptr};
+  static constexpr int SIDES = 2;
+  hipStream_t side[SIDES] = {};
+  hipEvent_t fork_ev = nullptr, join_ev[SIDES] = {};
   hipEvent_t done_ev = nullptr;                // recorded after each call's last enqueue
   uint8_t *scratch = nullptr;                  // this device's no-alloc scratch array (device address)
   int pool_alloc = 0;                          // workspace from the stream-ordered allocator
@@ -117,11 +118,45 @@ constexpr int lv_slot(int lv) { return lv == 2 ? 0 : lv == 3 ? 1 : lv == 5 ? 2 :
 
 // The kinds of call a workspace is laid out for: each carves only the
 // per-task rows its kernels read or write.
-enum WsForm { WS_KEYGEN = 0, WS_SIGN_STAGED = 1, WS_SIGN_PERSIST = 2, WS_VERIFY = 3 };
+enum WsForm { WS_KEYGEN = 0, WS_SIGN_STAGED = 1, WS_SIGN_PERSIST = 2, WS_VERIFY = 3, WS_SIGN_ROUNDS = 4 };
 
 template <int LV>
 constexpr int persist_slots(int waves) {
   return waves == 1 ? PCfg<LV>::G : waves * PCfg<LV>::G;
+}
+
+// ---- Sign in rounds: groups and rounds of a call ----
+// Groups of a call run one after another on the caller's stream: up to
+// ROUND_GROUP tasks (40 / 46 / 59 MB of scratch per 1,000 at l = 4 / 5 / 7) share
+// the launches of their rounds.  (Cutting 10,000 tasks into two to four groups
+// on streams of their own, so that one group's hashing would run beside
+// another's matrix work, measured 5-40% slower: the later rounds of a group are
+// latency-bound whatever its size.)
+constexpr uint32_t ROUND_GROUP = 16384;
+constexpr unsigned FINISH_GRID = 64;  // workgroups of the finishing launch
+struct RoundPlan {
+  uint32_t groups, size, cap;
+};
+inline RoundPlan round_plan(uint32_t count) {
+  RoundPlan p;
+  p.groups = (count + ROUND_GROUP - 1) / ROUND_GROUP;
+  p.size = (count + p.groups - 1) / p.groups;
+  p.cap = round_candidates(p.size);
+  return p;
+}
+// Rounds after which fewer than 1 in 50 groups is expected to hold an unsigned
+// task, at the mean iteration counts of Sec. 2.3 (4.25 / 5.1 / 3.85).
+template <int LV>
+int round_count(uint32_t n) {
+  constexpr double fail = 1.0 - 1.0 / (Lv<LV>::L == 4 ? 4.25 : Lv<LV>::L == 5 ? 5.1 : 3.85);
+  double left = n;
+  int r = 0;
+  while (r < ROUNDS_MAX && left > 0.02) {
+    const uint32_t m = round_nonces((uint32_t)std::max(1.0, left));
+    for (uint32_t k = 0; k < m; k++) left *= fail;
+    r++;
+  }
+  return r;
 }
 
 // Lay out the workspace of a call of `cap` tasks at `base` (nullptr: only
@@ -131,9 +166,10 @@ constexpr int persist_slots(int waves) {
 // for `grid` workgroups of `waves` wavefronts.
 template <int LV>
 size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, int waves, Ws *ws, PScr *sc,
-                 uint32_t **kidx) {
+                 uint32_t **kidx, Group *group = nullptr) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
-  const bool sign = form == WS_SIGN_STAGED || form == WS_SIGN_PERSIST, staged = form == WS_SIGN_STAGED;
+  const bool rounds = form == WS_SIGN_ROUNDS;
+  const bool sign = form == WS_SIGN_STAGED || form == WS_SIGN_PERSIST || rounds, staged = form == WS_SIGN_STAGED;
   size_t off = 0;
   auto take = [&](bool used, size_t bytes) -> uint8_t * {
     if (!used) return nullptr;
@@ -153,7 +189,7 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.A = (int32_t *)take(!keyset, cap * K * L * 1024);
   w.s12 = (int32_t *)take(form == WS_KEYGEN, cap * (L + K) * 1024);
   w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
-  w.y = (int32_t *)take(staged, cap * L * 1024);
+  w.y = take(staged, cap * L * P<LV>::YB);
   w.w = (int32_t *)take(staged, cap * K * 1024);
   w.hmask = (uint32_t *)take(form == WS_VERIFY, cap * K * 32);
   w.flag = (int32_t *)take(form == WS_VERIFY, cap * 4);
@@ -165,10 +201,29 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   if (form == WS_SIGN_PERSIST) {
     // the regions the loop kernels index with the same ScratchIdx (batch_sched.h)
     const ScratchIdx si{(size_t)persist_slots<LV>(waves), (size_t)L, (size_t)K, w1_stride<LV>(), sig_stride<LV>()};
-    p.y = (int32_t *)take(true, si.y_size(grid) * sizeof(int32_t));
+    p.y = take(true, si.y_size(grid) / N * P<LV>::YB);
     p.w = (int32_t *)take(true, si.w_size(grid) * sizeof(int32_t));
     p.w1 = take(true, si.w1_size(grid));
     p.stage = take(waves > 1, si.stage_size(grid));
+  }
+  if (rounds) {
+    // the finishing launch of a group uses the candidates' memory for its batches
+    const RoundPlan rp = round_plan((uint32_t)cap);
+    uint32_t *cnt = (uint32_t *)take(true, (size_t)rp.groups * ROUND_WORDS * 4);
+    const ScratchIdx si{(size_t)persist_slots<LV>(4), (size_t)L, (size_t)K, w1_stride<LV>(), sig_stride<LV>()};
+    // sized for the largest group a smaller call could have, so that a reservation covers it
+    const uint32_t gmax = (uint32_t)std::min<size_t>(cap, ROUND_GROUP);
+    const size_t fg = std::min<size_t>(FINISH_GRID, gmax), cands = round_candidates(gmax);
+    Group g{};
+    g.cap = rp.cap;
+    g.cnt = cnt;
+    for (uint32_t *&l : g.list) l = (uint32_t *)take(true, (size_t)gmax * 4);
+    g.y = take(true, std::max(cands * L, si.y_size(fg) / N) * P<LV>::YB);
+    g.w = (int32_t *)take(true, std::max(cands * K * N, si.w_size(fg)) * sizeof(int32_t));
+    g.w1 = take(true, std::max(cands * K * P<LV>::W1B, si.w1_size(fg)));
+    g.ct = take(true, cands * CT_STRIDE);
+    g.c = (int8_t *)take(true, std::max(cands * N, si.stage_size(fg)));
+    if (group) *group = g;
   }
   if (ws) *ws = w;
   if (sc) *sc = p;
@@ -211,11 +266,11 @@ int ws_reserve_bytes(dil_ctx *ctx, size_t need, hipStream_t st) {
 
 template <int LV>
 int ws_carve(dil_ctx *ctx, hipStream_t st, size_t cap, int form, bool keyset, Ws &ws, size_t grid = 0,
-             PScr *sc = nullptr, int waves = 1, uint32_t **kidx = nullptr) {
+             PScr *sc = nullptr, int waves = 1, uint32_t **kidx = nullptr, Group *group = nullptr) {
   const size_t need = ws_layout<LV>(nullptr, cap, form, keyset, grid, waves, nullptr, nullptr, nullptr);
   int rc = ws_reserve_bytes(ctx, need, st);
   if (rc) return rc;
-  const size_t got = ws_layout<LV>((uint8_t *)ctx->ws_mem, cap, form, keyset, grid, waves, &ws, sc, kidx);
+  const size_t got = ws_layout<LV>((uint8_t *)ctx->ws_mem, cap, form, keyset, grid, waves, &ws, sc, kidx, group);
   if (got > ctx->ws_bytes) return fail(ctx, DIL_ENOMEM, "workspace layout overflow");
   ws.kmap = nullptr;
   ws.t1h = nullptr;
@@ -282,17 +337,22 @@ int enqueue(dil_ctx *ctx, const uint64_t *key, hipStream_t st, F fn) {
   return DIL_OK;
 }
 
-// Fork: side streams wait for everything enqueued on st so far.
-int fork_side(dil_ctx *ctx, hipStream_t st) {
-  if (!ctx->side[0]) {
-    for (int i = 0; i < 2; i++) {
+// The first n side streams and the fork / join events.
+int make_side(dil_ctx *ctx, int n) {
+  if (!ctx->fork_ev) HIPCHK(ctx, hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
+  for (int i = 0; i < n; i++)
+    if (!ctx->side[i]) {
       HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->side[i], hipStreamNonBlocking));
       HIPCHK(ctx, hipEventCreateWithFlags(&ctx->join_ev[i], hipEventDisableTiming));
     }
-    HIPCHK(ctx, hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
-  }
+  return DIL_OK;
+}
+// Fork: the first n side streams wait for everything enqueued on st so far.
+int fork_side(dil_ctx *ctx, hipStream_t st, int n = 2) {
+  int rc = make_side(ctx, n);
+  if (rc) return rc;
   HIPCHK(ctx, hipEventRecord(ctx->fork_ev, st));
-  for (int i = 0; i < 2; i++) HIPCHK(ctx, hipStreamWaitEvent(ctx->side[i], ctx->fork_ev, 0));
+  for (int i = 0; i < n; i++) HIPCHK(ctx, hipStreamWaitEvent(ctx->side[i], ctx->fork_ev, 0));
   return DIL_OK;
 }
 // Join: st waits for the work enqueued so far on side stream i.
@@ -301,9 +361,9 @@ int join_one(dil_ctx *ctx, hipStream_t st, int i) {
   HIPCHK(ctx, hipStreamWaitEvent(st, ctx->join_ev[i], 0));
   return DIL_OK;
 }
-// Join: st waits for both side streams' work.
-int join_side(dil_ctx *ctx, hipStream_t st) {
-  for (int i = 0; i < 2; i++) {
+// Join: st waits for the first n side streams' work.
+int join_side(dil_ctx *ctx, hipStream_t st, int n = 2) {
+  for (int i = 0; i < n; i++) {
     int rc = join_one(ctx, st, i);
     if (rc) return rc;
   }
@@ -311,6 +371,19 @@ int join_side(dil_ctx *ctx, hipStream_t st) {
 }
 
 inline unsigned blocks_for(uint64_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
+
+// Verify's last kernel: a row or a lane pair per task
+template <int LV>
+void launch_vf_final(hipStream_t st, const uint8_t *sig, const Ws &ws, int32_t *verdict, uint32_t count) {
+  if (count <= ROW_STATES) vf_final_row_k<LV><<<blocks_for(count, 4), 64, 0, st>>>(sig, ws, verdict, count);
+  else vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, st>>>(sig, ws, verdict, count);
+}
+// tr = H(pk) of every row: a row or a lane pair per key
+template <int LV>
+void launch_tr(hipStream_t st, const uint8_t *pk, uint8_t *out, size_t stride, uint32_t count) {
+  if (count <= ROW_STATES) tr_row_k<LV><<<blocks_for(count, 4), 64, 0, st>>>(pk, out, stride, count);
+  else tr_pair_k<LV><<<blocks_for(2 * (uint64_t)count, 64), 64, 0, st>>>(pk, out, stride, count);
+}
 
 template <int LV>
 int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, uint32_t count, hipStream_t st) {
@@ -322,7 +395,7 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
   expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, st>>>(pk, P<LV>::PK, nullptr, ws.A, count);
   expand_s_k<LV><<<blocks_for((uint64_t)count * (K + L), 256), 256, 0, st>>>(ws, count);
   kg_main_k<LV><<<count, 64, 0, st>>>(ws, pk, sk, count);
-  kg_tr_k<LV><<<blocks_for(count, 256), 256, 0, st>>>(pk, sk, count);
+  launch_tr<LV>(st, pk, sk + 64, P<LV>::SK, count);
   LAUNCHCHK(ctx);
   return mark_done(ctx, st);
 }
@@ -346,6 +419,33 @@ void check_keys(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, uin
     keys_check_k<<<blocks_for(count, 256), 256, 0, st>>>(key_idx, ks->nkeys, checked, count, ctx->dev_stats + 9);
 }
 
+// mu and the mask seeds in the context's message form; on a row per task as
+// long as that takes at most one wavefront per SIMD
+template <int LV>
+void launch_prep(const dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
+                 const uint64_t *msg_off, const uint8_t *rnd, const Ws &ws, uint32_t count, uint32_t *err,
+                 hipStream_t st) {
+  const unsigned nb = blocks_for(2 * (uint64_t)count, 256);
+  if (count <= ROW_STATES) {
+    const unsigned rb = blocks_for(count, 4);
+    if constexpr (Lv<LV>::MLDSA) {
+      if (ctx->mldsa_internal) {
+        sg_prep_row_k<LV, true><<<rb, 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+        return;
+      }
+    }
+    sg_prep_row_k<LV><<<rb, 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+    return;
+  }
+  if constexpr (Lv<LV>::MLDSA) {
+    if (ctx->mldsa_internal) {
+      sg_prep_k<LV, true><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+      return;
+    }
+  }
+  sg_prep_k<LV><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+}
+
 // The setup stages are independent of each other: mu/rho' hash chains (one lane
 // per task, latency-bound for small batches), ExpandA (one lane per stream) and
 // the secrets' unpacking (one wave per key).  With `concurrent` they run on the
@@ -360,13 +460,7 @@ int sign_setup(dil_ctx *ctx, Ws &ws, const uint8_t *sk, const uint32_t *key_idx,
     int rc = fork_side(ctx, st);
     if (rc) return rc;
   }
-  const unsigned nb = blocks_for(2 * (uint64_t)count, 256);
-  bool internal = false;
-  if constexpr (Lv<LV>::MLDSA) internal = ctx->mldsa_internal;
-  if constexpr (Lv<LV>::MLDSA) {
-    if (internal) sg_prep_k<LV, true><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
-  }
-  if (!internal) sg_prep_k<LV><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+  launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, err, st);
   if (!ks) {
     hipStream_t s1 = concurrent ? ctx->side[0] : st, s2 = concurrent ? ctx->side[1] : st;
     expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, s1>>>(sk, P<LV>::SK, key_idx, ws.A, count);
@@ -472,10 +566,116 @@ int persist_schedule(dil_ctx *ctx, uint32_t count, uint64_t *grid_out, uint64_t 
   return DIL_OK;
 }
 
+// The automatic form of DIL_MODE_PERSISTENT: with no "persist.*" knob set, a
+// call runs in rounds (rounds.h); a schedule asked for runs the loop kernel.
+inline bool sign_in_rounds(const dil_ctx *ctx) {
+  return ctx->mode == DIL_MODE_PERSISTENT && ctx->persist_waves == 4 && ctx->persist_pad && ctx->persist_grid <= 0 &&
+         ctx->persist_hmax <= 0 && ctx->persist_tail < 0;
+}
+
+// Round 0 has its exact size; later ones at most as many tasks and cap candidates.
+inline uint32_t launch_candidates(const Group &gr, int r) { return r == 0 ? gr.n * round_nonces(gr.n) : gr.cap; }
+// ExpandMask of a round (it needs the mask seeds only).
+template <int LV>
+void launch_mask(const Ws &ws, const Group &gr, int r, hipStream_t s) {
+  const uint64_t streams = (uint64_t)launch_candidates(gr, r) * Lv<LV>::L;
+  rd_mask_k<LV><<<mask_blocks(streams, r == 0), 256, 0, s>>>(ws, gr, r);
+}
+// The rest of the round.
+template <int LV>
+void launch_round(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int r, hipStream_t s) {
+  const uint32_t cand = launch_candidates(gr, r);
+  const uint32_t wgs = r == 0 && round_nonces(gr.n) <= ROUND_SEQ ? blocks_for(gr.n, 4) : gr.n;
+  rd_w_k<LV><<<blocks_for(cand, 4), 256, 0, s>>>(ws, gr, r);
+  rd_chal_k<LV><<<chal_blocks(cand), 64, 0, s>>>(ws, gr, r);
+  rd_check_k<LV><<<wgs, 256, 0, s>>>(ws, gr, sig, r, ctx->dev_stats);
+}
+// The finishing launch after `rounds` rounds.
+template <int LV>
+void launch_finish(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int rounds, hipStream_t s) {
+  PScr sc;
+  sc.y = gr.y;
+  sc.w = gr.w;
+  sc.w1 = gr.w1;
+  sc.stage = (uint8_t *)gr.c;
+  const Resume rs{gr.list[rounds & 1], gr.cnt, gr.cnt + ROUNDS_MAX + 1, gr.n, rounds};
+  constexpr uint32_t HELD = 4, TAIL_SLOTS = 20;
+  sg_persistw_k<LV, 4, true, true, true><<<std::min<unsigned>(FINISH_GRID, gr.n), 256, 0, s>>>(
+      ws, sc, sig, 0, HELD | TAIL_SLOTS << 8, ctx->dev_stats, rs);
+}
+
+// mu / rho' and the rounds on the caller's stream; ExpandA of all tasks runs on
+// a side stream beside the hashes, the secrets and the first group's masks and
+// is joined before the first w kernel.
+template <int LV>
+int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
+                uint8_t *sig, uint32_t count, hipStream_t st, const dil_keyset *ks, const uint8_t *rnd) {
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
+  Ws ws;
+  uint32_t *kid = nullptr;
+  Group base;
+  int rc = ws_carve<LV>(ctx, st, count, WS_SIGN_ROUNDS, ks != nullptr, ws, 0, nullptr, 4, &kid, &base);
+  if (rc) return rc;
+  const RoundPlan rp = round_plan(count);
+  const uint32_t *key_in = key_idx;
+  if (ks) key_idx = use_keyset(ws, ks, key_idx, kid);
+  auto group = [&](uint32_t g) {
+    Group gr = base;
+    gr.first = g * rp.size;
+    gr.n = std::min(rp.size, count - gr.first);
+    gr.cnt += (size_t)g * ROUND_WORDS;
+    return gr;
+  };
+  uint64_t key[16] = {3, (uint64_t)LV, (uint64_t)sk, (uint64_t)key_in, (uint64_t)msg, (uint64_t)msg_off,
+                      (uint64_t)sig, count, (uint64_t)ks, 0, 0, (uint64_t)ctx->ws_mem, 0, 4,
+                      (uint64_t)rnd, (uint64_t)ctx->mldsa_internal};
+  hipEvent_t *evs = ctx->timing ? ctx->ev[ctx->ev_count % dil_ctx::RING] : nullptr;
+  if (evs) HIPCHK(ctx, hipEventRecord(evs[0], st));
+  rc = enqueue(ctx, key, st, [&](hipStream_t s) {
+    zero_words_k<<<1, 256, 0, s>>>(base.cnt, (int)(rp.groups * ROUND_WORDS), ctx->dev_stats, 8);
+    check_keys(ctx, ks, key_in, kid, count, s);
+    if (!ks) {
+      int r2 = fork_side(ctx, s, 1);
+      if (r2) return r2;
+      expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, ctx->side[0]>>>(sk, P<LV>::SK, key_idx,
+                                                                                         ws.A, count);
+    }
+    launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, ctx->dev_stats + 8, s);
+    launch_mask<LV>(ws, group(0), 0, s);
+    if (!ks) {
+      sg_secret_k<LV><<<count, 64, 0, s>>>(sk, key_idx, ws, count);
+      int r2 = join_side(ctx, s, 1);
+      if (r2) return r2;
+    }
+    LAUNCHCHK(ctx);
+    return DIL_OK;
+  });
+  if (rc) return rc;
+  if (evs) HIPCHK(ctx, hipEventRecord(evs[1], st));
+  for (uint32_t g = 0; g < rp.groups && (uint64_t)g * rp.size < count; g++) {
+    const Group gr = group(g);
+    const int rounds = round_count<LV>(gr.n);
+    for (int r = 0; r < rounds; r++) {
+      if (g + r > 0) launch_mask<LV>(ws, gr, r, st);
+      launch_round<LV>(ctx, ws, gr, sig, r, st);
+    }
+    launch_finish<LV>(ctx, ws, gr, sig, rounds, st);
+  }
+  LAUNCHCHK(ctx);
+  if (evs) {
+    HIPCHK(ctx, hipEventRecord(evs[2], st));
+    ctx->ev_count++;
+  }
+  ctx->last_stream = st;
+  ctx->stats_pending = 1;
+  return mark_done(ctx, st);
+}
+
 template <int LV>
 int sign_persistent(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
                     const uint64_t *msg_off, uint8_t *sig, uint32_t count, hipStream_t st,
                     const dil_keyset *ks = nullptr, const uint8_t *rnd = nullptr) {
+  if (sign_in_rounds(ctx)) return sign_rounds<LV>(ctx, sk, key_idx, msg, msg_off, sig, count, st, ks, rnd);
   const int waves = ctx->persist_waves;
   if (!ctx->persist_pad && waves != 4)
     return fail(ctx, DIL_EINVAL, "persist.pad = 0 exists for the four-wavefront loop kernel only");
@@ -515,17 +715,17 @@ int sign_persistent(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, co
   const bool tail = ntail > 0;
   const uint32_t sched = (uint32_t)hmax | (uint32_t)ntail << 8;  // hmax <= G <= 64, tail <= 64
   if constexpr (Lv<LV>::MLDSA) {
-    if (tail) sg_persistw_k<LV, 4, true, true><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
-    else sg_persistw_k<LV, 4><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
+    if (tail) sg_persistw_k<LV, 4, true, true><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
+    else sg_persistw_k<LV, 4><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
   } else {
     if (waves == 4 && !ctx->persist_pad)
-      sg_persistw_k<LV, 4, false><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
+      sg_persistw_k<LV, 4, false><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
     else if (waves == 4 && tail)
-      sg_persistw_k<LV, 4, true, true><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
+      sg_persistw_k<LV, 4, true, true><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
     else if (waves == 4)
-      sg_persistw_k<LV, 4><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
+      sg_persistw_k<LV, 4><<<(unsigned)grid, 256, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
     else if (waves == 2)
-      sg_persistw_k<LV, 2><<<(unsigned)grid, 128, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats);
+      sg_persistw_k<LV, 2><<<(unsigned)grid, 128, 0, st>>>(ws, sc, sig, count, sched, ctx->dev_stats, Resume{});
     else
       sg_persist_k<LV><<<(unsigned)grid, 64, 0, st>>>(ws, sc, sig, count, (uint32_t)hmax, ctx->dev_stats);
   }
@@ -544,6 +744,17 @@ template <int LV>
 void launch_vf_hash(const dil_ctx *ctx, hipStream_t st, const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
                     const uint64_t *msg_off, const Ws &ws, uint32_t count, uint32_t *err) {
   const unsigned nb = blocks_for(2 * (uint64_t)count, 64);
+  if (count <= ROW_STATES) {
+    const unsigned rb = blocks_for(count, 4);
+    if constexpr (Lv<LV>::MLDSA) {
+      if (ctx->mldsa_internal) {
+        vf_hash_row_k<LV, true><<<rb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+        return;
+      }
+    }
+    vf_hash_row_k<LV><<<rb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+    return;
+  }
   if constexpr (Lv<LV>::MLDSA) {
     if (ctx->mldsa_internal) {
       vf_hash_k<LV, true><<<nb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
@@ -596,7 +807,7 @@ int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const 
       int r2 = join_one(ctx, s, 1);
       if (r2) return r2;
     }
-    vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, s>>>(sig, ws, verdict, count);
+    launch_vf_final<LV>(s, sig, ws, verdict, count);
     LAUNCHCHK(ctx);
     return DIL_OK;
   });
@@ -650,7 +861,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   }
   if (pk) {
     ks_pk_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->pk, ks->t1h, ks->nkeys);
-    ks_tr_k<LV><<<blocks_for(n, 256), 256, 0, st>>>(ks->pk, ks->tr, ks->nkeys);
+    launch_tr<LV>(st, ks->pk, ks->tr, PP::TRB, ks->nkeys);
   } else {
     HIPCHK(ctx, hipMemcpy2DAsync(ks->tr, PP::TRB, ks->sk + 64, PP::SK, PP::TRB, n, hipMemcpyDeviceToDevice, st));
   }
@@ -766,7 +977,7 @@ int dil_ctx_destroy(dil_ctx *ctx) {
   if (ctx->dev_stats) hipFree(ctx->dev_stats);
   drop_graphs(ctx);
   if (ctx->cap_stream) hipStreamDestroy(ctx->cap_stream);
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < dil_ctx::SIDES; i++) {
     if (ctx->side[i]) hipStreamDestroy(ctx->side[i]);
     if (ctx->join_ev[i]) hipEventDestroy(ctx->join_ev[i]);
   }
@@ -973,7 +1184,7 @@ int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_
   launch_vf_hash<LV>(ctx, st, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG);
   vf_prep_k<LV><<<blocks_for(count, 64), 64, 0, st>>>(sig, ws, count);
   vf_main_k<LV><<<count, 64, 0, st>>>(ks->pk, kidx, sig, ws, count);
-  vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, st>>>(sig, ws, verdict, count);
+  launch_vf_final<LV>(st, sig, ws, verdict, count);
   LAUNCHCHK(ctx);
   return DIL_OK;
 }
@@ -1027,6 +1238,8 @@ int call_bytes(dil_ctx *ctx, int op, bool keyset, uint32_t count, bool upto, siz
     *bytes = ws_layout<LV>(nullptr, count, WS_VERIFY, keyset, 0, 1, nullptr, nullptr, nullptr);
   } else if (op == DIL_OP_SIGN && ctx->mode == DIL_MODE_STAGED) {
     *bytes = ws_layout<LV>(nullptr, count, WS_SIGN_STAGED, keyset, 0, 1, nullptr, nullptr, nullptr);
+  } else if (op == DIL_OP_SIGN && sign_in_rounds(ctx)) {
+    *bytes = ws_layout<LV>(nullptr, count, WS_SIGN_ROUNDS, keyset, 0, 4, nullptr, nullptr, nullptr);  // grows with count
   } else if (op == DIL_OP_SIGN) {
     uint64_t grid = 1, hmax = 1;
     int rc = persist_schedule<LV>(ctx, count, &grid, &hmax);

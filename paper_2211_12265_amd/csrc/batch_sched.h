@@ -132,6 +132,37 @@ DIL_HD int sched_retire(int nh, uint32_t *h_task, uint32_t *h_next, const uint32
   return o;
 }
 
+// Sign in rounds (rounds.h).  Round r evaluates the same number m of
+// consecutive nonces for every task of a group that is still unsigned:
+// ROUND_KNEE candidates' worth, but ROUND_NONCES_MIN .. ROUND_NONCES_MAX per
+// task.  cnt[r] is the number of unfinished tasks at the start of round r > 0
+// (n0 at the start of round 0), so that every kernel derives the round's
+// layout from the counts alone.
+constexpr uint32_t ROUND_NONCES_MIN = 4, ROUND_NONCES_MAX = 64, ROUND_KNEE = 8192;
+DIL_HD uint32_t round_nonces(uint32_t n) {
+  if (n == 0) return 0;
+  const uint32_t m = ROUND_KNEE / n;
+  return m < ROUND_NONCES_MIN ? ROUND_NONCES_MIN : m > ROUND_NONCES_MAX ? ROUND_NONCES_MAX : m;
+}
+// most candidates that a round of at most n tasks evaluates
+DIL_HD uint32_t round_candidates(uint32_t n) {
+  const uint64_t lo = (uint64_t)n * ROUND_NONCES_MIN, hi = (uint64_t)n * ROUND_NONCES_MAX;
+  const uint64_t mid = hi < ROUND_KNEE ? hi : ROUND_KNEE;
+  return (uint32_t)(lo > mid ? lo : mid);
+}
+struct RoundState {
+  uint32_t n, m, first;  // unfinished tasks, nonces per task, first nonce index of the round
+};
+DIL_HD RoundState round_state(const uint32_t *cnt, uint32_t n0, int r) {
+  RoundState st{n0, round_nonces(n0), 0};
+  for (int i = 1; i <= r; i++) {
+    st.first += st.m;
+    st.n = cnt[i];
+    st.m = round_nonces(st.n);
+  }
+  return st;
+}
+
 // Element offsets into the persistent kernels' scratch (one region of G slots
 // per workgroup; N = 256 coefficients per polynomial).  The workspace carves
 // grid * G * L * N words for y, grid * G * K * N for w, grid * G * w1_stride

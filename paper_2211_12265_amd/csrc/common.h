@@ -95,6 +95,7 @@ template <int LV> struct P : Lv<LV> {
   static constexpr int EBITS = B::ETA == 2 ? 3 : 4;
   static constexpr int M_HB = (Q - 1) / (2 * B::GAMMA2);            // number of HighBits values
   static constexpr int ZB = N * ZBITS / 8;                           // packed z poly
+  static constexpr int YB = N * ZBITS / 8;                           // one mask polynomial as squeezed
   static constexpr int W1B = N * W1BITS / 8;                         // packed w1 poly
   static constexpr int EB = N * EBITS / 8;                           // packed eta poly
   static constexpr int T1B = 320, T0B = 416;

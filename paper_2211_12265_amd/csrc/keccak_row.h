@@ -1,0 +1,373 @@
+// Keccak-f[1600] with one state on a 16-lane DPP row, for hash chains that have
+// the chip to themselves (small batches, the last rounds of Sign): what counts
+// there is the length of one permutation, and a lone wavefront issues one
+// instruction per five cycles whatever its lanes hold.
+//
+// Lane l of the row holds half h = l & 1 (low / high 32 bits) of the words of
+// sheet x = (l mod 10) / 2, register y the word (x, y); lanes 10 .. 15 repeat
+// x = 0, 1, 2, so that neighbouring sheets are a lane shift away:
+//   theta  column parity in the lane, C[x - 1] and C[x + 1] from lanes l -+ 2
+//          (lanes 10, 11 take C[1] from lanes 2, 3), the rotation's other half
+//          from the neighbour lane;
+//   rho, pi  the five words go through LDS: every lane reads back, for its new
+//          place, the two halves in the order in which one v_alignbit with the
+//          word's own amount rotates them;
+//   chi    the next two sheets from lanes l + 2, l + 4.
+// After chi lanes 0 .. 11 are valid, after theta lanes 2 .. 11, which hold every
+// sheet once and are the ones whose words are kept; the read-back makes all 16
+// valid again.  34 VALU and 15 LDS instructions per round against 120 VALU on a
+// lane pair (keccak_pair.h): 3.4 times the issue slots per state, half the time
+// per permutation of a lone wavefront.
+#pragma once
+#include "kernels.h"
+
+namespace dil {
+
+constexpr int ROW_LDS = 256;  // words of LDS per wavefront: four states of 50 words and a dump for unkept words
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+
+// rotation amounts of the words that land in register y of sheets 0 .. 4, six bits each
+constexpr uint32_t row_rot(int y) {
+  uint32_t v = 0;
+  for (int x = 0; x < 5; x++) v |= (uint32_t)kc_rho((3 * y + x) % 5 + 5 * x) << (6 * x);
+  return v;
+}
+template <int Y>
+struct RowRot {
+  static constexpr uint32_t v = row_rot(Y);
+};
+
+// the lane's constants; L: the wavefront's ROW_LDS words
+struct RowKeccak {
+  uint32_t *L;
+  int x, h;
+  int st;               // the state's words in L
+  int wr;               // where the lane keeps word (x, 0); (x, y) is 10 y further
+  int p[5], q[5];       // high and low operand of the rotation that yields word (x, y)
+  uint32_t s[5];        // its amount
+  uint32_t mlo, mhi;    // lanes that take the round constant's halves
+  __device__ __forceinline__ RowKeccak(uint32_t *lds, int lane) {
+    L = lds;
+    const int l = lane & 15, m = l < 10 ? l : l - 10;
+    x = m >> 1;
+    h = m & 1;
+    st = 50 * ((lane >> 4) & 3);
+    wr = l >= 2 && l < 12 ? st + 2 * x + h : 200;
+    place<0>();
+    place<1>();
+    place<2>();
+    place<3>();
+    place<4>();
+    mlo = x == 0 && h == 0 ? ~0u : 0u;
+    mhi = x == 0 && h == 1 ? ~0u : 0u;
+  }
+  // where register Y is read from: word (sx, sy) with (x, Y) = (sy, 2 sx + 3 sy)
+  template <int Y>
+  __device__ __forceinline__ void place() {
+    int sx = (3 * Y) % 5 + x;
+    sx = sx >= 5 ? sx - 5 : sx;
+    const int n = (int)((RowRot<Y>::v >> (6 * x)) & 63u);
+    const int mine = st + 2 * (sx + 5 * x) + h, other = mine + 1 - 2 * h;
+    p[Y] = n > 32 ? other : mine;
+    q[Y] = n == 0 || n > 32 ? mine : other;
+    s[Y] = (uint32_t)-n & 31u;  // 32 - n, 64 - n, or 0
+  }
+  // 8-byte word index of register y, and the 32-bit word of it that this lane holds
+  __device__ __forceinline__ int word(int y) const { return 5 * y + x; }
+  __device__ __forceinline__ int half_word(int y) const { return 2 * word(y) + h; }
+};
+
+__device__ __forceinline__ void keccak_f_row(uint32_t a[5], const RowKeccak &k) {
+#pragma unroll 1
+  for (int ir = 0; ir < 24; ir++) {
+    const uint32_t c = xor3(xor3(a[0], a[1], a[2]), a[3], a[4]);
+    const uint32_t cm = row_dpp<0x112>(c);  // lane l - 2
+    // lane l + 2; lanes 8 .. 11 from lane l - 8
+    const uint32_t cp =
+        (uint32_t)__builtin_amdgcn_update_dpp((int)row_dpp<0x102>(c), (int)c, 0x118, 0xF, 0x4, false);
+    const uint32_t r = __builtin_amdgcn_alignbit(cp, pair_swap(cp), 31);
+#pragma unroll
+    for (int y = 0; y < 5; y++) k.L[k.wr + 10 * y] = xor3(a[y], cm, r);
+    wave_sync();
+    uint32_t b[5];
+#pragma unroll
+    for (int y = 0; y < 5; y++) b[y] = __builtin_amdgcn_alignbit(k.L[k.p[y]], k.L[k.q[y]], k.s[y]);
+    wave_sync();
+#pragma unroll
+    for (int y = 0; y < 5; y++) a[y] = chi3(b[y], row_dpp<0x102>(b[y]), row_dpp<0x104>(b[y]));
+    a[0] ^= (kKRC.lo[ir] & k.mlo) ^ (kKRC.hi[ir] & k.mhi);
+  }
+}
+
+// SHAKE256 absorption of a LEN-byte string (LEN a multiple of 8) given by its
+// 32-bit words: word(i) is called for 4 i < LEN only.  The next block's words
+// are requested before the current one is permuted.
+template <int LEN, class W>
+__device__ __forceinline__ void shake256_absorb_row(uint32_t a[5], const RowKeccak &k, W word) {
+  static_assert(LEN % 8 == 0, "whole 8-byte words");
+  constexpr int RATE = 136, NBLK = LEN / RATE + 1;
+  auto fetch = [&](uint32_t v[4], int blk) {
+#pragma unroll
+    for (int y = 0; y < 4; y++) {
+      const int w = k.word(y), pos = blk * RATE + 8 * w;
+      v[y] = w < RATE / 8 && pos < LEN ? word(blk * (RATE / 4) + k.half_word(y)) : 0u;
+      if (w < RATE / 8 && pos == LEN && !k.h) v[y] = 0x1Fu;                     // suffix 1111 + first pad bit
+      if (w == RATE / 8 - 1 && blk == NBLK - 1 && k.h) v[y] ^= 0x80u << 24;     // last pad bit
+    }
+  };
+#pragma unroll
+  for (int y = 0; y < 5; y++) a[y] = 0;
+  uint32_t v[4];
+  fetch(v, 0);
+#pragma unroll 1
+  for (int blk = 0; blk < NBLK; blk++) {
+#pragma unroll
+    for (int y = 0; y < 4; y++) a[y] ^= v[y];
+    if (blk + 1 < NBLK) fetch(v, blk + 1);
+    keccak_f_row(a, k);
+  }
+}
+
+// SHAKE256 absorption of X = prefix || M (msg_words.h): pre[y] is the lane's
+// prefix word of register y where word(y) < PB / 8.
+template <int PB>
+__device__ __forceinline__ void absorb_prefix_msg_row(uint32_t a[5], const RowKeccak &k, const uint32_t pre[2],
+                                                      const uint8_t *msg, uint64_t mlen) {
+  using Plan = MwPlan<PB>;
+  const Plan pl(msg, mlen);
+  uint32_t lo[4], hi[4];
+  auto fetch = [&](uint64_t blk) {
+#pragma unroll
+    for (int y = 0; y < 4; y++) {
+      lo[y] = hi[y] = 0;
+      if (k.word(y) < MW_RATE / 8) mw_fetch_one(pl, blk, k.half_word(y), lo[y], hi[y]);
+    }
+  };
+  uint32_t p0 = pre[0], p1 = pre[1];
+#pragma unroll
+  for (int y = 0; y < 5; y++) a[y] = 0;
+  fetch(0);
+  for (uint64_t blk = 0; blk < pl.nblk; blk++) {
+#pragma unroll
+    for (int y = 0; y < 4; y++)
+      if (k.word(y) < MW_RATE / 8)
+        a[y] ^= mw_word_one(pl, blk, k.half_word(y), y == 0 ? p0 : p1, lo[y], hi[y]);
+    if (blk + 1 < pl.nblk) fetch(blk + 1);
+    keccak_f_row(a, k);
+  }
+}
+
+// SampleInBall on a row whose state holds the first SHAKE256 block of ctilde;
+// c: 256 bytes, bw: 34 words, both LDS, 4-byte aligned
+template <int TAU>
+__device__ __forceinline__ void sample_in_ball_row(uint32_t a[5], const RowKeccak &k, int lane, int8_t *c,
+                                                   uint32_t *bw) {
+  auto stage = [&]() {
+    if ((lane & 15) < 10) {
+#pragma unroll
+      for (int y = 0; y < 4; y++)
+        if (k.word(y) < RATE256 / 8) bw[k.half_word(y)] = a[y];
+    }
+    wave_sync();
+  };
+  stage();
+  uint32_t *cw = (uint32_t *)c;
+#pragma unroll
+  for (int w = 0; w < N / 64; w++) cw[16 * w + (lane & 15)] = 0;
+  wave_sync();
+  const uint8_t *bytes = (const uint8_t *)bw;
+  uint64_t signs = (uint64_t)bw[0] | ((uint64_t)bw[1] << 32);
+  int pos = 8;
+  for (int i = N - TAU; i < N; i++) {
+    int b;
+    for (;;) {
+      if (pos == RATE256) {
+        wave_sync();
+        keccak_f_row(a, k);
+        stage();
+        pos = 0;
+      }
+      b = bytes[pos++];
+      if (b <= i) break;
+    }
+    if ((lane & 15) == 0) {
+      c[i] = c[b];
+      c[b] = (int8_t)(1 - 2 * (int)(signs & 1));
+    }
+    signs >>= 1;
+  }
+}
+
+// ctilde = H(mu || w1) and c = SampleInBall(ctilde) on a row (as
+// dev_challenge_pair); ctilde_out: CT / 4 words
+template <int LV>
+__device__ __forceinline__ void dev_challenge_row(const uint8_t *mu, const uint8_t *w1, const RowKeccak &k, int lane,
+                                                  uint32_t *ctilde_out, int8_t *c, uint32_t *bw) {
+  constexpr int CW = P<LV>::CT / 8;  // 8-byte words of ctilde
+  uint32_t a[5];
+  shake256_absorb_row<P<LV>::MUW1>(a, k, [&](int i) {
+    return i < 16 ? ((const uint32_t *)mu)[i] : ((const uint32_t *)w1)[i - 16];
+  });
+#pragma unroll
+  for (int y = 0; y < 5; y++) {
+    const int w = k.word(y);
+    if (w < CW) {
+      if ((lane & 15) < 10) ctilde_out[k.half_word(y)] = a[y];
+    } else {
+      a[y] = w == CW && !k.h ? 0x1Fu : 0u;
+    }
+    if (w == RATE256 / 8 - 1 && k.h) a[y] ^= 0x80u << 24;
+  }
+  keccak_f_row(a, k);
+  sample_in_ball_row<Lv<LV>::TAU>(a, k, lane, c, bw);
+}
+
+// ---- kernels: four states per one-wavefront workgroup ----
+
+// as sg_prep_k (kernels.h), one row per task
+template <int LV, bool INTERNAL = false>
+__global__ void __launch_bounds__(64) sg_prep_row_k(const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
+                                                    const uint64_t *msg_off, const uint8_t *rnd, Ws ws,
+                                                    uint32_t count, uint32_t *err) {
+  __shared__ uint32_t L[ROW_LDS];
+  __builtin_amdgcn_s_setprio(3);
+  const int lane = threadIdx.x, l = lane & 15;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t >= count) return;  // a whole row
+  const RowKeccak k(L, lane);
+  const size_t key = key_idx ? key_idx[t] : t;
+  const uint32_t *skw = (const uint32_t *)(sk + key * P<LV>::SK);
+  const uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
+  uint64_t mlen = 0;
+  if (o1 >= o0) mlen = o1 - o0;
+  else if (l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
+  uint32_t pre[2];
+#pragma unroll
+  for (int y = 0; y < 2; y++) pre[y] = k.word(y) < P<LV>::TRB / 8 ? skw[16 + k.half_word(y)] : 0u;
+  uint32_t a[5];
+  absorb_prefix_msg_row<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
+  uint32_t *muw = (uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
+  uint32_t *rp = (uint32_t *)(ws.rhop + (size_t)t * 64);
+  // mu also to LDS, from where it is absorbed at another place
+#pragma unroll
+  for (int y = 0; y < 2; y++)
+    if (l < 10 && k.word(y) < 8) {
+      muw[k.half_word(y)] = a[y];
+      L[k.st + k.half_word(y)] = a[y];
+    }
+  wave_sync();
+  const bool round3_rnd = !Lv<LV>::MLDSA && rnd;  // rho' is the task's rnd itself
+  constexpr int MU0 = Lv<LV>::MLDSA ? 8 : 4;      // word of mu in K || rnd || mu, K || mu
+  uint32_t b[5];
+#pragma unroll
+  for (int y = 0; y < 5; y++) {
+    const int w = k.word(y), i = k.half_word(y);
+    b[y] = 0;
+    if (w < 4) b[y] = skw[8 + i];
+    else if (w < MU0) b[y] = rnd ? ((const uint32_t *)(rnd + (size_t)t * 32))[i - 8] : 0u;
+    else if (w < MU0 + 8) b[y] = L[k.st + i - 2 * MU0];
+    if (w == MU0 + 8 && !k.h) b[y] ^= 0x1Fu;
+    if (w == RATE256 / 8 - 1 && k.h) b[y] ^= 0x80u << 24;
+  }
+  wave_sync();
+  if (!round3_rnd) keccak_f_row(b, k);
+#pragma unroll
+  for (int y = 0; y < 2; y++)
+    if (l < 10 && k.word(y) < 8)
+      rp[k.half_word(y)] = round3_rnd ? ((const uint32_t *)(rnd + (size_t)t * 64))[k.half_word(y)] : b[y];
+  if (l == 0) {
+    ws.kappa[t] = 0;
+    ws.active0[t] = t;
+  }
+}
+
+// as vf_hash_k, one row per task
+template <int LV, bool INTERNAL = false>
+__global__ void __launch_bounds__(64) vf_hash_row_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
+                                                    const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
+  using PP = P<LV>;
+  __shared__ uint32_t L[ROW_LDS];
+  __builtin_amdgcn_s_setprio(3);
+  const int lane = threadIdx.x, l = lane & 15;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t >= count) return;  // a whole row
+  const RowKeccak k(L, lane);
+  const size_t key = key_idx ? key_idx[t] : t;
+  uint32_t a[5], pre[2];
+  if (ws.tr) {
+    const uint32_t *tg = (const uint32_t *)(ws.tr + key * PP::TRB);
+#pragma unroll
+    for (int y = 0; y < 2; y++) pre[y] = k.word(y) < PP::TRB / 8 ? tg[k.half_word(y)] : 0u;
+  } else {
+    const uint32_t *pkr = (const uint32_t *)(pk + key * PP::PK);
+    shake256_absorb_row<PP::PK>(a, k, [&](int i) { return pkr[i]; });
+    // the lane's words of the digest are its words of the prefix
+    pre[0] = a[0];
+    pre[1] = a[1];
+  }
+  const uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
+  uint64_t mlen = 0;
+  if (o1 >= o0) mlen = o1 - o0;
+  else if (l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
+  absorb_prefix_msg_row<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
+  uint32_t *muw = (uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
+#pragma unroll
+  for (int y = 0; y < 2; y++)
+    if (l < 10 && k.word(y) < 8) muw[k.half_word(y)] = a[y];
+}
+
+// as vf_final_k, one row per task
+template <int LV>
+__global__ void __launch_bounds__(64) vf_final_row_k(const uint8_t *sig, Ws ws, int32_t *verdict, uint32_t count) {
+  __shared__ uint32_t L[ROW_LDS];
+  const int lane = threadIdx.x, l = lane & 15;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t >= count) return;  // a whole row
+  const RowKeccak k(L, lane);
+  const uint32_t *row = (const uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
+  uint32_t a[5];
+  shake256_absorb_row<P<LV>::MUW1>(a, k, [&](int i) { return row[i]; });
+  const uint8_t *sg = sig + (size_t)t * P<LV>::SIG;
+  bool diff = false;
+#pragma unroll
+  for (int y = 0; y < 2; y++)
+    if (l < 10 && k.word(y) < P<LV>::CT / 8) diff |= (uint32_t)load_le_bytes(sg + 4 * k.half_word(y), 4) != a[y];
+  const uint64_t m = __ballot(diff) >> (lane & 48) & 0xFFFFu;
+  if (l == 0) verdict[t] = (ws.flag[t] && m == 0) ? 1 : 0;
+}
+
+// tr = H(pk) (TRB bytes) to out rows, one row per key
+template <int LV>
+__global__ void __launch_bounds__(64) tr_row_k(const uint8_t *pk, uint8_t *out, size_t out_stride, uint32_t count) {
+  __shared__ uint32_t L[ROW_LDS];
+  const int lane = threadIdx.x, l = lane & 15;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t >= count) return;  // a whole row
+  const RowKeccak k(L, lane);
+  const uint32_t *p = (const uint32_t *)(pk + (size_t)t * P<LV>::PK);
+  uint32_t a[5];
+  shake256_absorb_row<P<LV>::PK>(a, k, [&](int i) { return p[i]; });
+  uint32_t *o = (uint32_t *)(out + (size_t)t * out_stride);
+#pragma unroll
+  for (int y = 0; y < 2; y++)
+    if (l < 10 && k.word(y) < P<LV>::TRB / 8) o[k.half_word(y)] = a[y];
+}
+// the same on a lane pair, for batches that fill the chip
+template <int LV>
+__global__ void __launch_bounds__(64) tr_pair_k(const uint8_t *pk, uint8_t *out, size_t out_stride, uint32_t count) {
+  const uint32_t t = (blockIdx.x * 64 + threadIdx.x) >> 1;
+  const int half = threadIdx.x & 1;
+  if (t >= count) return;  // both lanes of a pair
+  const uint32_t *p = (const uint32_t *)(pk + (size_t)t * P<LV>::PK);
+  uint32_t a[25];
+  shake256_absorb_pair<P<LV>::PK>(a, half, [&](int pos) { return p[pos / 4 + half]; });
+  uint32_t *o = (uint32_t *)(out + (size_t)t * out_stride);
+#pragma unroll
+  for (int w = 0; w < P<LV>::TRB / 8; w++) o[2 * w + half] = a[w];
+}
+
+}  // namespace dil

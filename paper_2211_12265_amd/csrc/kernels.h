@@ -26,8 +26,8 @@ struct Ws {
   int32_t *A;        // [cap][K][L][256]  A-hat, canonical
   int32_t *s12;      // KeyGen: s1, s2 centred, [cap][L+K][256]
   int8_t *sec;       // [cap][sec_bytes] Sign: s1, s2, t0 as int8 tiles (toeplitz.h)
-  int32_t *y;        // [cap][L][256]  mask, centred
-  int32_t *w;        // [cap][K][256]  w = A y, canonical
+  uint8_t *y;        // [cap][L][YB]  mask, as squeezed
+  int32_t *w;        // [cap][K][256]  w = A y as dev_compute_w stores it
   uint32_t *hmask;   // [cap][K][8]   verify: hint bits
   uint32_t *kappa;   // [cap]
   int32_t *flag;     // [cap]
@@ -61,12 +61,12 @@ __device__ __forceinline__ size_t muw1_stride() {
   return ((size_t)P<LV>::MUW1 + 255) & ~(size_t)255;
 }
 
-// zero two small word arrays (used instead of hipMemsetAsync so that the
+// zero two word arrays with one workgroup (used instead of hipMemsetAsync so that the
 // launch sequence can be captured into a hipGraph)
 __global__ void zero_words_k(uint32_t *a, int na, uint32_t *b, int nb) {
-  int i = threadIdx.x;
-  if (i < na) a[i] = 0;
-  if (b && i < nb) b[i] = 0;
+  for (int i = threadIdx.x; i < na; i += blockDim.x) a[i] = 0;
+  if (b)
+    for (int i = threadIdx.x; i < nb; i += blockDim.x) b[i] = 0;
 }
 
 // Key-table calls: copy key_idx into the workspace with every index outside
@@ -359,19 +359,6 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
   for (int w = PP::OFF_S1 / 4 + lane; w < PP::SK / 4; w += 64) skg[w] = lds.buf[w];
 }
 
-// tr = H(pk) (TRB = 32 or 64 bytes) into sk bytes 64 .. 64 + TRB
-template <int LV>
-__global__ void __launch_bounds__(256) kg_tr_k(const uint8_t *pk, uint8_t *sk, uint32_t count) {
-  uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= count) return;
-  const uint8_t *p = pk + (size_t)t * P<LV>::PK;
-  uint32_t s[50];
-  shake_absorb<RATE256>(s, P<LV>::PK, [&](uint64_t pos) { return *(const uint64_t *)(p + pos); });
-  uint32_t *o = (uint32_t *)(sk + (size_t)t * P<LV>::SK + 64);
-#pragma unroll
-  for (int w = 0; w < P<LV>::TRB / 4; w++) o[w] = s[w];
-}
-
 // ------------------------------------------------------------------------
 // Sign (Alg. 2), staged
 // ------------------------------------------------------------------------
@@ -461,7 +448,7 @@ __global__ void __launch_bounds__(64) sg_secret_k(const uint8_t *sk, const uint3
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, ETA = Lv<LV>::ETA;
   constexpr int NW = (PP::SK - PP::OFF_S1) / 4;
   __shared__ uint32_t buf[NW + 2];
-  uint32_t task = blockIdx.x;
+  const uint32_t task = blockIdx.x;
   if (task >= count) return;
   const int lane = threadIdx.x;
   size_t key = key_idx ? key_idx[task] : task;
@@ -498,14 +485,15 @@ __global__ void __launch_bounds__(64) sg_secret_k(const uint8_t *sk, const uint3
 
 // ExpandMask stream i of iteration kappa (one lane)
 template <int LV>
-__device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t kappa, int i, int32_t *y_out) {
+__device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t kappa, int i, uint8_t *y_out) {
   uint32_t s[50];
   absorb_seed66(s, rhop, (kappa + (uint32_t)i) & 0xFFFFu);
-  expand_mask_squeeze<P<LV>::ZBITS, Lv<LV>::GAMMA1>(s, y_out);
+  expand_mask_squeeze<P<LV>::ZBITS>(s, y_out);
 }
 
-// w = INTT(A-hat * NTT(y)) for one task by one wavefront: w (canonical) to
-// w_out, HighBits(w) packed into w1_out (4-byte aligned, K * W1B bytes).
+// w = INTT(A-hat * NTT(y)) for one task by one wavefront: w as the checks take it
+// (pack_low; each lane's 16 strided coefficients contiguous: word 16 t + r of a
+// polynomial is coefficient t + 16 r) to w_out, HighBits(w) packed into w1_out (4-byte aligned, K * W1B bytes).
 // hat: L * HAT_POLY words of LDS; tr: this group's transpose region; w1buf: LDS
 // staging; ftw / itw: forward / inverse twiddles.
 // EARLY: the group's first A-hat polynomial (row g, column 0) is requested
@@ -514,7 +502,7 @@ __device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t ka
 // loads by itself, which leaves each load's latency exposed; requesting them
 // early costs 16 registers per lane, which only the l = 4 loop kernels have.
 template <int LV, bool PAD = true, bool EARLY = false, class TW>
-__device__ __forceinline__ void dev_compute_w(const int32_t *y, const int32_t *A, int32_t *w_out, uint8_t *w1_out,
+__device__ __forceinline__ void dev_compute_w(const uint8_t *y, const int32_t *A, int32_t *w_out, uint8_t *w1_out,
                                               int32_t *hat, int32_t *tr, uint32_t *w1buf, const TW &ftw,
                                               const TW &itw, int lane) {
   using PP = P<LV>;
@@ -526,7 +514,7 @@ __device__ __forceinline__ void dev_compute_w(const int32_t *y, const int32_t *A
   }
   for (int j = g; j < L; j += 4) {
     int32_t x[16];
-    load_strided(x, y + j * N, t);
+    load_mask<PP::ZBITS, Lv<LV>::GAMMA1>(x, y + j * PP::YB, t);
     ntt16<TW, PAD>(x, ftw, tr, t);
 #pragma unroll
     for (int r = 0; r < 16; r++) hat[hat_idx(j, t, r)] = x[r];
@@ -562,10 +550,11 @@ __device__ __forceinline__ void dev_compute_w(const int32_t *y, const int32_t *A
     int32_t w1[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) {
-      x[r] = canon(x[r]);
-      w1[r] = highbits<LV>(x[r]);
+      int32_t r0;
+      decompose<LV>(canon(x[r]), w1[r], r0);
+      x[r] = pack_low<LV>(w1[r], r0);
     }
-    store_strided(x, w_out + i * N, t);
+    store_slots(x, w_out + i * N, t);
     uint32_t v[16];
     to_consecutive<PAD>(w1, v, tr, t);
     pack16_to_lds<PP::W1BITS>(v, (uint8_t *)w1buf + i * PP::W1B, t);
@@ -648,7 +637,7 @@ struct CheckLds {
 // The products by c run on the matrix cores (toeplitz.h): 64 products per tile
 // of four polynomials, exact, instead of one NTT and twelve INTTs of four
 // polynomials each and no reductions mod q afterwards.  Group g evaluates
-// polynomial 4 T + g of tile T; a tile whose z or r0 norm fails ends the
+// polynomial 4 T + g of tile T; w comes as dev_compute_w stores it; a tile whose z or r0 norm fails ends the
 // evaluation before its c t0, hints and packing (about 77% of the candidates
 // at level 2).  z is packed by OR-ing each strided coefficient's bits into the
 // signature: only passing tiles pay for it, and no transpose is needed.
@@ -656,57 +645,67 @@ struct CheckLds {
 // four-wavefront loop kernel): level 2 1470 to 1410 us, level 5 2799 to 2680 us;
 // staged form, level 3, 1000 tasks: 6996 to 6725 us.
 template <int LV>
-__device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctilde, const int32_t *y, const int32_t *w,
+__device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctilde, const uint8_t *y, const int32_t *w,
                                           const int8_t *sec, CheckLds<LV> &lds, int lane) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, BETA = Lv<LV>::BETA, OMEGA = Lv<LV>::OMEGA;
   constexpr int32_t G1 = Lv<LV>::GAMMA1, G2 = Lv<LV>::GAMMA2;
-  static_assert(sizeof lds.sigbuf >= 512, "the build scratch lies in the signature buffer");
+  static_assert(sizeof lds.sigbuf >= 129 * 4, "the build scratch lies in the signature buffer");
   const int g = lane >> 4, t = lane & 15;
   uint8_t *sb = (uint8_t *)lds.sigbuf;
+  // the operands of the first tile are requested before the copies are built
+  const uint32_t cw = ((const uint32_t *)c)[lane];
   v4i s[4];
   toep_load(s, sec, lane);
-  toep_build(c, lds.ct, lds.sigbuf, lane);
+  int32_t yv[16], wv[16], ct0[16];
+  static_assert(K >= 4 && L >= 4, "the first tile is full");
+  load_mask<PP::ZBITS, G1>(yv, y + g * PP::YB, t);
+  load_slots(wv, w + g * N, t);
+  toep_build(cw, lds.ct, lds.sigbuf, lane);
   for (int q = lane; q < (int)(sizeof lds.sigbuf / 4); q += 64) lds.sigbuf[q] = 0;
   wave_sync();
 #pragma unroll 1
   for (int T = 0; T < sec_tiles<LV>(); T++) {
     const int p = 4 * T + g;
-    const bool hz = p < L, hr = p < K;
-    int32_t yv[16], wv[16];
-    if (hz) load_strided(yv, y + p * N, t);
-    if (hr) load_strided(wv, w + p * N, t);
-    v4i acc[16];
-    toep_mul(acc, s, lds.ct, lane);
-    if (T + 1 < sec_tiles<LV>()) toep_load(s, sec + (T + 1) * TILE_BYTES, lane);
+    const bool hz = L % 4 == 0 || p < L, hr = K % 4 == 0 || p < K;  // every group has work in a full tile
+    if (T > 0) {
+      if (hz) load_mask<PP::ZBITS, G1>(yv, y + p * PP::YB, t);
+      if (hr) load_slots(wv, w + p * N, t);
+    }
     // |z| < gamma1 - beta and |r0| < gamma2 - beta, as offset maxima
     uint32_t zm = 0, rm = 0;
-    int32_t r1v[16];
-    if (hz) {
+    auto half = [&](auto I0c) {
+      constexpr int I0 = decltype(I0c)::value;
+      v4i acc[8];
+      toep_mul<I0, 8>(acc, s, lds.ct, lane);
+      if (hz) {
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        yv[r] += acc[r][0];
-        zm = max(zm, (uint32_t)(yv[r] + (G1 - BETA - 1)));
+        for (int r = 0; r < 8; r++) {
+          yv[I0 + r] += acc[r][0];
+          zm = max(zm, (uint32_t)(yv[I0 + r] + (G1 - BETA - 1)));
+        }
       }
-    }
-    if (hr) {
+      if (hr) {
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        wv[r] = canon_near(wv[r] - acc[r][1]);
-        int32_t r0;
-        decompose<LV>(wv[r], r1v[r], r0);
-        rm = max(rm, (uint32_t)(r0 + (G2 - BETA - 1)));
+        for (int r = 0; r < 8; r++) {
+          wv[I0 + r] -= 2 * acc[r][1];  // 2 LowBits(w - c s2) + [HighBits != 0], if the check passes
+          rm = max(rm, (uint32_t)((wv[I0 + r] >> 1) + (G2 - BETA - 1)));
+          ct0[I0 + r] = acc[r][2] + 64 * acc[r][3];
+        }
       }
-    }
+    };
+    half(std::integral_constant<int, 0>{});
+    __builtin_amdgcn_sched_barrier(0);  // or both halves' reads are hoisted and their registers held at once
+    half(std::integral_constant<int, 8>{});
     if (wave_any(zm > 2u * (G1 - BETA - 1) || rm > 2u * (G2 - BETA - 1))) return false;
+    if (T + 1 < sec_tiles<LV>()) toep_load(s, sec + (T + 1) * TILE_BYTES, lane);
     bool bad = false;
     if (hr) {
       int cnt = 0;
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int32_t ct0 = acc[r][2] + 64 * acc[r][3];
-        bad |= (uint32_t)(ct0 + (G2 - 1)) > 2u * (G2 - 1);
-        const bool h = highbits<LV>(canon_near(wv[r] + ct0)) != r1v[r];
+        bad |= (uint32_t)(ct0[r] + (G2 - 1)) > 2u * (G2 - 1);
+        const bool h = hint_of<LV>((wv[r] >> 1) + ct0[r], wv[r] & 1);
         const uint64_t m = __ballot(h);
         const uint32_t m16 = (uint32_t)(m >> (16 * g)) & 0xFFFFu;
         if (t == 0) lds.hmask[p][r] = (uint16_t)m16;
@@ -758,7 +757,7 @@ __global__ void __launch_bounds__(256) expand_mask_k(Ws ws, const uint32_t *acti
   if (st >= (uint64_t)nactive * L) return;
   uint32_t task = active[st / L];
   int i = (int)(st % L);
-  dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, ws.kappa[task], i, ws.y + ((size_t)task * L + i) * N);
+  dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, ws.kappa[task], i, ws.y + ((size_t)task * L + i) * P<LV>::YB);
 }
 
 // w = INTT(A * NTT(y)); w1 = HighBits(w) packed after mu
@@ -771,7 +770,7 @@ __global__ void __launch_bounds__(64) sg_w_k(Ws ws, const uint32_t *active, uint
   uint32_t task = active[blockIdx.x];
   int lane = threadIdx.x, t = lane & 15;
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
-  dev_compute_w<LV>(ws.y + (size_t)task * L * N, ws.A + kix(ws, task) * K * L * N, ws.w + (size_t)task * K * N,
+  dev_compute_w<LV>(ws.y + (size_t)task * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * N, ws.w + (size_t)task * K * N,
                     ws.muw1 + (size_t)task * muw1_stride<LV>() + 64, lds.hat, lds.tr + (lane >> 4) * NTT_LDS_GROUP,
                     lds.buf, ftw, itw, lane);
   (void)PP::K;
@@ -812,7 +811,7 @@ __global__ void __launch_bounds__(64) sg_check_k(Ws ws, uint8_t *sig, const uint
   uint32_t task = active[blockIdx.x];
   const int lane = threadIdx.x;
   bool ok = dev_check<LV>(ws.cpoly + (size_t)task * N, (const uint32_t *)(ws.ctilde + (size_t)task * CT_STRIDE),
-                          ws.y + (size_t)task * L * N, ws.w + (size_t)task * K * N,
+                          ws.y + (size_t)task * L * P<LV>::YB, ws.w + (size_t)task * K * N,
                           ws.sec + kix(ws, task) * sec_bytes<LV>(), lds, lane);
   if (ok) {
     l2g_bytes(lds.sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
@@ -1065,7 +1064,7 @@ __global__ void __launch_bounds__(256) vf_final_k(const uint8_t *sig, Ws ws, int
 // ------------------------------------------------------------------------
 // Resident key tables
 // ------------------------------------------------------------------------
-// NTT(t1 2^d) (slots layout) and tr = H(pk) for every key row of a table
+// NTT(t1 2^d) (slots layout) for every key row of a table
 template <int LV>
 __global__ void __launch_bounds__(64) ks_pk_k(const uint8_t *pk, int32_t *t1h, uint32_t nkeys) {
   using PP = P<LV>;
@@ -1089,18 +1088,6 @@ __global__ void __launch_bounds__(64) ks_pk_k(const uint8_t *pk, int32_t *t1h, u
     ntt16(x, ftw, trl + g * NTT_LDS_GROUP, t);
     store_slots(x, t1h + ((size_t)key * K + i) * N, t);
   }
-}
-
-template <int LV>
-__global__ void __launch_bounds__(256) ks_tr_k(const uint8_t *pk, uint8_t *tr, uint32_t nkeys) {
-  uint32_t key = blockIdx.x * blockDim.x + threadIdx.x;
-  if (key >= nkeys) return;
-  const uint8_t *p = pk + (size_t)key * P<LV>::PK;
-  uint32_t s[50];
-  shake_absorb<RATE256>(s, P<LV>::PK, [&](uint64_t pos) { return *(const uint64_t *)(p + pos); });
-  uint32_t *o = (uint32_t *)(tr + (size_t)key * P<LV>::TRB);
-#pragma unroll
-  for (int w = 0; w < P<LV>::TRB / 4; w++) o[w] = s[w];
 }
 
 // ------------------------------------------------------------------------

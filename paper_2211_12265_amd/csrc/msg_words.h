@@ -93,7 +93,7 @@ DIL_HD uint32_t mw_word(int j, const uint32_t *pre, const uint32_t *D, uint32_t 
 // block b's message words start.
 template <int PB>
 struct MwPlan {
-  static constexpr int PW = PB / 4, DL = PB % 4;
+  static constexpr int PREFIX = PB, PW = PB / 4, DL = PB % 4;
   static_assert(DL == 0 || DL == 2, "prefix ends on a word or half-word boundary");
   static_assert(PB + 8 <= MW_RATE, "the prefix fits the first block with a message word to spare");
   uint32_t sh, fs;
@@ -114,5 +114,34 @@ struct MwPlan {
     return r < 0 ? -4 : r > 4 * MW_WPB + 4 ? 4 * MW_WPB + 4 : (int)r;
   }
 };
+
+// One word at a time, for a hash whose lanes hold different words of a block:
+// the two dwords that cover word j (0..33) of block blk ...
+template <class PLAN>
+DIL_HD void mw_fetch_one(const PLAN &pl, uint64_t blk, int j, uint32_t &lo, uint32_t &hi) {
+  lo = hi = 0;
+  const int64_t m = (int64_t)blk * MW_RATE + 4 * j - PLAN::PREFIX;  // message byte at which the word starts
+  if (pl.last < 0 || m + 4 <= 0) return;                            // empty message, or a word of the prefix
+  const int64_t d = ((int64_t)pl.sh + m) >> 2;                      // -1: the word starts in the prefix before M
+  const int64_t d1 = d + 1 > pl.last ? pl.last : d + 1;
+  if (d >= 0) lo = pl.base[d > pl.last ? pl.last : d];
+  hi = pl.base[d1];
+}
+// ... and the word: pre where it belongs to the prefix, else the message's
+// bytes with the SHAKE suffix and padding
+template <class PLAN>
+DIL_HD uint32_t mw_word_one(const PLAN &pl, uint64_t blk, int j, uint32_t pre, uint32_t lo, uint32_t hi) {
+  const int64_t m = (int64_t)blk * MW_RATE + 4 * j - PLAN::PREFIX;
+  uint32_t v = pre;
+  if (m + 4 > 0) {
+    v = mw_funnel(hi, lo, pl.fs);
+    const int64_t rem = (int64_t)pl.mlen - m;
+    v = rem <= 0 ? 0u : rem < 4 ? v & ((1u << (8 * (int)rem)) - 1u) : v;
+    if (m < 0) v &= ~((1u << (8 * (int)(-m))) - 1u);  // the prefix's zero bytes
+    if (rem >= 0 && rem < 4) v ^= 0x1Fu << (8 * (int)rem);
+  }
+  if (j == MW_WPB - 1 && blk + 1 == pl.nblk) v ^= 0x80u << 24;
+  return v;
+}
 
 }  // namespace dil

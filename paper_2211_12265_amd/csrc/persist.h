@@ -28,7 +28,7 @@ struct PCfg {
 
 // per-workgroup scratch in global memory
 struct PScr {
-  int32_t *y;    // [P][G][L][256]
+  uint8_t *y;    // [P][G][L][YB]
   int32_t *w;    // [P][G][K][256]
   uint8_t *w1;   // [P][G][K * W1B rounded to 256]
   uint8_t *stage; // multi-wave kernels only: [P][G][SIG rounded to 256]
@@ -42,6 +42,10 @@ template <int LV>
 __host__ __device__ __forceinline__ size_t sig_stride() {
   return ((size_t)P<LV>::SIG + 255) & ~(size_t)255;
 }
+
+// byte offset of the mask polynomial whose coefficient offset is `coef` (a multiple of N)
+template <int LV>
+__device__ __forceinline__ size_t ybytes(size_t coef) { return coef / N * P<LV>::YB; }
 
 // Optional per-phase cycle accounting (compile with -DDIL_PHASE_TIMERS): lane 0
 // of every workgroup accumulates the s_memtime cycles of each batch phase p and
@@ -84,6 +88,16 @@ __device__ __forceinline__ int claim_tasks(uint32_t *queue, uint32_t count, uint
                                            uint32_t *h_next, int &queue_empty) {
   return sched_claim(atomicAdd(queue, want), count, want, nh, h_task, h_next, queue_empty);
 }
+
+// Where the finishing launch of Sign in rounds (rounds.h) starts: the unsigned
+// tasks' list and count, the next nonce index of each and the work queue.
+// list = nullptr: all tasks of the call from nonce 0.
+struct Resume {
+  const uint32_t *list, *cnt;
+  uint32_t *queue;
+  uint32_t n0;
+  int rounds;
+};
 
 // the scratch offsets of a workgroup shape with G slots per batch
 template <int LV>
@@ -145,7 +159,7 @@ __global__ void __launch_bounds__(64, 2) sg_persist_k(Ws ws, PScr sc, uint8_t *s
   const int lane = threadIdx.x, t = lane & 15;
   const size_t wg = blockIdx.x;
   const ScratchIdx si = scratch_idx<LV>(G);
-  int32_t *yb = sc.y + si.y(wg, 0, 0);
+  uint8_t *yb = sc.y + ybytes<LV>(si.y(wg, 0, 0));
   int32_t *wb = sc.w + si.w(wg, 0, 0);
   uint8_t *w1b = sc.w1 + si.w1(wg, 0);
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
@@ -178,14 +192,14 @@ __global__ void __launch_bounds__(64, 2) sg_persist_k(Ws ws, PScr sc, uint8_t *s
     if (lane < ns * L) {
       int s = lane / L, i = lane % L;
       uint32_t task = lds.h_task[lds.s_h[s]];
-      dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + si.y(0, s, i));
+      dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + ybytes<LV>(si.y(0, s, i)));
     }
     wave_sync_global();
     PHASE_MARK(1);
     // ---- w = INTT(A NTT(y)) per slot ----
     for (int s = 0; s < ns; s++) {
       uint32_t task = lds.h_task[lds.s_h[s]];
-      dev_compute_w<LV>(yb + si.y(0, s, 0), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
+      dev_compute_w<LV>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
                         w1b + si.w1(0, s), lds.u.wp.hat, lds.u.wp.tr + (lane >> 4) * NTT_LDS_GROUP,
                         lds.u.wp.w1buf, ftw, itw, lane);
       wave_sync();
@@ -206,7 +220,7 @@ __global__ void __launch_bounds__(64, 2) sg_persist_k(Ws ws, PScr sc, uint8_t *s
       int h = lds.s_h[s];
       if (lds.h_win[h] != SCHED_NONE) continue;
       uint32_t task = lds.h_task[h];
-      bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + si.y(0, s, 0), wb + si.w(0, s, 0),
+      bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + ybytes<LV>(si.y(0, s, 0)), wb + si.w(0, s, 0),
                               ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.u.ck, lane);
       if (ok) {
         l2g_bytes(lds.u.ck.sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
@@ -333,9 +347,9 @@ __device__ __forceinline__ void copy_sig_row(const uint32_t *src, uint8_t *dst, 
 // The bound of two wavefronts per SIMD keeps the accumulators of dev_check in
 // the same 256 registers (left alone, the compiler adds 64 AGPRs to them and
 // the kernel falls to one wavefront per SIMD); no form spills.
-template <int LV, int NW, bool PAD = true, bool TAIL = false>
+template <int LV, int NW, bool PAD = true, bool TAIL = false, bool RESUME = false>
 __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count,
-                                                     uint32_t sched, uint32_t *stats) {
+                                                     uint32_t sched, uint32_t *stats, Resume rs) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, G = PCfgW<LV, NW>::G, W = NW;
   constexpr bool CONTIG = NW == 4 && L == 4 && PAD;  // contiguous slot ranges per wavefront
   static_assert(G <= 64, "the winner search takes one slot per lane");
@@ -344,10 +358,18 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, t = lane & 15;
   const size_t wg = blockIdx.x;
   const ScratchIdx si = scratch_idx<LV>(G);
-  int32_t *yb = sc.y + si.y(wg, 0, 0);
+  uint8_t *yb = sc.y + ybytes<LV>(si.y(wg, 0, 0));
   int32_t *wb = sc.w + si.w(wg, 0, 0);
   uint8_t *w1b = sc.w1 + si.w1(wg, 0);
   uint8_t *stg = sc.stage + si.stage(wg, 0);
+  uint32_t *queue = ws.counters;
+  uint32_t first = 0;
+  if constexpr (RESUME) {
+    const RoundState st = round_state(rs.cnt, rs.n0, rs.rounds);
+    count = st.n;
+    first = st.first;
+    queue = rs.queue;
+  }
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
   if (tid == 0) {
     lds.tally.clear();
@@ -363,8 +385,14 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
     if (tid == 0) {
       int nh = lds.nheld;
       const int hmax = (int)(sched & 0xFFu), tail = (int)(sched >> 8);
-      if (!lds.queue_empty && nh < hmax) nh = claim_tasks(ws.counters, count, (uint32_t)(hmax - nh), nh, lds.h_task,
+      const int had = nh;
+      if (!lds.queue_empty && nh < hmax) nh = claim_tasks(queue, count, (uint32_t)(hmax - nh), nh, lds.h_task,
                                                           lds.h_next, lds.queue_empty);
+      if constexpr (RESUME)
+        for (int h = had; h < nh; h++) {
+          lds.h_task[h] = rs.list[lds.h_task[h]];
+          lds.h_next[h] = first;
+        }
       lds.nheld = nh;
       const int want = TAIL ? sched_slots(nh, G, W, lds.queue_empty, tail) : G;
       const int ns = CONTIG ? sched_assign_contig(nh, want, lds.h_next, lds.h_win, lds.s_h, lds.s_att)
@@ -387,7 +415,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
       if (s_lo + lane / L < s_hi) {
         int s = s_lo + lane / L, i = lane % L;
         uint32_t task = lds.h_task[lds.s_h[s]];
-        dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + si.y(0, s, i));
+        dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + ybytes<LV>(si.y(0, s, i)));
       }
       wave_sync_global();
     } else {
@@ -395,7 +423,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
       if (tid < ns * L) {
         int s = tid / L, i = tid % L;
         uint32_t task = lds.h_task[lds.s_h[s]];
-        dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + si.y(0, s, i));
+        dev_expand_mask<LV>(ws.rhop + (size_t)task * 64, lds.s_att[s] * (uint32_t)L, i, yb + ybytes<LV>(si.y(0, s, i)));
       }
       __threadfence_block();
       __syncthreads();
@@ -404,7 +432,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
     // w per slot
     for (int s = s_lo; s < s_hi; s += s_step) {
       uint32_t task = lds.h_task[lds.s_h[s]];
-      dev_compute_w<LV, PAD, CONTIG>(yb + si.y(0, s, 0), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
+      dev_compute_w<LV, PAD, CONTIG>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
                         w1b + si.w1(0, s), lds.u[wave].wp.hat,
                         lds.u[wave].wp.tr + (lane >> 4) * NTT_LDS_GROUP, lds.u[wave].wp.w1buf, ftw, itw, lane);
       wave_sync();
@@ -430,7 +458,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
       // another wave may lower h_win meanwhile: read it once, wave-uniformly
       if (__builtin_amdgcn_readfirstlane(lds.h_win[h]) < lds.s_att[s]) continue;
       uint32_t task = lds.h_task[h];
-      bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + si.y(0, s, 0), wb + si.w(0, s, 0),
+      bool ok = dev_check<LV>(lds.c[s], lds.ct[s], yb + ybytes<LV>(si.y(0, s, 0)), wb + si.w(0, s, 0),
                               ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.u[wave].ck, lane);
       if (ok) {
         const uint32_t *sb = lds.u[wave].ck.sigbuf;

@@ -1,0 +1,252 @@
+// Sign in rounds (Alg. 2 loop), one launch per stage and round, with no host
+// in the loop.
+//
+// A group of tasks goes through a fixed number of rounds.  In a round every
+// unsigned task gets the same number of consecutive nonces (round_nonces in
+// batch_sched.h), and four kernels run over
+// all candidates: ExpandMask (one lane per stream), w = A y (one wavefront per
+// candidate), the challenge (two lanes per candidate) and the checks (one
+// wavefront per task going through its candidates in order, or a workgroup per
+// task when m is large).  The checks stop at a task's first passing nonce, so
+// the signature is the sequential algorithm's; tasks without one are appended
+// to the next round's list and counted, and the next kernels read the count on
+// the device.  Tasks still unsigned after the last round (about one in 10^2
+// calls reaches that) are finished by the persistent kernel of persist.h,
+// started at the next nonce.
+//
+// Against the persistent kernel, every stage gets the registers, the LDS and
+// the wavefronts it wants: the loop kernel holds two wavefronts per SIMD for
+// all stages and parks half of them while challenges are hashed.  Whole Sign
+// call, loop kernel / rounds: 10,000 tasks at level 2 1465 / 1199 us, at level 5
+// (32 to 4096-byte messages) 2844 / 2031 us; 2,503 hedged ML-DSA-65 1328 / 911
+// us; 613 tasks on resident level-2 keys 834 / 460 us, one on a level-3 key
+// 271 / 126 us.
+#pragma once
+#include <algorithm>
+
+#include "keccak_row.h"
+#include "persist.h"
+
+namespace dil {
+
+constexpr int ROUNDS_MAX = 8;
+constexpr int ROUND_WORDS = 16;  // counter words of a group: [r] unfinished tasks at the start of round r > 0,
+                                 // [ROUNDS_MAX + 1] work queue of the finishing kernel
+static_assert(ROUNDS_MAX + 2 <= ROUND_WORDS, "a group's counters");
+
+// One group: tasks [first, first + n) of the call; cap = round_candidates(n).
+struct Group {
+  uint32_t first, n, cap;
+  uint32_t *cnt;      // [ROUND_WORDS], zeroed before the first round
+  uint32_t *list[2];  // unsigned tasks of odd / even rounds, [n] each (round 0 takes all, in order)
+  uint8_t *y;         // [cap][L][YB]
+  int32_t *w;         // [cap][K][256], register order
+  uint8_t *w1;        // [cap][K * W1B]
+  uint8_t *ct;        // [cap][CT_STRIDE]
+  int8_t *c;          // [cap][256]
+};
+
+// task of entry e of round r's list
+__device__ __forceinline__ uint32_t round_task(const Group &gr, int r, uint32_t e) {
+  return r == 0 ? gr.first + e : gr.list[r & 1][e];
+}
+
+// ExpandMask streams: a round of many has one lane each; as long as the chip
+// would hold at most one wavefront per SIMD, a stream gets a lane pair, and
+// with still fewer a 16-lane row.  A stream is five permutations one after
+// another and a lone wavefront's permutation takes 9.2 us on one lane, 6.8 us
+// on a pair and about half of that on a row, so the stage then lasts 51, 36 or
+// 20 us; beyond these counts the wider forms would queue for the SIMDs.
+constexpr uint32_t ROW_STATES = 4096, PAIR_STATES = 32768, ROW_CHALLENGES = 8192;
+inline uint32_t mask_blocks(uint64_t streams, bool exact) {
+  // 256-lane workgroups that the form of at most `streams` streams needs (exact: of that many)
+  auto need = [](uint64_t n) -> uint64_t {
+    return n <= ROW_STATES ? (n + 15) / 16 : n <= PAIR_STATES ? (n + 127) / 128 : (n + 255) / 256;
+  };
+  uint64_t b = need(streams);
+  if (!exact) {
+    if (streams > ROW_STATES) b = b > need(ROW_STATES) ? b : need(ROW_STATES);
+    if (streams > PAIR_STATES) b = b > need(PAIR_STATES) ? b : need(PAIR_STATES);
+  }
+  return (uint32_t)b;
+}
+
+// the squeezed stream of one candidate polynomial on a lane pair / a row
+template <int LV>
+__device__ __forceinline__ void dev_expand_mask_pair(const uint8_t *rhop, uint32_t nonce, int half, uint8_t *out) {
+  constexpr int WPB = RATE256 / 4, NWORD = N * P<LV>::ZBITS / 32, NBLK = (NWORD + WPB - 1) / WPB;
+  const uint32_t *rw = (const uint32_t *)rhop;
+  uint32_t *o = (uint32_t *)out + half;
+  uint32_t a[25];
+#pragma unroll
+  for (int i = 0; i < 25; i++) a[i] = i < 8 ? rw[2 * i + half] : 0u;
+  if (!half) a[8] = (nonce & 0xFFFFu) | (0x1Fu << 16);
+  else a[RATE256 / 8 - 1] = 0x80u << 24;
+#pragma unroll
+  for (int blk = 0; blk < NBLK; blk++) {
+    keccak_f_pair(a, half);
+#pragma unroll
+    for (int i = 0; i < WPB / 2; i++)
+      if (blk * WPB + 2 * i < NWORD) o[blk * WPB + 2 * i] = a[i];
+  }
+}
+template <int LV>
+__device__ __forceinline__ void dev_expand_mask_row(const uint8_t *rhop, uint32_t nonce, const RowKeccak &k, int lane,
+                                                    uint8_t *out) {
+  constexpr int WPB = RATE256 / 4, NWORD = N * P<LV>::ZBITS / 32, NBLK = (NWORD + WPB - 1) / WPB;
+  const uint32_t *rw = (const uint32_t *)rhop;
+  uint32_t *o = (uint32_t *)out;
+  uint32_t a[5];
+#pragma unroll
+  for (int y = 0; y < 5; y++) {
+    const int w = k.word(y);
+    a[y] = w < 8 ? rw[k.half_word(y)] : 0u;
+    if (w == 8 && !k.h) a[y] = (nonce & 0xFFFFu) | (0x1Fu << 16);
+    if (w == RATE256 / 8 - 1 && k.h) a[y] = 0x80u << 24;
+  }
+#pragma unroll 1
+  for (int blk = 0; blk < NBLK; blk++) {
+    keccak_f_row(a, k);
+#pragma unroll
+    for (int y = 0; y < 4; y++)
+      if ((lane & 15) < 10 && k.word(y) < RATE256 / 8 && blk * WPB + k.half_word(y) < NWORD)
+        o[blk * WPB + k.half_word(y)] = a[y];
+  }
+}
+
+template <int LV>
+__global__ void __launch_bounds__(256) rd_mask_k(Ws ws, Group gr, int r) {
+  constexpr uint32_t L = Lv<LV>::L;
+  __shared__ uint32_t rows[4][ROW_LDS];
+  __builtin_amdgcn_s_setprio(2);
+  const RoundState st = round_state(gr.cnt, gr.n, r);
+  const uint32_t total = st.n * st.m * L;
+  const uint32_t lanes = total <= ROW_STATES ? 16 : total <= PAIR_STATES ? 2 : 1;
+  const uint32_t id = (blockIdx.x * 256 + threadIdx.x) / lanes;
+  if (id >= total) return;
+  const uint32_t s = id / L, i = id - s * L, e = s / st.m;
+  const uint8_t *rhop = ws.rhop + (size_t)round_task(gr, r, e) * 64;
+  const uint32_t kappa = (st.first + (s - e * st.m)) * L;
+  uint8_t *out = gr.y + (size_t)id * P<LV>::YB;
+  if (lanes == 1) {
+    dev_expand_mask<LV>(rhop, kappa, (int)i, out);
+  } else if (lanes == 2) {
+    dev_expand_mask_pair<LV>(rhop, kappa + i, threadIdx.x & 1, out);
+  } else {
+    const int lane = threadIdx.x & 63;
+    dev_expand_mask_row<LV>(rhop, kappa + i, RowKeccak(rows[threadIdx.x >> 6], lane), lane, out);
+  }
+}
+
+// w = INTT(A NTT(y)) and its packed high bits: one wavefront per candidate.
+// Four candidates per workgroup, so that candidates of one task mostly share
+// a CU and read its A-hat from the vector cache once.
+template <int LV>
+struct RoundWLds {
+  int32_t hat[Lv<LV>::L * HAT_POLY];
+  int32_t tr[4 * NTT_LDS_GROUP];
+  uint32_t w1buf[Lv<LV>::K * P<LV>::W1B / 4 + 1];
+};
+template <int LV>
+__global__ void __launch_bounds__(256) rd_w_k(Ws ws, Group gr, int r) {
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
+  __shared__ __align__(16) RoundWLds<LV> lds[4];
+  const RoundState st = round_state(gr.cnt, gr.n, r);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, t = lane & 15;
+  const uint32_t s = blockIdx.x * 4 + wave;
+  if (s >= st.n * st.m) return;
+  const uint32_t task = round_task(gr, r, s / st.m);
+  const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
+  RoundWLds<LV> &l = lds[wave];
+  dev_compute_w<LV, true, true>(gr.y + (size_t)s * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * N, gr.w + (size_t)s * K * N,
+                    gr.w1 + (size_t)s * K * P<LV>::W1B, l.hat, l.tr + (lane >> 4) * NTT_LDS_GROUP, l.w1buf, ftw, itw,
+                    lane);
+}
+
+// ctilde = H(mu || w1), c = SampleInBall(ctilde): two lanes per candidate, or a
+// 16-lane row as long as that takes at most one wavefront per SIMD (eight
+// permutations in series: 65 us on pairs)
+inline uint32_t chal_blocks(uint32_t cand) {
+  const uint32_t rows = (std::min(cand, ROW_CHALLENGES) + 3) / 4, pairs = (cand + 31) / 32;
+  return std::max(rows, pairs);
+}
+template <int LV>
+__global__ void __launch_bounds__(64) rd_chal_k(Ws ws, Group gr, int r) {
+  __shared__ int8_t cl[32][C_ROW];
+  __shared__ uint32_t bb[32][RATE256 / 4];
+  __shared__ uint32_t rows[ROW_LDS];
+  __builtin_amdgcn_s_setprio(3);
+  const RoundState st = round_state(gr.cnt, gr.n, r);
+  const uint32_t total = st.n * st.m;
+  const bool row = total <= ROW_CHALLENGES;
+  const int lane = threadIdx.x, p = row ? lane >> 4 : lane >> 1;
+  const uint32_t s = blockIdx.x * (row ? 4 : 32) + p;
+  if (s >= total) return;  // a whole pair or row
+  const uint32_t task = round_task(gr, r, s / st.m);
+  const uint8_t *mu = ws.muw1 + (size_t)task * muw1_stride<LV>();
+  const uint8_t *w1 = gr.w1 + (size_t)s * Lv<LV>::K * P<LV>::W1B;
+  uint32_t *ct = (uint32_t *)(gr.ct + (size_t)s * CT_STRIDE);
+  if (row) dev_challenge_row<LV>(mu, w1, RowKeccak(rows, lane), lane, ct, cl[p], bb[p]);
+  else dev_challenge_pair<LV>(mu, w1, lane & 1, ct, cl[p], bb[p]);
+  wave_sync();
+  const uint32_t *cw = (const uint32_t *)cl[p];
+  int4 *d = (int4 *)(gr.c + (size_t)s * N);
+  for (int v = row ? lane & 15 : lane & 1; v < N / 16; v += row ? 16 : 2)
+    d[v] = make_int4(cw[4 * v], cw[4 * v + 1], cw[4 * v + 2], cw[4 * v + 3]);
+}
+
+// The checks.  Up to ROUND_SEQ nonces per task, each wavefront takes a task and
+// evaluates its candidates in order, so that none after the first passing one
+// is looked at; with more, the four wavefronts of a workgroup share a task.
+constexpr uint32_t ROUND_SEQ = 6;
+template <int LV>
+__global__ void __launch_bounds__(256, 3) rd_check_k(Ws ws, Group gr, uint8_t *sig, int r, uint32_t *stats) {
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
+  __shared__ __align__(16) CheckLds<LV> lds[4];
+  __shared__ uint32_t seq;
+  __shared__ int okw[4];
+  const RoundState st = round_state(gr.cnt, gr.n, r);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    atomicAdd((unsigned long long *)&stats[2], (unsigned long long)st.n * st.m);
+  const bool shared = st.m > ROUND_SEQ;  // uniform over the launch
+  const uint32_t e = shared ? blockIdx.x : blockIdx.x * 4 + wave;
+  if ((shared ? e : blockIdx.x * 4) >= st.n) return;
+  if (threadIdx.x == 0) seq = 0;
+  __syncthreads();
+  const bool live = e < st.n;
+  const uint32_t task = live ? round_task(gr, r, e) : 0;
+  uint32_t win = SCHED_NONE;
+  for (uint32_t k0 = 0; k0 < st.m && win == SCHED_NONE; k0 += shared ? 4 : 1) {
+    const uint32_t k = shared ? k0 + wave : k0;
+    bool ok = false;
+    if (live && k < st.m) {
+      const size_t s = (size_t)e * st.m + k;
+      ok = dev_check<LV>(gr.c + s * N, (const uint32_t *)(gr.ct + s * CT_STRIDE), gr.y + s * L * P<LV>::YB,
+                         gr.w + s * K * N, ws.sec + kix(ws, task) * sec_bytes<LV>(), lds[wave], lane);
+    }
+    if (shared) {
+      if (lane == 0) okw[wave] = ok;
+      __syncthreads();
+      for (int v = 3; v >= 0; v--)
+        if (okw[v]) win = k0 + v;
+      __syncthreads();
+    } else if (ok) {
+      win = k;
+    }
+  }
+  if (live) {
+    if (win != SCHED_NONE) {
+      if (!shared || (win & 3) == (uint32_t)wave) {
+        l2g_bytes(lds[wave].sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
+        if (lane == 0) atomicAdd(&seq, st.first + win + 1);
+      }
+    } else if (lane == 0 && (!shared || wave == 0)) {
+      gr.list[(r + 1) & 1][atomicAdd(&gr.cnt[r + 1], 1u)] = task;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && seq) atomicAdd((unsigned long long *)&stats[6], (unsigned long long)seq);
+}
+
+}  // namespace dil

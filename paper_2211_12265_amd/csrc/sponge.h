@@ -70,34 +70,43 @@ __device__ __forceinline__ void absorb_seed66(uint32_t s[50], const uint8_t *rho
   keccak_f(s);
 }
 
-// ExpandMask: y_i coefficients from the lane's SHAKE256 stream (absorbed and
-// permuted once).  B-bit little-endian values v, coefficient gamma1 - v.
-// Stores the 256 coefficients to out (natural order) four at a time.
-template <int B, int32_t GAMMA1>
-__device__ __forceinline__ void expand_mask_squeeze(uint32_t s[50], int32_t *out) {
-  constexpr int HPB = RATE256 / 4;              // 34 halves per block
-  constexpr int NBLK = (N * B / 8 + RATE256 - 1) / RATE256;  // 5
-  uint32_t carry = 0;                           // last half of the previous block
-  int32_t quad[4];
+// ExpandMask: the lane's SHAKE256 stream (absorbed and permuted once) stored as
+// it comes, 16 bytes at a time.  The first 32 B bytes are the B-bit little-endian
+// fields v of the polynomial's 256 coefficients gamma1 - v, which the readers
+// unpack (load_mask): 576 / 640 bytes per polynomial move instead of 1024, and
+// the squeezing lane does no work per coefficient.  out is 16-byte aligned.
+template <int B>
+__device__ __forceinline__ void expand_mask_squeeze(uint32_t s[50], uint8_t *out) {
+  constexpr int WPB = RATE256 / 4;              // 34 words per block
+  constexpr int NWORD = N * B / 32;             // 144 / 160
+  constexpr int NBLK = (NWORD + WPB - 1) / WPB; // 5
+  uint32_t quad[4];
 #pragma unroll
   for (int blk = 0; blk < NBLK; blk++) {
     if (blk > 0) keccak_f(s);
 #pragma unroll
-    for (int c = 0; c < N; c++) {
-      // coefficient c is emitted in the block holding its last bit
-      const int p0 = c * B, p1 = c * B + B - 1;
-      const int end_blk = (p1 / 32) / HPB;
-      if (end_blk == blk) {
-        const int h0 = p0 / 32 - blk * HPB, h1 = p1 / 32 - blk * HPB, sh = p0 & 31;
-        uint32_t lo = h0 < 0 ? carry : s[h0 < 0 ? 0 : h0];
-        uint32_t hi = s[h1];
-        uint32_t v = (h0 == h1) ? (lo >> sh) : __builtin_amdgcn_alignbit(hi, lo, sh);
-        v &= (1u << B) - 1u;
-        quad[c & 3] = GAMMA1 - (int32_t)v;
-        if ((c & 3) == 3) ((int4 *)out)[c >> 2] = make_int4(quad[0], quad[1], quad[2], quad[3]);
+    for (int w = 0; w < WPB; w++) {
+      const int gw = blk * WPB + w;
+      if (gw < NWORD) {
+        quad[gw & 3] = s[w];
+        if ((gw & 3) == 3) ((uint4 *)out)[gw >> 2] = make_uint4(quad[0], quad[1], quad[2], quad[3]);
       }
     }
-    carry = s[HPB - 1];
+  }
+}
+// the lane's strided coefficients (t + 16 r) of a polynomial stored by
+// expand_mask_squeeze: field t + 16 r starts 16 B r bits, a whole number of
+// words, after field t.  Every field is fetched as the two words it may span;
+// the second word of a row's last field is the one after the row (its bits are
+// not used), so a row is followed by at least four more bytes of its memory.
+template <int B, int32_t GAMMA1>
+__device__ __forceinline__ void load_mask(int32_t x[16], const uint8_t *row, int t) {
+  const uint32_t *w = (const uint32_t *)row + ((B * t) >> 5);
+  const int sh = (B * t) & 31;
+#pragma unroll
+  for (int r = 0; r < 16; r++) {
+    const uint32_t lo = w[r * (B / 2)], hi = w[r * (B / 2) + 1];
+    x[r] = GAMMA1 - (int32_t)(__builtin_amdgcn_alignbit(hi, lo, sh) & ((1u << B) - 1u));
   }
 }
 

@@ -15,10 +15,14 @@
 //
 // T in LDS: every fragment is a 16-byte window of f[m] = c[255 - m] (m < 256),
 // -c[511 - m] (m >= 256): lane (i, kg) of the block (I, J) needs f from
-// 15 - i + 16 u on, u = 4 J + kg - I + 15.  Copy i of f starts at byte 15 - i,
-// so that all windows are 16-byte aligned; copies are 132 words apart, which
-// spreads the 16 lanes of a group over all 64 banks.  Only w = 4 J - I matters
-// for the address: 28 reads feed the 64 products.
+// 15 - i + 16 u on, u = 4 J + kg - I + 15.  Copy b of f starts at byte b, so
+// that every window is word-aligned in copy (15 - i) & 3; copies are 136 words
+// apart, which puts the words that 32 lanes read at once into 32 different
+// banks.  Only w = 4 J - I matters for the address: 28 windows feed the 64
+// products (20 + 20 when they are made in two halves, which holds 32
+// accumulator registers instead of 64).  (16 copies, one per i, make every
+// window one aligned 16-byte read but take 8.4 KB of LDS per wavefront instead
+// of 2.3 and three times the instructions to build.)
 #pragma once
 #include "common.h"
 #include "poly.h"
@@ -27,34 +31,29 @@ namespace dil {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-constexpr int TOEP_ROW = 132;              // words of one shifted copy: 31 windows of 16 bytes, padded
-constexpr int TOEP_WORDS = 16 * TOEP_ROW;  // one wavefront's copies
+constexpr int TOEP_ROW = 136;             // words of one shifted copy: 127 used, padded
+constexpr int TOEP_WORDS = 4 * TOEP_ROW;  // one wavefront's copies
 
-// Build the 16 shifted copies from the dense challenge (256 int8, 4-byte
-// aligned, LDS or global) with one wavefront.  f: 128 words of LDS scratch.
-__device__ __forceinline__ void toep_build(const int8_t *c, uint32_t *ct, uint32_t *f, int lane) {
-  const uint32_t v = ((const uint32_t *)c)[lane];
-  const uint32_t rev = __builtin_amdgcn_perm(v, v, 0x00010203u);  // bytes reversed
+// Build the four shifted copies from the dense challenge (cw: the lane's four
+// coefficients 4 lane .. 4 lane + 3) with one wavefront.  f: 129 words of LDS scratch.
+__device__ __forceinline__ void toep_build(uint32_t cw, uint32_t *ct, uint32_t *f, int lane) {
+  const uint32_t rev = __builtin_amdgcn_perm(cw, cw, 0x00010203u);  // bytes reversed
   f[63 - lane] = rev;
   // bytes of {-1, 0, 1} negated: flip the upper seven bits of the non-zero ones
   f[127 - lane] = rev ^ ((rev & 0x01010101u) * 0xFEu);
+  if (lane == 0) f[128] = 0;  // read, never used
   wave_sync();
-  const int i = lane & 15, q = lane >> 4, sh = (15 - i) & 3;
-  const uint32_t *src = f + 32 * q + ((15 - i) >> 2);
-  v4i *dst = (v4i *)(ct + i * TOEP_ROW + 32 * q);
-  uint32_t x = src[0];
+  const int b = lane & 3, q = lane >> 2;  // copy b, words 8 q .. 8 q + 7
+  uint32_t x[9];
 #pragma unroll
-  for (int u = 0; u < 8; u++) {  // windows 8 q .. 8 q + 7; the last group has seven
-    if (u < 7 || q < 3) {
-      v4i o;
+  for (int k = 0; k < 9; k++) x[k] = f[8 * q + k];
+  v4i *dst = (v4i *)(ct + b * TOEP_ROW + 8 * q);
 #pragma unroll
-      for (int k = 0; k < 4; k++) {
-        const uint32_t nx = src[4 * u + k + 1];
-        o[k] = (int)__builtin_amdgcn_alignbyte(nx, x, sh);
-        x = nx;
-      }
-      dst[u] = o;
-    }
+  for (int u = 0; u < 2; u++) {
+    v4i o;
+#pragma unroll
+    for (int k = 0; k < 4; k++) o[k] = (int)__builtin_amdgcn_alignbyte(x[4 * u + k + 1], x[4 * u + k], b);
+    dst[u] = o;
   }
   wave_sync();
 }
@@ -66,17 +65,21 @@ __device__ __forceinline__ void toep_load(v4i s[4], const int8_t *tile, int lane
   for (int J = 0; J < 4; J++) s[J] = *(const v4i *)(p + 64 * J);
 }
 
-__device__ __forceinline__ void toep_mul(v4i acc[16], const v4i s[4], const uint32_t *ct, int lane) {
-  const uint32_t *row = ct + (lane & 15) * TOEP_ROW + 4 * (lane >> 4);
+// Accumulators I = I0 .. I0 + NI - 1 of a tile.
+template <int I0, int NI>
+__device__ __forceinline__ void toep_mul(v4i acc[NI], const v4i s[4], const uint32_t *ct, int lane) {
+  const int o = 15 - (lane & 15);
+  const uint32_t *row = ct + (o & 3) * TOEP_ROW + (o >> 2) + 4 * (lane >> 4);
 #pragma unroll
-  for (int I = 0; I < 16; I++) acc[I] = v4i{0, 0, 0, 0};
+  for (int I = 0; I < NI; I++) acc[I] = v4i{0, 0, 0, 0};
 #pragma unroll
-  for (int w = -15; w <= 12; w++) {
-    const v4i b = *(const v4i *)(row + 4 * (w + 15));
+  for (int w = -(I0 + NI - 1); w <= 12 - I0; w++) {
+    const uint32_t *p = row + 4 * (w + 15);
+    const v4i b = {(int)p[0], (int)p[1], (int)p[2], (int)p[3]};
 #pragma unroll
     for (int J = 0; J < 4; J++) {
-      const int I = 4 * J - w;
-      if (I >= 0 && I < 16) acc[I] = __builtin_amdgcn_mfma_i32_16x16x64_i8(s[J], b, acc[I], 0, 0, 0);
+      const int I = 4 * J - w - I0;
+      if (I >= 0 && I < NI) acc[I] = __builtin_amdgcn_mfma_i32_16x16x64_i8(s[J], b, acc[I], 0, 0, 0);
     }
   }
 }
