@@ -419,31 +419,26 @@ void check_keys(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, uin
     keys_check_k<<<blocks_for(count, 256), 256, 0, st>>>(key_idx, ks->nkeys, checked, count, ctx->dev_stats + 9);
 }
 
-// mu and the mask seeds in the context's message form; on a row per task as
-// long as that takes at most one wavefront per SIMD
+// The hash kernels in the form for `count` tasks and the context's message form:
+// mu and the mask seeds
+template <int LV, bool INTERNAL>
+void launch_prep_form(const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
+                      const uint64_t *msg_off, const uint8_t *rnd, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
+  if (count <= ROW_STATES)
+    sg_prep_row_k<LV, INTERNAL><<<blocks_for(count, 4), 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+  else
+    sg_prep_k<LV, INTERNAL><<<blocks_for(count, 32), 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+}
 template <int LV>
 void launch_prep(const dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
-                 const uint64_t *msg_off, const uint8_t *rnd, const Ws &ws, uint32_t count, uint32_t *err,
-                 hipStream_t st) {
-  const unsigned nb = blocks_for(2 * (uint64_t)count, 256);
-  if (count <= ROW_STATES) {
-    const unsigned rb = blocks_for(count, 4);
-    if constexpr (Lv<LV>::MLDSA) {
-      if (ctx->mldsa_internal) {
-        sg_prep_row_k<LV, true><<<rb, 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
-        return;
-      }
-    }
-    sg_prep_row_k<LV><<<rb, 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
-    return;
-  }
+                      const uint64_t *msg_off, const uint8_t *rnd, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
   if constexpr (Lv<LV>::MLDSA) {
     if (ctx->mldsa_internal) {
-      sg_prep_k<LV, true><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+      launch_prep_form<LV, true>(sk, key_idx, msg, msg_off, rnd, ws, count, err, st);
       return;
     }
   }
-  sg_prep_k<LV><<<nb, 256, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+  launch_prep_form<LV, false>(sk, key_idx, msg, msg_off, rnd, ws, count, err, st);
 }
 
 // The setup stages are independent of each other: mu/rho' hash chains (one lane
@@ -637,10 +632,12 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     if (!ks) {
       int r2 = fork_side(ctx, s, 1);
       if (r2) return r2;
+    }
+    // the hashes are few wavefronts in long chains: they take their places before ExpandA fills the SIMDs
+    launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, ctx->dev_stats + 8, s);
+    if (!ks)
       expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, ctx->side[0]>>>(sk, P<LV>::SK, key_idx,
                                                                                          ws.A, count);
-    }
-    launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, ctx->dev_stats + 8, s);
     launch_mask<LV>(ws, group(0), 0, s);
     if (!ks) {
       sg_secret_k<LV><<<count, 64, 0, s>>>(sk, key_idx, ws, count);
@@ -739,29 +736,25 @@ int sign_persistent(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, co
   return mark_done(ctx, st);
 }
 
-// Verify's tr / mu kernel in the context's message form
+// Verify's tr / mu
+template <int LV, bool INTERNAL>
+void launch_vf_hash_form(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
+                         const uint64_t *msg_off, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
+  if (count <= ROW_STATES)
+    vf_hash_row_k<LV, INTERNAL><<<blocks_for(count, 4), 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+  else
+    vf_hash_k<LV, INTERNAL><<<blocks_for(count, 32), 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+}
 template <int LV>
-void launch_vf_hash(const dil_ctx *ctx, hipStream_t st, const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
-                    const uint64_t *msg_off, const Ws &ws, uint32_t count, uint32_t *err) {
-  const unsigned nb = blocks_for(2 * (uint64_t)count, 64);
-  if (count <= ROW_STATES) {
-    const unsigned rb = blocks_for(count, 4);
-    if constexpr (Lv<LV>::MLDSA) {
-      if (ctx->mldsa_internal) {
-        vf_hash_row_k<LV, true><<<rb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
-        return;
-      }
-    }
-    vf_hash_row_k<LV><<<rb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
-    return;
-  }
+void launch_vf_hash(const dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
+                         const uint64_t *msg_off, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
   if constexpr (Lv<LV>::MLDSA) {
     if (ctx->mldsa_internal) {
-      vf_hash_k<LV, true><<<nb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+      launch_vf_hash_form<LV, true>(pk, key_idx, msg, msg_off, ws, count, err, st);
       return;
     }
   }
-  vf_hash_k<LV><<<nb, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+  launch_vf_hash_form<LV, false>(pk, key_idx, msg, msg_off, ws, count, err, st);
 }
 
 template <int LV>
@@ -793,7 +786,7 @@ int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const 
       if (r2) return r2;
     }
     hipStream_t s_hash = conc ? ctx->side[1] : s, s_ea = conc ? ctx->side[0] : s;
-    launch_vf_hash<LV>(ctx, s_hash, pk, key_idx, msg, msg_off, ws, count, ctx->dev_stats + 8);
+    launch_vf_hash<LV>(ctx, pk, key_idx, msg, msg_off, ws, count, ctx->dev_stats + 8, s_hash);
     if (!ks)
       expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, s_ea>>>(pk, P<LV>::PK, key_idx, ws.A,
                                                                                 count);
@@ -1181,7 +1174,7 @@ int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_
   const uint32_t *kidx = use_keyset(ws, ks, key_idx, kid);
   zero_words_k<<<1, 64, 0, st>>>(ws.counters, 16, nullptr, 0);
   check_keys(ctx, ks, key_idx, kid, count, st);
-  launch_vf_hash<LV>(ctx, st, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG);
+  launch_vf_hash<LV>(ctx, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG, st);
   vf_prep_k<LV><<<blocks_for(count, 64), 64, 0, st>>>(sig, ws, count);
   vf_main_k<LV><<<count, 64, 0, st>>>(ks->pk, kidx, sig, ws, count);
   launch_vf_final<LV>(st, sig, ws, verdict, count);

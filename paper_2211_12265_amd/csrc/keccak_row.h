@@ -17,7 +17,8 @@
 // sheet once and are the ones whose words are kept; the read-back makes all 16
 // valid again.  34 VALU and 15 LDS instructions per round against 120 VALU on a
 // lane pair (keccak_pair.h): 3.4 times the issue slots per state, half the time
-// per permutation of a lone wavefront.
+// per permutation of a lone wavefront (3.5 against 6.8 us): the mu chains of 613
+// messages of up to 6 KB 493 -> 213 us, of 2,503 messages of up to 4 KB 328 -> 176.
 #pragma once
 #include "kernels.h"
 
@@ -226,18 +227,12 @@ __device__ __forceinline__ void dev_challenge_row(const uint8_t *mu, const uint8
   sample_in_ball_row<Lv<LV>::TAU>(a, k, lane, c, bw);
 }
 
-// ---- kernels: four states per one-wavefront workgroup ----
-
-// as sg_prep_k (kernels.h), one row per task
-template <int LV, bool INTERNAL = false>
-__global__ void __launch_bounds__(64) sg_prep_row_k(const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
-                                                    const uint64_t *msg_off, const uint8_t *rnd, Ws ws,
-                                                    uint32_t count, uint32_t *err) {
-  __shared__ uint32_t L[ROW_LDS];
-  __builtin_amdgcn_s_setprio(3);
-  const int lane = threadIdx.x, l = lane & 15;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t >= count) return;  // a whole row
+// as dev_prep_pair (kernels.h) on a row; L: the wavefront's ROW_LDS words
+template <int LV, bool INTERNAL>
+__device__ __forceinline__ void dev_prep_row(uint32_t t, uint32_t *L, int lane, const uint8_t *sk,
+                                             const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
+                                             const uint8_t *rnd, const Ws &ws, uint32_t *err) {
+  const int l = lane & 15;
   const RowKeccak k(L, lane);
   const size_t key = key_idx ? key_idx[t] : t;
   const uint32_t *skw = (const uint32_t *)(sk + key * P<LV>::SK);
@@ -285,16 +280,13 @@ __global__ void __launch_bounds__(64) sg_prep_row_k(const uint8_t *sk, const uin
   }
 }
 
-// as vf_hash_k, one row per task
-template <int LV, bool INTERNAL = false>
-__global__ void __launch_bounds__(64) vf_hash_row_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
-                                                    const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
+// as dev_hash_pair on a row
+template <int LV, bool INTERNAL>
+__device__ __forceinline__ void dev_hash_row(uint32_t t, uint32_t *L, int lane, const uint8_t *pk,
+                                             const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
+                                             const Ws &ws, uint32_t *err) {
   using PP = P<LV>;
-  __shared__ uint32_t L[ROW_LDS];
-  __builtin_amdgcn_s_setprio(3);
-  const int lane = threadIdx.x, l = lane & 15;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t >= count) return;  // a whole row
+  const int l = lane & 15;
   const RowKeccak k(L, lane);
   const size_t key = key_idx ? key_idx[t] : t;
   uint32_t a[5], pre[2];
@@ -318,6 +310,46 @@ __global__ void __launch_bounds__(64) vf_hash_row_k(const uint8_t *pk, const uin
 #pragma unroll
   for (int y = 0; y < 2; y++)
     if (l < 10 && k.word(y) < 8) muw[k.half_word(y)] = a[y];
+}
+
+// ---- kernels: one-wavefront workgroups of 32 lane pairs or four rows ----
+// mu needs one permutation per 136 message bytes in series, whatever the chip
+// does beside it: up to 31 for 4 KB, and Verify's tr = H(pk) 10 / 15 / 20 before
+// them.  A batch that leaves room gives every task a row.  Larger ones take
+// lane pairs: beside ExpandA rows would cost it more than they gain (level-3
+// Verify, 10,000 tasks of up to 4 KB: 555-697 us with rows for the messages of
+// more than 2 KB against 551).
+template <int LV, bool INTERNAL>
+__global__ void __launch_bounds__(64) sg_prep_k(const uint8_t *sk, const uint32_t *key_idx,
+                                                    const uint8_t *msg, const uint64_t *msg_off, const uint8_t *rnd, Ws ws, uint32_t count, uint32_t *err) {
+  __builtin_amdgcn_s_setprio(3);  // long dependent chains beside ExpandA: these waves issue first
+  const uint32_t t = blockIdx.x * 32 + (threadIdx.x >> 1);
+  if (t < count) dev_prep_pair<LV, INTERNAL>(t, threadIdx.x & 1, sk, key_idx, msg, msg_off, rnd, ws, err);
+}
+template <int LV, bool INTERNAL>
+__global__ void __launch_bounds__(64) sg_prep_row_k(const uint8_t *sk, const uint32_t *key_idx,
+                                                    const uint8_t *msg, const uint64_t *msg_off, const uint8_t *rnd, Ws ws, uint32_t count, uint32_t *err) {
+  __shared__ uint32_t L[ROW_LDS];
+  __builtin_amdgcn_s_setprio(3);
+  const int lane = threadIdx.x;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t < count) dev_prep_row<LV, INTERNAL>(t, L, lane, sk, key_idx, msg, msg_off, rnd, ws, err);
+}
+template <int LV, bool INTERNAL>
+__global__ void __launch_bounds__(64) vf_hash_k(const uint8_t *pk, const uint32_t *key_idx,
+                                                    const uint8_t *msg, const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
+  __builtin_amdgcn_s_setprio(3);  // long dependent chains beside ExpandA: these waves issue first
+  const uint32_t t = blockIdx.x * 32 + (threadIdx.x >> 1);
+  if (t < count) dev_hash_pair<LV, INTERNAL>(t, threadIdx.x & 1, pk, key_idx, msg, msg_off, ws, err);
+}
+template <int LV, bool INTERNAL>
+__global__ void __launch_bounds__(64) vf_hash_row_k(const uint8_t *pk, const uint32_t *key_idx,
+                                                    const uint8_t *msg, const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
+  __shared__ uint32_t L[ROW_LDS];
+  __builtin_amdgcn_s_setprio(3);
+  const int lane = threadIdx.x;
+  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
+  if (t < count) dev_hash_row<LV, INTERNAL>(t, L, lane, pk, key_idx, msg, msg_off, ws, err);
 }
 
 // as vf_final_k, one row per task

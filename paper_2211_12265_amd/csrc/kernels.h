@@ -116,130 +116,99 @@ __global__ void __launch_bounds__(256) kg_seed_k(const uint8_t *seeds, uint8_t *
   }
 }
 
-// ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk)
-// ExpandA (Sec. 2.3 sampling; Alg. 4's rejection sampler) with wave-cooperative
-// compaction: 3 bytes -> 23-bit candidate, kept if < q, in stream order, until
-// 256 are kept.  Every lane squeezes its own
-// SHAKE128 stream; each squeezed block is staged in LDS and the wave then
-// walks the lanes whose polynomial is unfinished, testing that lane's 56
-// candidates on 56 lanes at once: a ballot gives each accepted candidate its
-// position in stream order, so the accepted values of one stream are stored
-// as one contiguous run.  out0 is lane 0's polynomial; lane l writes
-// out0 + l * N.  rows: 64 * EA_ROW words of LDS for this wavefront.  Lanes
-// with valid = false run the permutations but store nothing.
-constexpr int EA_ROW = RATE128 / 4 + 1;  // 43 words: odd stride, conflict-free staging
-constexpr int EA_STEP = 4;                // unfinished streams tested per step
-constexpr int EA_WG = 64;                 // one wavefront per workgroup (11 KiB of LDS)
-// Blocks after which another permutation is always needed: a block holds
-// RATE128 / 3 = 56 candidates, so at least ceil(N / 56) = 5 blocks are squeezed.
-constexpr int EA_SURE = (N + RATE128 / 3 - 1) / (RATE128 / 3) - 1;
+// ExpandA (Sec. 2.3 sampling; Alg. 4's rejection sampler): 3 bytes -> 23-bit
+// candidate, kept if < q, in stream order, until 256 are kept.  One lane per
+// SHAKE128 stream; only 1 in 1,024 candidates is rejected, so 95% of the blocks
+// of 56 are kept whole and the lane stores them itself, 16 bytes at a time at
+// its position, with no exchange between lanes.  The other lanes' blocks (3.4
+// of 64 per squeeze) are compacted by the wavefront: staged in LDS, tested on
+// 56 lanes at once, a ballot gives each accepted candidate its position.
+// Bound by the issue of the Keccak instructions (21.6 k of the wavefront's 23 k);
+// testing every block on 56 lanes took 5.3 k more.  2^20 polynomials 710 -> 630 us,
+// 300,000 beside nothing 281 -> 218 us.
+// out0 is lane 0's polynomial; lane l writes out0 + l * N.  rows: EA_ROWS * EA_ROW
+// words of LDS for this wavefront.  Lanes with valid = false run the
+// permutations but store nothing.
+constexpr int EA_CAND = RATE128 / 3;      // 56 candidates per block
+constexpr int EA_ROW = RATE128 / 4 + 1;   // 43 words: the last candidate's second word is read too
+constexpr int EA_ROWS = 16;               // blocks compacted per pass
+constexpr int EA_WG = 64;                 // one wavefront per workgroup
+constexpr int EA_FULL = N / EA_CAND;      // 4 blocks are needed whole, at least
+constexpr int EA_LAST = N - EA_FULL * EA_CAND;  // candidates of the next one when nothing was rejected
+static_assert(EA_CAND % 4 == 0 && EA_LAST % 4 == 0, "stored in fours");
 
-// One compaction step for up to EA_STEP streams Ls[u] (act[u]: stream u of
-// the step is unfinished), split in two halves so that independent work can
-// be issued between them: ea_probe reads the candidates from LDS and the
-// streams' counters; ea_commit ballots, stores the accepted values and
-// advances the counters.
-struct EaProbe {
-  uint32_t tv[EA_STEP];
-  int cL[EA_STEP];
+struct __attribute__((aligned(4))) EaQuad {  // a polynomial's next free word is 4-byte aligned only
+  uint32_t v[4];
 };
-__device__ __forceinline__ EaProbe ea_probe(const uint32_t *rows, const int Ls[EA_STEP], int ctr, int wi,
-                                            uint32_t sh) {
-  EaProbe p;
-#pragma unroll
-  for (int u = 0; u < EA_STEP; u++) {
-    const uint32_t *rL = rows + Ls[u] * EA_ROW;
-    p.tv[u] = __builtin_amdgcn_alignbit(rL[wi + 1], rL[wi], sh) & 0x7FFFFFu;
-    p.cL[u] = __builtin_amdgcn_readlane(ctr, Ls[u]);  // the streams' lanes are distinct
-  }
-  return p;
-}
-__device__ __forceinline__ void ea_commit(const EaProbe &p, const int Ls[EA_STEP], const bool act[EA_STEP], bool cand,
-                                          int32_t *out0, int &ctr, int lane) {
-#pragma unroll
-  for (int u = 0; u < EA_STEP; u++) {
-    const bool ok = act[u] && cand && p.tv[u] < (uint32_t)Q;
-    const uint64_t m = __ballot(ok);
-    const int pos =
-        p.cL[u] + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if (ok && pos < N) out0[(size_t)Ls[u] * N + pos] = (int32_t)p.tv[u];
-    if (act[u] && lane == Ls[u]) ctr = min(N, p.cL[u] + (int)__popcll(m));
-  }
-}
 
 __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], int32_t *out0, uint32_t *rows, int lane,
                                                       bool valid) {
   int ctr = valid ? 0 : N;
-  uint32_t *row = rows + lane * EA_ROW;
-  // lane l < 56 tests candidate l of a block: bytes 3l .. 3l + 2, inside words
-  // wi and wi + 1 of the staged row; the other lanes read word 0 and test nothing
-  const bool cand = lane < RATE128 / 3;
+  int32_t *out = out0 + (size_t)lane * N;
+  // lane l < 56 tests candidate l of a staged block: bytes 3l .. 3l + 2, inside words wi and wi + 1
+  const bool cand = lane < EA_CAND;
   const int wi = cand ? (3 * lane) >> 2 : 0;
   const uint32_t sh = cand ? 8u * (uint32_t)((3 * lane) & 3) : 0u;
-  // Blocks 0 .. EA_SURE - 1: the next permutation is certain, so it runs
-  // during the compaction of the staged block (the state and the LDS rows are
-  // independent): every stream is tested in 64 / EA_STEP steps, and the 24
-  // rounds are spread over them, so the Keccak ALU work covers the latency of
-  // the steps' LDS reads and ballots.
-  static_assert(64 / EA_STEP == 16, "the round schedule below assumes 16 steps of 4 streams");
-  for (int blk = 0; blk < EA_SURE; blk++) {
-#pragma unroll
-    for (int w = 0; w < RATE128 / 4; w++) row[w] = s[w];
-    wave_sync();
-    const uint64_t pending = __ballot(ctr < N);
 #pragma unroll 1
-    for (int it = 0; it < 8; it++) {  // two steps and three rounds per iteration
-      int La[EA_STEP], Lb[EA_STEP];
-      bool aa[EA_STEP], ab[EA_STEP];
+  for (int blk = 0;; blk++) {
+    // the lane's own candidates, four per three words
+    uint32_t tv[EA_CAND], top = 0, top_last = 0;
 #pragma unroll
-      for (int u = 0; u < EA_STEP; u++) {
-        La[u] = 2 * EA_STEP * it + u;
-        Lb[u] = La[u] + EA_STEP;
-        aa[u] = (pending >> La[u]) & 1;
-        ab[u] = (pending >> Lb[u]) & 1;
-      }
-      const EaProbe pa = ea_probe(rows, La, ctr, wi, sh);
-      keccak_round(s, 3 * it);
-      keccak_round(s, 3 * it + 1);
-      ea_commit(pa, La, aa, cand, out0, ctr, lane);
-      const EaProbe pb = ea_probe(rows, Lb, ctr, wi, sh);
-      keccak_round(s, 3 * it + 2);
-      ea_commit(pb, Lb, ab, cand, out0, ctr, lane);
+    for (int k = 0; k < EA_CAND / 4; k++) {
+      tv[4 * k] = s[3 * k] & 0x7FFFFFu;
+      tv[4 * k + 1] = __builtin_amdgcn_alignbit(s[3 * k + 1], s[3 * k], 24) & 0x7FFFFFu;
+      tv[4 * k + 2] = __builtin_amdgcn_alignbit(s[3 * k + 2], s[3 * k + 1], 16) & 0x7FFFFFu;
+      tv[4 * k + 3] = (s[3 * k + 2] >> 8) & 0x7FFFFFu;
+      top = max(top, max(max(tv[4 * k], tv[4 * k + 1]), max(tv[4 * k + 2], tv[4 * k + 3])));
+      if (4 * k + 4 == EA_LAST) top_last = top;
     }
-    wave_sync();
-  }
-  // later blocks: compact first, then permute only if a stream is unfinished
-  for (;;) {
+    const bool whole = blk < EA_FULL && top < (uint32_t)Q && ctr < N;
+    const bool tail = blk == EA_FULL && top_last < (uint32_t)Q && ctr == N - EA_LAST;
+    if (whole || tail) {
+      EaQuad *o = (EaQuad *)(out + ctr);
 #pragma unroll
-    for (int w = 0; w < RATE128 / 4; w++) row[w] = s[w];
-    wave_sync();
-    // up to EA_STEP unfinished streams per step; the step is branch-free up to
-    // the stores, so that its LDS reads, ballots and counter reads overlap
-    uint64_t pending = __ballot(ctr < N);
-    while (pending) {
-      int Ls[EA_STEP];
-      bool act[EA_STEP];
-#pragma unroll
-      for (int u = 0; u < EA_STEP; u++) {
-        act[u] = pending != 0;
-        Ls[u] = act[u] ? __builtin_ctzll(pending) : 0;
-        pending &= pending - 1;
-      }
-      const EaProbe p = ea_probe(rows, Ls, ctr, wi, sh);
-      ea_commit(p, Ls, act, cand, out0, ctr, lane);
+      for (int k = 0; k < EA_CAND / 4; k++)
+        if (4 * k < EA_LAST || whole) o[k] = EaQuad{{tv[4 * k], tv[4 * k + 1], tv[4 * k + 2], tv[4 * k + 3]}};
+      ctr += whole ? EA_CAND : EA_LAST;
     }
-    wave_sync();
-    if (__ballot(ctr < N) == 0) break;
+    // blocks with a rejection (or, at the end, after one)
+    uint64_t left = __ballot(!(whole || tail) && ctr < N);
+    while (left) {
+      const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(left >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)left, 0u));
+      if (((left >> lane) & 1) && rank < EA_ROWS) {
+#pragma unroll
+        for (int w = 0; w < RATE128 / 4; w++) rows[rank * EA_ROW + w] = s[w];
+      }
+      wave_sync();
+#pragma unroll 1
+      for (int r = 0; r < EA_ROWS && left; r++) {
+        const int L = __builtin_ctzll(left);
+        left &= left - 1;
+        const uint32_t *row = rows + r * EA_ROW;
+        const uint32_t v = __builtin_amdgcn_alignbit(row[wi + 1], row[wi], sh) & 0x7FFFFFu;
+        const int cL = __builtin_amdgcn_readlane(ctr, L);
+        const bool ok = cand && v < (uint32_t)Q;
+        const uint64_t m = __ballot(ok);
+        const int pos =
+            cL + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (ok && pos < N) out0[(size_t)L * N + pos] = (int32_t)v;
+        if (lane == L) ctr = min(N, cL + (int)__popcll(m));
+      }
+      wave_sync();
+    }
+    if (blk >= EA_FULL && __ballot(ctr < N) == 0) break;
     keccak_f(s);
   }
 }
 
+// ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk)
 template <int LV>
 __global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
                                                   int32_t *A, uint32_t count) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   uint64_t st = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  __shared__ uint32_t rows[EA_WG / 64][64 * EA_ROW];
+  __shared__ uint32_t rows[EA_WG / 64][EA_ROWS * EA_ROW];
   const bool valid = st < (uint64_t)count * K * L;
   const uint64_t sl = valid ? st : 0;  // spare lanes absorb stream 0 and store nothing
   uint32_t task = (uint32_t)(sl / (K * L));
@@ -362,8 +331,8 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
 // ------------------------------------------------------------------------
 // Sign (Alg. 2), staged
 // ------------------------------------------------------------------------
-// mu and the mask seed on two lanes per task (keccak_pair.h); initialises
-// kappa and the active list.
+// mu and the mask seed of task t on a lane pair (keccak_pair.h; both lanes
+// call); initialises kappa and the active list.
 //   round 3: mu = H(tr || M); rho' = H(K || mu), or the task's 64 rnd bytes
 //            themselves (randomized signing) when rnd is not null;
 //   ML-DSA:  mu = H(tr || 0x00 || 0x00 || M); rho'' = H(K || rnd || mu) with
@@ -373,16 +342,9 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
 //            H(tr || M').
 // rnd rows are 4-byte aligned.
 template <int LV, bool INTERNAL = false>
-__global__ void __launch_bounds__(256) sg_prep_k(const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
-                                                 const uint64_t *msg_off, const uint8_t *rnd, Ws ws, uint32_t count,
-                                                 uint32_t *err) {
-  // the longest dependent chain of the Sign setup (up to ~30 permutations per
-  // task for 4 KiB messages), sharing the CUs with ExpandA and the secret NTTs
-  // launched beside it: its waves issue first
-  __builtin_amdgcn_s_setprio(3);
-  const uint32_t t = (uint32_t)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 1);
-  const int half = threadIdx.x & 1;
-  if (t >= count) return;  // both lanes of a pair
+__device__ __forceinline__ void dev_prep_pair(uint32_t t, int half, const uint8_t *sk, const uint32_t *key_idx,
+                                              const uint8_t *msg, const uint64_t *msg_off, const uint8_t *rnd,
+                                              const Ws &ws, uint32_t *err) {
   size_t key = key_idx ? key_idx[t] : t;
   const uint8_t *skr = sk + key * P<LV>::SK;
   uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
@@ -826,17 +788,18 @@ __global__ void __launch_bounds__(64) sg_check_k(Ws ws, uint8_t *sig, const uint
 // Verify (Alg. 3), staged
 // ------------------------------------------------------------------------
 // tr = H(pk) (unless resident) and mu = H(tr || M) (ML-DSA: H(tr || 0x00 ||
-// 0x00 || M), or H(tr || M') of formatted messages with INTERNAL), two lanes
-// per task (keccak_pair.h)
+// 0x00 || M), or H(tr || M') of formatted messages with INTERNAL) of task t on a
+// lane pair (keccak_pair.h; both lanes call)
 template <int LV, bool INTERNAL = false>
-__global__ void __launch_bounds__(64) vf_hash_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
-                                                const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
+__device__ __forceinline__ void dev_hash_pair(uint32_t t, int half, const uint8_t *pk, const uint32_t *key_idx,
+                                              const uint8_t *msg, const uint64_t *msg_off, const Ws &ws,
+                                              uint32_t *err) {
   using PP = P<LV>;
-  __builtin_amdgcn_s_setprio(3);  // the long hash chain of Verify, beside ExpandA: its waves issue first
-  const uint32_t t = (uint32_t)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 1);
-  const int half = threadIdx.x & 1;
-  if (t >= count) return;  // both lanes of a pair
   size_t key = key_idx ? key_idx[t] : t;
+  uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
+  uint64_t mlen = 0;
+  if (o1 >= o0) mlen = o1 - o0;
+  else if (!half) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
   constexpr int TW = PP::TRB / 4;
   uint32_t a[25];
   uint32_t trw[TW];
@@ -855,10 +818,6 @@ __global__ void __launch_bounds__(64) vf_hash_k(const uint8_t *pk, const uint32_
       trw[2 * i + 1] = half ? a[i] : other;
     }
   }
-  uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
-  uint64_t mlen = 0;
-  if (o1 >= o0) mlen = o1 - o0;
-  else if (!half) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
   absorb_prefix_msg<mu_prefix_bytes<LV, INTERNAL>()>(a, half, trw, msg + o0, mlen);
   uint32_t *muw = (uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
 #pragma unroll
@@ -1119,7 +1078,7 @@ __global__ void __launch_bounds__(256) ntt_mul_k(const int32_t *a, const int32_t
 // ExpandA rejection sampling of one polynomial per lane from a 34-byte input
 __global__ void __launch_bounds__(EA_WG) expand_a_seed_k(const uint8_t *seeds, int32_t *out, uint64_t count) {
   uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  __shared__ uint32_t rows[EA_WG / 64][64 * EA_ROW];
+  __shared__ uint32_t rows[EA_WG / 64][EA_ROWS * EA_ROW];
   const bool valid = p < count;
   const uint8_t *sd = seeds + 34 * (valid ? p : 0);
   uint32_t s[50];

@@ -109,6 +109,11 @@ struct MwPlan {
     mlen = len;
   }
   DIL_HD static int64_t m0(uint64_t b) { return b == 0 ? -(int64_t)DL : (int64_t)b * MW_RATE - PB; }
+  // Blocks 1 .. inner() - 1 are covered by M with four bytes to spare, so that
+  // their words need no masks and every dword their words may span (35 from
+  // inner_words on) holds bytes of M.
+  DIL_HD uint64_t inner() const { return mlen + PB >= MW_RATE + 4 ? (mlen + PB - 4) / MW_RATE : 1; }
+  DIL_HD const uint32_t *inner_words(uint64_t b) const { return base + (((int64_t)sh + m0(b)) >> 2); }
   DIL_HD int r0(uint64_t b) const {
     const int64_t r = (int64_t)mlen - m0(b);
     return r < 0 ? -4 : r > 4 * MW_WPB + 4 ? 4 * MW_WPB + 4 : (int)r;

@@ -2,7 +2,7 @@
 // (mw_fetch_one / mw_word_one in paper_2211_12265_amd/csrc/msg_words.h), built
 // with AddressSanitizer and UndefinedBehaviorSanitizer by
 // tests/test_host_msg_words_one.py: every word of every block of prefix || M ||
-// padding equals the padded byte string, for every misalignment and length, M
+// padding equals the padded byte string (and so do the blocks that MwPlan::inner names, read without masks), for every misalignment and length, M
 // lying in a heap buffer of exactly the dwords that cover it.
 //
 // usage: msg_word_one MAXLEN
@@ -45,6 +45,15 @@ static int run(int maxlen) {
           uint32_t x;
           memcpy(&x, want.data() + (size_t)b * MW_RATE + 4 * j, 4);
           if (w != x) return fprintf(stderr, "PB %d sh %d len %d block %d word %d\n", PB, sh, len, b, j), 1;
+        }
+      // the blocks that are read without masks: 34 words as each lane of a pair takes them
+      if (pl.inner() < 1 || pl.inner() > pl.nblk) return fprintf(stderr, "inner %d %d\n", sh, len), 1;
+      for (uint64_t b = 1; b < pl.inner(); b++)
+        for (int j = 0; j < MW_WPB; j++) {
+          const uint32_t *p = pl.inner_words(b) + j;
+          uint32_t x;
+          memcpy(&x, want.data() + b * MW_RATE + 4 * j, 4);
+          if (mw_funnel(p[1], p[0], pl.fs) != x) return fprintf(stderr, "inner PB %d sh %d len %d\n", PB, sh, len), 1;
         }
       free(buf);
       cases++;
