@@ -74,8 +74,8 @@ struct dil_keyset {
   void *mem = nullptr;
   uint8_t *pk = nullptr, *sk = nullptr, *tr = nullptr;   // key rows (copies) and tr = H(pk)
   size_t bytes = 0;                                      // device memory held
-  int32_t *A = nullptr, *t1h = nullptr;
-  int8_t *sec = nullptr;
+  int32_t *A = nullptr;
+  int8_t *sec = nullptr, *t1s = nullptr;
 };
 
 namespace {
@@ -273,7 +273,7 @@ int ws_carve(dil_ctx *ctx, hipStream_t st, size_t cap, int form, bool keyset, Ws
   const size_t got = ws_layout<LV>((uint8_t *)ctx->ws_mem, cap, form, keyset, grid, waves, &ws, sc, kidx, group);
   if (got > ctx->ws_bytes) return fail(ctx, DIL_ENOMEM, "workspace layout overflow");
   ws.kmap = nullptr;
-  ws.t1h = nullptr;
+  ws.t1s = nullptr;
   ws.tr = nullptr;
   return DIL_OK;
 }
@@ -408,7 +408,7 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
 const uint32_t *use_keyset(Ws &ws, const dil_keyset *ks, const uint32_t *key_idx, uint32_t *checked) {
   ws.A = ks->A;
   ws.sec = ks->sec;
-  ws.t1h = ks->t1h;
+  ws.t1s = ks->t1s;
   ws.tr = ks->tr;
   ws.kmap = key_idx ? checked : nullptr;
   return ws.kmap;
@@ -817,7 +817,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   auto rnd = [](size_t b) { return (b + 255) & ~(size_t)255; };
   bytes += rnd(n * K * L * 1024);
   if (sk) bytes += rnd(n * PP::SK) + rnd(n * sec_bytes<LV>());
-  if (pk) bytes += rnd(n * PP::PK) + rnd(n * K * 1024);
+  if (pk) bytes += rnd(n * PP::PK) + rnd(n * TILE_BYTES);
   bytes += rnd(n * PP::TRB);
   hipError_t e = hipMalloc(&ks->mem, bytes);
   if (e != hipSuccess) {
@@ -840,7 +840,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   }
   if (pk) {
     ks->pk = take(n * PP::PK);
-    ks->t1h = (int32_t *)take(n * K * 1024);
+    ks->t1s = (int8_t *)take(n * TILE_BYTES);
     HIPCHK(ctx, hipMemcpyAsync(ks->pk, pk, n * PP::PK, hipMemcpyDeviceToDevice, st));
   }
   unsigned nb = blocks_for(n * K * L, EA_WG);
@@ -853,7 +853,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
     expand_a_k<LV><<<nb, EA_WG, 0, st>>>(ks->pk, PP::PK, nullptr, ks->A, ks->nkeys);
   }
   if (pk) {
-    ks_pk_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->pk, ks->t1h, ks->nkeys);
+    ks_pk_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->pk, ks->t1s, ks->nkeys);
     launch_tr<LV>(st, ks->pk, ks->tr, PP::TRB, ks->nkeys);
   } else {
     HIPCHK(ctx, hipMemcpy2DAsync(ks->tr, PP::TRB, ks->sk + 64, PP::SK, PP::TRB, n, hipMemcpyDeviceToDevice, st));
@@ -1169,7 +1169,7 @@ int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_
   uint32_t *kid = nullptr;
   ws_layout<LV>(ctx->scratch, count, WS_VERIFY, true, 0, 1, &ws, nullptr, &kid);
   ws.kmap = nullptr;
-  ws.t1h = nullptr;
+  ws.t1s = nullptr;
   ws.tr = nullptr;
   const uint32_t *kidx = use_keyset(ws, ks, key_idx, kid);
   zero_words_k<<<1, 64, 0, st>>>(ws.counters, 16, nullptr, 0);

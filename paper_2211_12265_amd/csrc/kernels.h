@@ -35,10 +35,10 @@ struct Ws {
   uint32_t *counters;           // [8]: next active count, error flags, attempts
   size_t cap;
   size_t muw1_stride;
-  // Resident key tables: when kmap is set, A, sec (and t1h, tr) are
+  // Resident key tables: when kmap is set, A, sec (and t1s, tr) are
   // indexed by key row kmap[task] instead of by task.
   const uint32_t *kmap;
-  const int32_t *t1h;   // [keys][K][256] NTT(t1 2^d), slots layout (verify), or null
+  const int8_t *t1s;    // [keys][TILE_BYTES] t1 as an int8 tile (verify), or null
   const uint8_t *tr;    // [keys][TRB] tr = H(pk) (verify), or null
 };
 
@@ -824,26 +824,17 @@ __device__ __forceinline__ void dev_hash_pair(uint32_t t, int half, const uint8_
   for (int i = 0; i < 8; i++) muw[2 * i + half] = a[i];
 }
 
-// c = SampleInBall(ctilde) and strict hint decoding, one lane per task
+// c = SampleInBall(ctilde), one lane per task
 template <int LV>
 __global__ void __launch_bounds__(64) vf_prep_k(const uint8_t *sig, Ws ws, uint32_t count) {
   using PP = P<LV>;
-  constexpr int K = Lv<LV>::K, OMEGA = Lv<LV>::OMEGA;
-  constexpr int HB = OMEGA + K;        // hint section bytes
-  constexpr int HMW = K * 8 + 1;       // mask words per lane (+1: odd stride)
   __shared__ int8_t cl[64][C_ROW];
   __shared__ uint32_t bb[64][RATE256 / 4];
-  __shared__ uint8_t hbl[64][HB];
-  __shared__ uint32_t hml[64][HMW];
   uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= count) return;
   const uint8_t *sg = sig + (size_t)t * PP::SIG;
-  // the hint bytes are fetched now (independent loads, one wait) and decoded from LDS at the end
-  uint8_t *hb = hbl[threadIdx.x];
-#pragma unroll
-  for (int j = 0; j < HB; j++) hb[j] = sg[PP::OFF_H + j];
   uint32_t s[50];
-  // SampleInBall(ctilde), all CT bytes of it
+  // all CT bytes of ctilde
   keccak_zero(s);
 #pragma unroll
   for (int w = 0; w < PP::CT / 8; w++) {
@@ -857,75 +848,78 @@ __global__ void __launch_bounds__(64) vf_prep_k(const uint8_t *sig, Ws ws, uint3
   int8_t *c = cl[threadIdx.x];
   sample_in_ball<Lv<LV>::TAU>(s, c, (uint8_t *)bb[threadIdx.x]);
   store_c_row(c, ws.cpoly + (size_t)t * N);
-  // strict hint decoding into bit masks (built in LDS, then stored row-wise)
-  uint32_t *hml_t = hml[threadIdx.x];
-#pragma unroll
-  for (int w = 0; w < K * 8; w++) hml_t[w] = 0;
-  int ok = 1, prev = 0;
-  for (int i = 0; i < K; i++) {
-    int cnt = hb[OMEGA + i];
-    if (cnt < prev || cnt > OMEGA) {
-      ok = 0;
-      break;
-    }
-    for (int j = prev; j < cnt; j++) {
-      if (j > prev && hb[j] <= hb[j - 1]) ok = 0;
-      hml_t[i * 8 + (hb[j] >> 5)] |= 1u << (hb[j] & 31);
-    }
-    prev = cnt;
-  }
-  if (ok)
-    for (int j = prev; j < OMEGA; j++)
-      if (hb[j] != 0) ok = 0;
-  uint32_t *hm = ws.hmask + (size_t)t * K * 8;
-#pragma unroll
-  for (int w = 0; w < K * 8; w++) hm[w] = hml_t[w];
-  ws.flag[t] = ok;
 }
 
-// w1' = UseHint(h, INTT(A NTT(z) - c-hat NTT(t1 2^d))), packed after mu; z norm check
+// Strict decoding of the OMEGA + K hint bytes hb (LDS) into hm[K][8] (LDS, bit
+// masks) by one wavefront, byte j on lane j mod 64.  Returns whether this
+// lane's bytes break a rule: counts non-decreasing and at most OMEGA, indices
+// strictly increasing within a polynomial, unused bytes zero.
 template <int LV>
-__global__ void __launch_bounds__(64) vf_main_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *sig, Ws ws,
+__device__ __forceinline__ bool dev_decode_hints(const uint8_t *hb, uint32_t *hm, int lane) {
+  constexpr int K = Lv<LV>::K, OMEGA = Lv<LV>::OMEGA;
+  static_assert(8 * K <= 64 && OMEGA <= 128, "one mask word and two hint bytes per lane at most");
+  if (lane < 8 * K) hm[lane] = 0;
+  wave_sync();
+  bool bad = false;
+  int cnt[K], prev = 0;
+#pragma unroll
+  for (int i = 0; i < K; i++) {
+    cnt[i] = hb[OMEGA + i];
+    bad |= cnt[i] < prev || cnt[i] > OMEGA;
+    prev = cnt[i];
+  }
+#pragma unroll
+  for (int q = 0; q < 2; q++) {
+    const int j = lane + 64 * q;
+    if (j < OMEGA) {
+      const uint32_t v = hb[j];
+      int i = 0, start = 0;  // polynomial of byte j and its first byte
+#pragma unroll
+      for (int p = 0; p < K; p++)
+        if (j >= cnt[p]) {
+          i = p + 1;
+          start = cnt[p];
+        }
+      if (i >= K) bad |= v != 0;
+      else {
+        if (j > start) bad |= v <= hb[j - 1];
+        atomicOr(&hm[8 * i + (v >> 5)], 1u << (v & 31));
+      }
+    }
+  }
+  wave_sync();
+  return bad;
+}
+
+// w1' = UseHint(h, INTT(A NTT(z)) - c t1 2^d), packed after mu; z norm check and
+// hint decoding.  One wavefront per task.  c t1 comes from the matrix cores
+// (toeplitz.h) after the INTT, which leaves two NTT passes of four polynomials
+// per four rows: NTT(c) and NTT(t1 2^d) ran as two more.
+template <int LV>
+__global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *sig, Ws ws,
                                                 uint32_t count) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, BETA = Lv<LV>::BETA;
   constexpr int32_t G1 = Lv<LV>::GAMMA1;
-  // The signature's bytes are read only to unpack z; t1 (from pk) and the
-  // packed w1' rows are used only after that, so the three share one region
-  // (less LDS per workgroup, more resident workgroups).  pk is fetched into
-  // registers up front and written to the region once z is unpacked.
-  constexpr int SIGW = PP::SIG / 4 + 3, PKW = PP::PK / 4, W1W = K * PP::W1B / 4 + 1;
-  constexpr int PKPER = (PKW + 63) / 64;
-  __shared__ int32_t trl[4 * NTT_LDS_GROUP];
+  // The signature's bytes are dead once z and the hints are unpacked; the
+  // copies of the challenge and the packed w1' rows take their place.
+  constexpr int SIGW = PP::SIG / 4 + 3, W1W = K * PP::W1B / 4 + 1, TW = TOEP_WORDS + 132;
+  __shared__ __align__(16) int32_t trl[4 * NTT_LDS_GROUP];
   __shared__ int32_t zh[L * HAT_POLY];
-  __shared__ uint32_t region[SIGW > PKW + 2 + W1W ? SIGW : PKW + 2 + W1W];
-  uint32_t *const sigw = region, *const pkw = region, *const w1b = region + PKW + 2;
+  __shared__ __align__(16) uint32_t region[SIGW > TW + W1W ? SIGW : TW + W1W];
+  __shared__ uint32_t hm[8 * K];
+  uint32_t *const sigw = region, *const ct = region, *const w1b = region + TW;
   uint32_t task = blockIdx.x;
   if (task >= count) return;
   int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
   int32_t *tr = trl + g * NTT_LDS_GROUP;
-  size_t key = key_idx ? key_idx[task] : task;
-  uint32_t pkv[PKPER];
-  if (!ws.t1h) {
-    const uint32_t *pkg = (const uint32_t *)(pk + key * PP::PK);
-#pragma unroll
-    for (int q = 0; q < PKPER; q++) {
-      const int i = lane + 64 * q;
-      pkv[q] = i < PKW ? pkg[i] : 0u;
-    }
-  }
+  const size_t key = key_idx ? key_idx[task] : task;
   g2l_bytes<PP::SIG>(sig + (size_t)task * PP::SIG, sigw, lane);
   if (lane < 2) sigw[PP::SIG / 4 + 1 + lane] = 0;
+  const uint32_t cw = ((const uint32_t *)(ws.cpoly + (size_t)task * N))[lane];
   wave_sync();
+  bool bad = dev_decode_hints<LV>((const uint8_t *)sigw + PP::OFF_H, hm, lane);
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
-  int32_t ch[16];
-  {
-    const int8_t *cp = ws.cpoly + (size_t)task * N;
-#pragma unroll
-    for (int r = 0; r < 16; r++) ch[r] = cp[t + 16 * r];
-    ntt16(ch, ftw, tr, t);
-  }
-  bool bad = false;
   for (int j = g; j < L; j += 4) {
     uint32_t v[16];
     unpack_strided<PP::ZBITS>(sigw + (PP::OFF_Z + j * PP::ZB) / 4, v, t);
@@ -942,17 +936,31 @@ __global__ void __launch_bounds__(64) vf_main_k(const uint8_t *pk, const uint32_
   }
   bad = wave_any(bad);
   wave_sync();
-  if (!ws.t1h) {  // z is unpacked: the region now takes t1
+  // c t1: two parts of every coefficient, rows g (and g + 4) for the group
+  int32_t lo[K > 4 ? 2 : 1][16];
+  {
+    v4i s[4];
+    if (ws.t1s) toep_load(s, ws.t1s + key * TILE_BYTES, lane);
+    else toep_load_t1<LV>(s, (const uint32_t *)(pk + key * PP::PK) + 8, lane);
+    toep_build(cw, ct, ct + TOEP_WORDS, lane);
+    auto half = [&](auto I0c) {
+      constexpr int I0 = decltype(I0c)::value;
+      v4i acc[8];
+      toep_mul<I0, 8>(acc, s, ct, lane);
 #pragma unroll
-    for (int q = 0; q < PKPER; q++) {
-      const int i = lane + 64 * q;
-      if (i < PKW) pkw[i] = pkv[q];
-    }
-    if (lane < 2) pkw[PKW + lane] = 0;
-    wave_sync();
+      for (int r = 0; r < 8; r++) {
+        lo[0][I0 + r] = acc[r][0] + 32 * acc[r][1];
+        if constexpr (K > 4) lo[1][I0 + r] = acc[r][2] + 32 * acc[r][3];
+      }
+    };
+    half(std::integral_constant<int, 0>{});
+    __builtin_amdgcn_sched_barrier(0);
+    half(std::integral_constant<int, 8>{});
   }
-  const uint32_t *hm = ws.hmask + (size_t)task * K * 8;
-  for (int i = g; i < K; i += 4) {
+#pragma unroll
+  for (int q = 0; q < (K + 3) / 4; q++) {
+    const int i = g + 4 * q;
+    if (i >= K) break;
     const int32_t *Ai = ws.A + (kix(ws, task) * K + i) * L * N;
     int64_t acc[16];
 #pragma unroll
@@ -964,33 +972,18 @@ __global__ void __launch_bounds__(64) vf_main_k(const uint8_t *pk, const uint32_
       for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * zh[hat_idx(j, t, r)];
     }
     int32_t x[16];
-    if (ws.t1h) {
-      load_slots(x, ws.t1h + (kix(ws, task) * K + i) * N, t);
-    } else {
-      uint32_t v[16];
-      unpack_strided<10>(pkw + (32 + i * PP::T1B) / 4, v, t);
 #pragma unroll
-      for (int r = 0; r < 16; r++) x[r] = (int32_t)(v[r] << D);
-      ntt16(x, ftw, tr, t);
-    }
-    // transpose-free: t1-hat comes out in slots layout like acc
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      int32_t d = mont_reduce(acc[r]) - mont_mul(ch[r], x[r]);  // in (-2q, 2q)
-      d += (d <= -Q) ? Q : 0;
-      d -= (d >= Q) ? Q : 0;
-      x[r] = d;
-    }
+    for (int r = 0; r < 16; r++) x[r] = mont_reduce(acc[r]);
     intt16(x, itw, tr, t);
     int32_t w1[16];
     uint32_t hw[8];
 #pragma unroll
-    for (int q = 0; q < 8; q++) hw[q] = hm[i * 8 + q];
+    for (int p = 0; p < 8; p++) hw[p] = hm[i * 8 + p];
 #pragma unroll
     for (int r = 0; r < 16; r++) {
       int c = t + 16 * r;
       int32_t h = (hw[c >> 5] >> (c & 31)) & 1;
-      w1[r] = use_hint<LV>(h, canon(x[r]));
+      w1[r] = use_hint<LV>(h, sub_ct1(canon(x[r]), lo[q][r]));
     }
     uint32_t vv[16];
     to_consecutive(w1, vv, tr, t);
@@ -999,7 +992,7 @@ __global__ void __launch_bounds__(64) vf_main_k(const uint8_t *pk, const uint32_
   wave_sync();
   uint32_t *dst = (uint32_t *)(ws.muw1 + (size_t)task * muw1_stride<LV>() + 64);
   for (int w = lane; w < K * PP::W1B / 4; w += 64) dst[w] = w1b[w];
-  if (lane == 0 && bad) ws.flag[task] = 0;
+  if (lane == 0) ws.flag[task] = !bad;
 }
 
 // ctilde' = H(mu || w1'), verdict; two lanes per task (keccak_pair.h), the
@@ -1023,30 +1016,17 @@ __global__ void __launch_bounds__(256) vf_final_k(const uint8_t *sig, Ws ws, int
 // ------------------------------------------------------------------------
 // Resident key tables
 // ------------------------------------------------------------------------
-// NTT(t1 2^d) (slots layout) for every key row of a table
+// t1 as an int8 tile (toeplitz.h) for every key row of a table
 template <int LV>
-__global__ void __launch_bounds__(64) ks_pk_k(const uint8_t *pk, int32_t *t1h, uint32_t nkeys) {
-  using PP = P<LV>;
-  constexpr int K = Lv<LV>::K;
-  __shared__ int32_t trl[4 * NTT_LDS_GROUP];
-  __shared__ uint32_t pkw[PP::PK / 4 + 2];
-  uint32_t key = blockIdx.x;
+__global__ void __launch_bounds__(64) ks_pk_k(const uint8_t *pk, int8_t *t1s, uint32_t nkeys) {
+  const uint32_t key = blockIdx.x;
   if (key >= nkeys) return;
-  int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
-  const uint32_t *pkg = (const uint32_t *)(pk + (size_t)key * PP::PK);
-  g2l_words<PP::PK / 4>(pkg, pkw, lane);
-  if (lane < 2) pkw[PP::PK / 4 + lane] = 0;
-  wave_sync();
-  const Tw ftw = ntt_lane_tw(t);
-  for (int i = g; i < K; i += 4) {
-    uint32_t v[16];
-    unpack_strided<10>(pkw + (32 + i * PP::T1B) / 4, v, t);
-    int32_t x[16];
+  const int lane = threadIdx.x;
+  v4i s[4];
+  toep_load_t1<LV>(s, (const uint32_t *)(pk + (size_t)key * P<LV>::PK) + 8, lane);
+  int8_t *out = t1s + (size_t)key * TILE_BYTES + (lane & 15) * N + 16 * (lane >> 4);
 #pragma unroll
-    for (int r = 0; r < 16; r++) x[r] = (int32_t)(v[r] << D);
-    ntt16(x, ftw, trl + g * NTT_LDS_GROUP, t);
-    store_slots(x, t1h + ((size_t)key * K + i) * N, t);
-  }
+  for (int J = 0; J < 4; J++) *(v4i *)(out + 64 * J) = s[J];
 }
 
 // ------------------------------------------------------------------------

@@ -93,4 +93,40 @@ constexpr int TILE_BYTES = 16 * N;
 template <int LV>
 constexpr size_t sec_bytes() { return (size_t)sec_tiles<LV>() * TILE_BYTES; }
 
+// Verify's t1 = lo + 32 hi (5 bits each), one tile for all K <= 8 polynomials:
+// parts 0 / 1 of group g are lo / hi of polynomial g, parts 2 / 3 those of
+// polynomial g + 4.  The lane's operands come straight from the packed public
+// key: 16 coefficients are five of its words.  t1 = pk + 32 bytes.
+template <int LV>
+__device__ __forceinline__ void toep_load_t1(v4i s[4], const uint32_t *t1, int lane) {
+  constexpr int K = Lv<LV>::K, T1W = 320 / 4;
+  const int n = lane & 15, kg = lane >> 4, p = (n >> 2) + 4 * ((n >> 1) & 1), sh = 5 * (n & 1);
+  const uint32_t *src = t1 + (p < K ? p : 0) * T1W + 5 * kg;
+#pragma unroll
+  for (int J = 0; J < 4; J++) {
+    uint32_t w[5];
+#pragma unroll
+    for (int q = 0; q < 5; q++) w[q] = src[20 * J + q];
+#pragma unroll
+    for (int d = 0; d < 4; d++) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int b = 0; b < 4; b++) {
+        const int c = 10 * (4 * d + b), i = c >> 5;  // bit of the coefficient in the five words
+        const uint32_t f = __builtin_amdgcn_alignbit(w[i + 1 < 5 ? i + 1 : 4], w[i], c & 31) >> sh;
+        v |= (f & 31u) << (8 * b);
+      }
+      s[J][d] = p < K ? (int)v : 0;
+    }
+  }
+}
+// x - 2^13 c t1 mod q in [0, q) of one coefficient (x in [0, q)):
+// |c t1| <= tau 1023 < 2^16, so the product fits 30 bits, and z - (z + 2^22 >> 23) q lies in (-q, q)
+// for |z| < 2^31 - 2^22 (2^23 = q + 2^13 - 1).
+__device__ __forceinline__ int32_t sub_ct1(int32_t x, int32_t ct1) {
+  int32_t z = x - ct1 * (1 << D);
+  z -= ((z + (1 << 22)) >> 23) * Q;
+  return canon(z);
+}
+
 }  // namespace dil
