@@ -74,7 +74,7 @@ struct dil_keyset {
   void *mem = nullptr;
   uint8_t *pk = nullptr, *sk = nullptr, *tr = nullptr;   // key rows (copies) and tr = H(pk)
   size_t bytes = 0;                                      // device memory held
-  int32_t *A = nullptr;
+  uint8_t *A = nullptr;
   int8_t *sec = nullptr, *t1s = nullptr;
 };
 
@@ -186,7 +186,7 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.rhop = take(sign || form == WS_KEYGEN, cap * 64);
   w.ctilde = take(staged, cap * CT_STRIDE);
   w.cpoly = (int8_t *)take(staged || form == WS_VERIFY, cap * 256);
-  w.A = (int32_t *)take(!keyset, cap * K * L * 1024);
+  w.A = take(!keyset, cap * K * L * A_POLY);
   w.s12 = (int32_t *)take(form == WS_KEYGEN, cap * (L + K) * 1024);
   w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
   w.y = take(staged, cap * L * P<LV>::YB);
@@ -815,7 +815,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
   size_t n = ks->nkeys;
   size_t bytes = 0;
   auto rnd = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  bytes += rnd(n * K * L * 1024);
+  bytes += rnd(n * K * L * A_POLY);
   if (sk) bytes += rnd(n * PP::SK) + rnd(n * sec_bytes<LV>());
   if (pk) bytes += rnd(n * PP::PK) + rnd(n * TILE_BYTES);
   bytes += rnd(n * PP::TRB);
@@ -831,7 +831,7 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
     p += rnd(b);
     return r;
   };
-  ks->A = (int32_t *)take(n * K * L * 1024);
+  ks->A = take(n * K * L * A_POLY);
   ks->tr = take(n * PP::TRB);
   if (sk) {
     ks->sk = take(n * PP::SK);

@@ -23,7 +23,7 @@ struct Ws {
   uint8_t *rhop;     // [cap][64]   rho' (KeyGen: expanded secret seed; Sign: mask seed)
   uint8_t *ctilde;   // [cap][CT_STRIDE]
   int8_t *cpoly;     // [cap][256]  challenge c, dense
-  int32_t *A;        // [cap][K][L][256]  A-hat, canonical
+  uint8_t *A;        // [cap][K][L][A_POLY]  A-hat, 24 bits per coefficient (load_a)
   int32_t *s12;      // KeyGen: s1, s2 centred, [cap][L+K][256]
   int8_t *sec;       // [cap][sec_bytes] Sign: s1, s2, t0 as int8 tiles (toeplitz.h)
   uint8_t *y;        // [cap][L][YB]  mask, as squeezed
@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(256) kg_seed_k(const uint8_t *seeds, uint8_t *
 // Bound by the issue of the Keccak instructions (21.6 k of the wavefront's 23 k);
 // testing every block on 56 lanes took 5.3 k more.  2^20 polynomials 710 -> 630 us,
 // 300,000 beside nothing 281 -> 218 us.
-// out0 is lane 0's polynomial; lane l writes out0 + l * N.  rows: EA_ROWS * EA_ROW
+// out0 is lane 0's polynomial, lane l's the l-th after it.  rows: EA_ROWS * EA_ROW
 // words of LDS for this wavefront.  Lanes with valid = false run the
 // permutations but store nothing.
 constexpr int EA_CAND = RATE128 / 3;      // 56 candidates per block
@@ -135,16 +135,26 @@ constexpr int EA_ROWS = 16;               // blocks compacted per pass
 constexpr int EA_WG = 64;                 // one wavefront per workgroup
 constexpr int EA_FULL = N / EA_CAND;      // 4 blocks are needed whole, at least
 constexpr int EA_LAST = N - EA_FULL * EA_CAND;  // candidates of the next one when nothing was rejected
-static_assert(EA_CAND % 4 == 0 && EA_LAST % 4 == 0, "stored in fours");
+static_assert(EA_CAND % 4 == 0 && EA_LAST % 16 == 0, "stored in fours, and in 16 bytes when packed");
 
-struct __attribute__((aligned(4))) EaQuad {  // a polynomial's next free word is 4-byte aligned only
+// 16 bytes at a polynomial's next free place, which a rejection leaves at any byte
+template <int ALIGN>
+struct __attribute__((packed, aligned(ALIGN))) EaQuad {
   uint32_t v[4];
 };
+template <int ALIGN>
+struct __attribute__((packed, aligned(ALIGN))) EaPair {
+  uint32_t v[2];
+};
 
-__device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], int32_t *out0, uint32_t *rows, int lane,
+// PACKED: polynomials of A_POLY bytes, 24 bits per coefficient as squeezed (bit 23
+// is not part of it), else 256 words each.
+template <bool PACKED>
+__device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], uint8_t *out0, uint32_t *rows, int lane,
                                                       bool valid) {
+  constexpr int POLY = PACKED ? A_POLY : 4 * N, CB = PACKED ? 3 : 4;  // bytes per polynomial, per coefficient
   int ctr = valid ? 0 : N;
-  int32_t *out = out0 + (size_t)lane * N;
+  uint8_t *out = out0 + (size_t)lane * POLY;
   // lane l < 56 tests candidate l of a staged block: bytes 3l .. 3l + 2, inside words wi and wi + 1
   const bool cand = lane < EA_CAND;
   const int wi = cand ? (3 * lane) >> 2 : 0;
@@ -165,10 +175,19 @@ __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], int32_t *o
     const bool whole = blk < EA_FULL && top < (uint32_t)Q && ctr < N;
     const bool tail = blk == EA_FULL && top_last < (uint32_t)Q && ctr == N - EA_LAST;
     if (whole || tail) {
-      EaQuad *o = (EaQuad *)(out + ctr);
+      uint8_t *o = out + CB * ctr;
+      if constexpr (PACKED) {
 #pragma unroll
-      for (int k = 0; k < EA_CAND / 4; k++)
-        if (4 * k < EA_LAST || whole) o[k] = EaQuad{{tv[4 * k], tv[4 * k + 1], tv[4 * k + 2], tv[4 * k + 3]}};
+        for (int k = 0; k < RATE128 / 16; k++)
+          if (16 * k < 3 * EA_LAST || whole)
+            ((EaQuad<1> *)o)[k] = EaQuad<1>{{s[4 * k], s[4 * k + 1], s[4 * k + 2], s[4 * k + 3]}};
+        if (whole) *(EaPair<1> *)(o + RATE128 / 16 * 16) = EaPair<1>{{s[RATE128 / 4 - 2], s[RATE128 / 4 - 1]}};
+      } else {
+#pragma unroll
+        for (int k = 0; k < EA_CAND / 4; k++)
+          if (4 * k < EA_LAST || whole)
+            ((EaQuad<4> *)o)[k] = EaQuad<4>{{tv[4 * k], tv[4 * k + 1], tv[4 * k + 2], tv[4 * k + 3]}};
+      }
       ctr += whole ? EA_CAND : EA_LAST;
     }
     // blocks with a rejection (or, at the end, after one)
@@ -192,7 +211,16 @@ __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], int32_t *o
         const uint64_t m = __ballot(ok);
         const int pos =
             cL + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (ok && pos < N) out0[(size_t)L * N + pos] = (int32_t)v;
+        if (ok && pos < N) {
+          uint8_t *o = out0 + (size_t)L * POLY + CB * pos;
+          if constexpr (PACKED) {
+            o[0] = (uint8_t)v;
+            o[1] = (uint8_t)(v >> 8);
+            o[2] = (uint8_t)(v >> 16);
+          } else {
+            *(uint32_t *)o = v;
+          }
+        }
         if (lane == L) ctr = min(N, cL + (int)__popcll(m));
       }
       wave_sync();
@@ -205,7 +233,7 @@ __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], int32_t *o
 // ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk)
 template <int LV>
 __global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
-                                                  int32_t *A, uint32_t count) {
+                                                  uint8_t *A, uint32_t count) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   uint64_t st = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   __shared__ uint32_t rows[EA_WG / 64][EA_ROWS * EA_ROW];
@@ -219,7 +247,7 @@ __global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size
   uint32_t s[50];
   absorb_seed34(s, [&](int pos) { return rho[pos >> 3]; }, (uint32_t)j | ((uint32_t)i << 8));
   const int lane = threadIdx.x & 63;
-  expand_a_squeeze_wave(s, A + (size_t)(st - lane) * N, rows[threadIdx.x >> 6], lane, valid);
+  expand_a_squeeze_wave<true>(s, A + (size_t)(st - lane) * A_POLY, rows[threadIdx.x >> 6], lane, valid);
 }
 
 // ExpandS: one lane per (task, r < L + K); centred coefficients to ws.s12
@@ -284,13 +312,13 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
   }
   wave_sync();
   for (int i = g; i < K; i += 4) {
-    const int32_t *Ai = ws.A + ((size_t)task * K + i) * L * N;
+    const uint8_t *Ai = ws.A + ((size_t)task * K + i) * L * A_POLY;
     int64_t acc[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[r] = 0;
     for (int j = 0; j < L; j++) {
       int32_t a[16];
-      load_slots(a, Ai + j * N, t);
+      load_a(a, Ai + j * A_POLY, t);
 #pragma unroll
       for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * lds.hat[hat_idx(j, t, r)];
     }
@@ -462,17 +490,17 @@ __device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t ka
 // before the NTT of y, and each next one before the current one is multiplied.
 // The fences of the NTT's LDS transposes keep the compiler from hoisting these
 // loads by itself, which leaves each load's latency exposed; requesting them
-// early costs 16 registers per lane, which only the l = 4 loop kernels have.
+// early costs 12 registers per lane, which only the l = 4 loop kernels have.
 template <int LV, bool PAD = true, bool EARLY = false, class TW>
-__device__ __forceinline__ void dev_compute_w(const uint8_t *y, const int32_t *A, int32_t *w_out, uint8_t *w1_out,
+__device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A, int32_t *w_out, uint8_t *w1_out,
                                               int32_t *hat, int32_t *tr, uint32_t *w1buf, const TW &ftw,
                                               const TW &itw, int lane) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   int g = lane >> 4, t = lane & 15;
-  int32_t an[16];
+  APart an;
   if constexpr (EARLY) {
-    if (g < K) load_slots(an, A + (size_t)g * L * N, t);
+    if (g < K) an.load(A + (size_t)g * L * A_POLY, t);
   }
   for (int j = g; j < L; j += 4) {
     int32_t x[16];
@@ -483,24 +511,23 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const int32_t *A
   }
   wave_sync();
   for (int i = g; i < K; i += 4) {
-    const int32_t *Ai = A + (size_t)i * L * N;
+    const uint8_t *Ai = A + (size_t)i * L * A_POLY;
     int64_t acc[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[r] = 0;
     if constexpr (EARLY) {
       for (int j = 0; j < L; j++) {
         int32_t a[16];
-#pragma unroll
-        for (int r = 0; r < 16; r++) a[r] = an[r];
-        if (j + 1 < L) load_slots(an, Ai + (j + 1) * N, t);
-        else if (i + 4 < K) load_slots(an, A + (size_t)(i + 4) * L * N, t);
+        an.get(a);
+        if (j + 1 < L) an.load(Ai + (j + 1) * A_POLY, t);
+        else if (i + 4 < K) an.load(A + (size_t)(i + 4) * L * A_POLY, t);
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * hat[hat_idx(j, t, r)];
       }
     } else {
       for (int j = 0; j < L; j++) {
         int32_t a[16];
-        load_slots(a, Ai + j * N, t);
+        load_a(a, Ai + j * A_POLY, t);
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * hat[hat_idx(j, t, r)];
       }
@@ -732,7 +759,7 @@ __global__ void __launch_bounds__(64) sg_w_k(Ws ws, const uint32_t *active, uint
   uint32_t task = active[blockIdx.x];
   int lane = threadIdx.x, t = lane & 15;
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
-  dev_compute_w<LV>(ws.y + (size_t)task * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * N, ws.w + (size_t)task * K * N,
+  dev_compute_w<LV>(ws.y + (size_t)task * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * A_POLY, ws.w + (size_t)task * K * N,
                     ws.muw1 + (size_t)task * muw1_stride<LV>() + 64, lds.hat, lds.tr + (lane >> 4) * NTT_LDS_GROUP,
                     lds.buf, ftw, itw, lane);
   (void)PP::K;
@@ -914,22 +941,20 @@ __global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uin
   int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
   int32_t *tr = trl + g * NTT_LDS_GROUP;
   const size_t key = key_idx ? key_idx[task] : task;
+  const uint32_t cw = ((const uint32_t *)(ws.cpoly + (size_t)task * N))[lane];
+  const uint8_t *A = ws.A + kix(ws, task) * K * L * A_POLY;
   g2l_bytes<PP::SIG>(sig + (size_t)task * PP::SIG, sigw, lane);
   if (lane < 2) sigw[PP::SIG / 4 + 1 + lane] = 0;
-  const uint32_t cw = ((const uint32_t *)(ws.cpoly + (size_t)task * N))[lane];
   wave_sync();
   bool bad = dev_decode_hints<LV>((const uint8_t *)sigw + PP::OFF_H, hm, lane);
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
   for (int j = g; j < L; j += 4) {
-    uint32_t v[16];
-    unpack_strided<PP::ZBITS>(sigw + (PP::OFF_Z + j * PP::ZB) / 4, v, t);
     int32_t x[16];
+    load_mask<PP::ZBITS, G1>(x, (const uint8_t *)sigw + PP::OFF_Z + j * PP::ZB, t);
+    uint32_t zm = 0;  // |z| < gamma1 - beta, as an offset maximum
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-      int32_t z = G1 - (int32_t)v[r];
-      bad |= (z >= G1 - BETA) || (z <= -(G1 - BETA));
-      x[r] = z;
-    }
+    for (int r = 0; r < 16; r++) zm = max(zm, (uint32_t)(x[r] + (G1 - BETA - 1)));
+    bad |= zm > 2u * (G1 - BETA - 1);
     ntt16(x, ftw, tr, t);
 #pragma unroll
     for (int r = 0; r < 16; r++) zh[hat_idx(j, t, r)] = x[r];
@@ -961,13 +986,12 @@ __global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uin
   for (int q = 0; q < (K + 3) / 4; q++) {
     const int i = g + 4 * q;
     if (i >= K) break;
-    const int32_t *Ai = ws.A + (kix(ws, task) * K + i) * L * N;
     int64_t acc[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[r] = 0;
     for (int j = 0; j < L; j++) {
       int32_t a[16];
-      load_slots(a, Ai + j * N, t);
+      load_a(a, A + ((size_t)i * L + j) * A_POLY, t);
 #pragma unroll
       for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * zh[hat_idx(j, t, r)];
     }
@@ -983,7 +1007,7 @@ __global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uin
     for (int r = 0; r < 16; r++) {
       int c = t + 16 * r;
       int32_t h = (hw[c >> 5] >> (c & 31)) & 1;
-      w1[r] = use_hint<LV>(h, sub_ct1(canon(x[r]), lo[q][r]));
+      w1[r] = use_hint<LV>(h, sub_ct1(x[r], lo[q][r]));
     }
     uint32_t vv[16];
     to_consecutive(w1, vv, tr, t);
@@ -1065,7 +1089,7 @@ __global__ void __launch_bounds__(EA_WG) expand_a_seed_k(const uint8_t *seeds, i
   uint32_t nonce = (uint32_t)sd[32] | ((uint32_t)sd[33] << 8);
   absorb_seed34(s, [&](int pos) { return load_le_bytes(sd + pos, 8); }, nonce);
   const int lane = threadIdx.x & 63;
-  expand_a_squeeze_wave(s, out + (p - lane) * N, rows[threadIdx.x >> 6], lane, valid);
+  expand_a_squeeze_wave<false>(s, (uint8_t *)(out + (p - lane) * N), rows[threadIdx.x >> 6], lane, valid);
 }
 
 }  // namespace dil

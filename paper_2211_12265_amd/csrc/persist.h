@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(64, 2) sg_persist_k(Ws ws, PScr sc, uint8_t *s
     // ---- w = INTT(A NTT(y)) per slot ----
     for (int s = 0; s < ns; s++) {
       uint32_t task = lds.h_task[lds.s_h[s]];
-      dev_compute_w<LV>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
+      dev_compute_w<LV>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * A_POLY, wb + si.w(0, s, 0),
                         w1b + si.w1(0, s), lds.u.wp.hat, lds.u.wp.tr + (lane >> 4) * NTT_LDS_GROUP,
                         lds.u.wp.w1buf, ftw, itw, lane);
       wave_sync();
@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
     // w per slot
     for (int s = s_lo; s < s_hi; s += s_step) {
       uint32_t task = lds.h_task[lds.s_h[s]];
-      dev_compute_w<LV, PAD, CONTIG>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * N, wb + si.w(0, s, 0),
+      dev_compute_w<LV, PAD, CONTIG>(yb + ybytes<LV>(si.y(0, s, 0)), ws.A + kix(ws, task) * K * L * A_POLY, wb + si.w(0, s, 0),
                         w1b + si.w1(0, s), lds.u[wave].wp.hat,
                         lds.u[wave].wp.tr + (lane >> 4) * NTT_LDS_GROUP, lds.u[wave].wp.w1buf, ftw, itw, lane);
       wave_sync();

@@ -14,8 +14,11 @@ template <int LV>
 __device__ __forceinline__ void decompose(int32_t r, int32_t &r1, int32_t &r0) {
   constexpr uint32_t G2 = Lv<LV>::GAMMA2, ALPHA = 2 * G2, M = (Q - 1) / ALPHA;
   uint32_t a1 = ((uint32_t)r + G2 - 1) / ALPHA;
-  int32_t a0 = r - (int32_t)(a1 * ALPHA);
-  if (a1 == M) {
+  int32_t a0 = r - __mul24((int)a1, (int)ALPHA);
+  if constexpr ((M & (M - 1)) == 0) {  // 16: the special case is the carry out of the low bits
+    a0 -= (int32_t)(a1 / M);
+    a1 &= M - 1;
+  } else if (a1 == M) {
     a1 = 0;
     a0 -= 1;
   }
@@ -28,6 +31,36 @@ __device__ __forceinline__ int32_t highbits(int32_t r) {
   decompose<LV>(r, r1, r0);
   return r1;
 }
+// A-hat as ExpandA squeezes it: 24 bits per coefficient, of which bit 23 is not
+// part of the value.  768 instead of 1024 bytes per polynomial; the kernels that
+// read A-hat once per task wait for these bytes (10,000 tasks of level 5: 430
+// against 573 MB), and 24 more instructions per 16 coefficients unpack them.
+constexpr int A_POLY = 3 * N;
+// the lane's 16 consecutive coefficients (slots 16 t .. 16 t + 15): 48 bytes
+struct APart {
+  uint4 v[3];
+  __device__ __forceinline__ void load(const uint8_t *poly, int t) {
+    const uint4 *p = (const uint4 *)(poly + 48 * t);
+#pragma unroll
+    for (int q = 0; q < 3; q++) v[q] = p[q];
+  }
+  __device__ __forceinline__ void get(int32_t a[16]) const {
+    const uint32_t w[12] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w, v[2].x, v[2].y, v[2].z, v[2].w};
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      a[4 * k] = (int32_t)(w[3 * k] & 0x7FFFFFu);
+      a[4 * k + 1] = (int32_t)(__builtin_amdgcn_alignbit(w[3 * k + 1], w[3 * k], 24) & 0x7FFFFFu);
+      a[4 * k + 2] = (int32_t)(__builtin_amdgcn_alignbit(w[3 * k + 2], w[3 * k + 1], 16) & 0x7FFFFFu);
+      a[4 * k + 3] = (int32_t)((w[3 * k + 2] >> 8) & 0x7FFFFFu);
+    }
+  }
+};
+__device__ __forceinline__ void load_a(int32_t a[16], const uint8_t *poly, int t) {
+  APart p;
+  p.load(poly, t);
+  p.get(a);
+}
+
 // One word per coefficient of w for the checks of Alg. 2: 2 LowBits(w) + [HighBits(w) != 0].
 // They need no more than that.  r ~ HighBits 2 gamma2 + LowBits (mod q), and for
 // |x| < gamma2 the pair (HighBits(r), x) is the decomposition of HighBits(r) 2 gamma2 + x.

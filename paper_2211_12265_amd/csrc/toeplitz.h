@@ -109,23 +109,22 @@ __device__ __forceinline__ void toep_load_t1(v4i s[4], const uint32_t *t1, int l
     for (int q = 0; q < 5; q++) w[q] = src[20 * J + q];
 #pragma unroll
     for (int d = 0; d < 4; d++) {
-      uint32_t v = 0;
-#pragma unroll
-      for (int b = 0; b < 4; b++) {
-        const int c = 10 * (4 * d + b), i = c >> 5;  // bit of the coefficient in the five words
-        const uint32_t f = __builtin_amdgcn_alignbit(w[i + 1 < 5 ? i + 1 : 4], w[i], c & 31) >> sh;
-        v |= (f & 31u) << (8 * b);
-      }
+      // four fields of 10 bits from bit 40 d = 32 d + 8 d on: three in x, the last in y
+      // 14 / 6 / 14 / 22 bits up; each gives the five bits that start at its bit sh
+      const uint32_t x = __builtin_amdgcn_alignbit(w[d + 1], w[d], 8 * d + sh);
+      const uint32_t y = (d == 0 ? __builtin_amdgcn_alignbit(w[1], w[0], 16) : w[d + 1]) >> sh;
+      const int up = d == 1 ? 6 : d == 3 ? 22 : 14;
+      const uint32_t v = (x & 0x1Fu) | ((x >> 2) & 0x1F00u) | ((x >> 4) & 0x1F0000u) | ((y << (24 - up)) & 0x1F000000u);
       s[J][d] = p < K ? (int)v : 0;
     }
   }
 }
-// x - 2^13 c t1 mod q in [0, q) of one coefficient (x in [0, q)):
-// |c t1| <= tau 1023 < 2^16, so the product fits 30 bits, and z - (z + 2^22 >> 23) q lies in (-q, q)
+// x - 2^13 c t1 mod q in [0, q) of one coefficient (|x| < q): |c t1| <= tau 1023 <
+// 2^16, so the difference fits 31 bits, and z - (z + 2^22 >> 23) q lies in (-q, q)
 // for |z| < 2^31 - 2^22 (2^23 = q + 2^13 - 1).
 __device__ __forceinline__ int32_t sub_ct1(int32_t x, int32_t ct1) {
-  int32_t z = x - ct1 * (1 << D);
-  z -= ((z + (1 << 22)) >> 23) * Q;
+  int32_t z = x - __mul24(ct1, 1 << D);
+  z -= __mul24((z + (1 << 22)) >> 23, Q);
   return canon(z);
 }
 
