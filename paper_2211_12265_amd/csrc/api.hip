@@ -372,17 +372,39 @@ int join_side(dil_ctx *ctx, hipStream_t st, int n = 2) {
 
 inline unsigned blocks_for(uint64_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
 
-// Verify's last kernel: a row or a lane pair per task
+// f with the Keccak engine for `count` states that have one wavefront each or a
+// row each (WAVE_STATES, ROW_STATES); false when there are more of them
+template <class F>
+bool with_coop(uint32_t count, uint32_t max_rows, F f) {
+  if (count <= WAVE_STATES) f((WaveKeccak *)nullptr, count);
+  else if (count <= max_rows) f((RowKeccak *)nullptr, blocks_for(count, RowKeccak::STATES));
+  else return false;
+  return true;
+}
+#define DIL_ENGINE(e) std::remove_pointer_t<decltype(e)>
+
+// Verify's challenges and last kernel: a state each, or a lane / a lane pair per task
+template <int LV>
+void launch_vf_prep(hipStream_t st, const uint8_t *sig, const Ws &ws, uint32_t count) {
+  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+        vf_prep_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(sig, ws, count);
+      }))
+    vf_prep_k<LV><<<blocks_for(count, 64), 64, 0, st>>>(sig, ws, count);
+}
 template <int LV>
 void launch_vf_final(hipStream_t st, const uint8_t *sig, const Ws &ws, int32_t *verdict, uint32_t count) {
-  if (count <= ROW_STATES) vf_final_row_k<LV><<<blocks_for(count, 4), 64, 0, st>>>(sig, ws, verdict, count);
-  else vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, st>>>(sig, ws, verdict, count);
+  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+        vf_final_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(sig, ws, verdict, count);
+      }))
+    vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, st>>>(sig, ws, verdict, count);
 }
-// tr = H(pk) of every row: a row or a lane pair per key
+// tr = H(pk) of every row: a state or a lane pair per key
 template <int LV>
 void launch_tr(hipStream_t st, const uint8_t *pk, uint8_t *out, size_t stride, uint32_t count) {
-  if (count <= ROW_STATES) tr_row_k<LV><<<blocks_for(count, 4), 64, 0, st>>>(pk, out, stride, count);
-  else tr_pair_k<LV><<<blocks_for(2 * (uint64_t)count, 64), 64, 0, st>>>(pk, out, stride, count);
+  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+        tr_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(pk, out, stride, count);
+      }))
+    tr_pair_k<LV><<<blocks_for(2 * (uint64_t)count, 64), 64, 0, st>>>(pk, out, stride, count);
 }
 
 template <int LV>
@@ -424,9 +446,9 @@ void check_keys(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, uin
 template <int LV, bool INTERNAL>
 void launch_prep_form(const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg,
                       const uint64_t *msg_off, const uint8_t *rnd, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
-  if (count <= ROW_STATES)
-    sg_prep_row_k<LV, INTERNAL><<<blocks_for(count, 4), 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
-  else
+  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+        sg_prep_coop_k<LV, INTERNAL, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
+      }))
     sg_prep_k<LV, INTERNAL><<<blocks_for(count, 32), 64, 0, st>>>(sk, key_idx, msg, msg_off, rnd, ws, count, err);
 }
 template <int LV>
@@ -490,9 +512,17 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     if (++rounds > 4096) return fail(ctx, DIL_EHIP, "sign loop did not terminate");
     evaluated += nactive;
     HIPCHK(ctx, hipMemsetAsync(ws.counters, 0, 4, st));
-    expand_mask_k<LV><<<blocks_for((uint64_t)nactive * L, 256), 256, 0, st>>>(ws, cur, nactive);
+    // a round ends on the host: few tasks make it as long as its chains of permutations
+    const uint32_t streams = std::min<uint64_t>((uint64_t)nactive * L, UINT32_MAX);
+    if (!with_coop(streams, ROW_STATES, [&](auto *e, uint32_t wgs) {
+          expand_mask_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(ws, cur, streams);
+        }))
+      expand_mask_k<LV><<<blocks_for((uint64_t)nactive * L, 256), 256, 0, st>>>(ws, cur, nactive);
     sg_w_k<LV><<<nactive, 64, 0, st>>>(ws, cur, nactive);
-    sg_chal_k<LV><<<blocks_for(nactive, 64), 64, 0, st>>>(ws, cur, nactive);
+    if (!with_coop(nactive, ROW_CHALLENGES, [&](auto *e, uint32_t wgs) {
+          sg_chal_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(ws, cur, nactive);
+        }))
+      sg_chal_k<LV><<<blocks_for(nactive, 64), 64, 0, st>>>(ws, cur, nactive);
     sg_check_k<LV><<<nactive, 64, 0, st>>>(ws, sig, cur, nactive, nxt);
     LAUNCHCHK(ctx);
     HIPCHK(ctx, hipMemcpyAsync(ctx->host_counters, ws.counters, 4, hipMemcpyDeviceToHost, st));
@@ -740,9 +770,9 @@ int sign_persistent(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, co
 template <int LV, bool INTERNAL>
 void launch_vf_hash_form(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
                          const uint64_t *msg_off, const Ws &ws, uint32_t count, uint32_t *err, hipStream_t st) {
-  if (count <= ROW_STATES)
-    vf_hash_row_k<LV, INTERNAL><<<blocks_for(count, 4), 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
-  else
+  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+        vf_hash_coop_k<LV, INTERNAL, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
+      }))
     vf_hash_k<LV, INTERNAL><<<blocks_for(count, 32), 64, 0, st>>>(pk, key_idx, msg, msg_off, ws, count, err);
 }
 template <int LV>
@@ -790,7 +820,7 @@ int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const 
     if (!ks)
       expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, s_ea>>>(pk, P<LV>::PK, key_idx, ws.A,
                                                                                 count);
-    vf_prep_k<LV><<<blocks_for(count, 64), 64, 0, s>>>(sig, ws, count);
+    launch_vf_prep<LV>(s, sig, ws, count);
     if (conc) {
       int r2 = join_one(ctx, s, 0);
       if (r2) return r2;
@@ -1175,7 +1205,7 @@ int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_
   zero_words_k<<<1, 64, 0, st>>>(ws.counters, 16, nullptr, 0);
   check_keys(ctx, ks, key_idx, kid, count, st);
   launch_vf_hash<LV>(ctx, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG, st);
-  vf_prep_k<LV><<<blocks_for(count, 64), 64, 0, st>>>(sig, ws, count);
+  launch_vf_prep<LV>(st, sig, ws, count);
   vf_main_k<LV><<<count, 64, 0, st>>>(ks->pk, kidx, sig, ws, count);
   launch_vf_final<LV>(st, sig, ws, verdict, count);
   LAUNCHCHK(ctx);

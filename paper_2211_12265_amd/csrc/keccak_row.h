@@ -17,35 +17,30 @@
 // sheet once and are the ones whose words are kept; the read-back makes all 16
 // valid again.  34 VALU and 15 LDS instructions per round against 120 VALU on a
 // lane pair (keccak_pair.h): 3.4 times the issue slots per state, half the time
-// per permutation of a lone wavefront (3.5 against 6.8 us): the mu chains of 613
-// messages of up to 6 KB 493 -> 213 us, of 2,503 messages of up to 4 KB 328 -> 176.
+// per permutation of a lone wavefront (3.8 against 6.8 us): the mu chains of 2,503
+// messages of up to 4 KB 328 -> 176 us.
+//
+// The functions after the two engines run on either (E: RowKeccak or
+// WaveKeccak, keccak_wave.h).
 #pragma once
+#include "keccak_wave.h"
 #include "kernels.h"
 
 namespace dil {
 
-constexpr int ROW_LDS = 256;  // words of LDS per wavefront: four states of 50 words and a dump for unkept words
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t row_dpp(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
-
-// rotation amounts of the words that land in register y of sheets 0 .. 4, six bits each
-constexpr uint32_t row_rot(int y) {
-  uint32_t v = 0;
-  for (int x = 0; x < 5; x++) v |= (uint32_t)kc_rho((3 * y + x) % 5 + 5 * x) << (6 * x);
-  return v;
-}
 template <int Y>
 struct RowRot {
   static constexpr uint32_t v = row_rot(Y);
 };
 
-// the lane's constants; L: the wavefront's ROW_LDS words
+// the lane's constants; L: the wavefront's KECCAK_LDS words (four states of 50
+// words and a dump for unkept words)
 struct RowKeccak {
+  static constexpr int NR = 5, NA = 4, ND = 2;  // registers; those with words of the rate; with words 0 .. 9
+  static constexpr int LANES = 16, STATES = 4;
   uint32_t *L;
-  int x, h;
+  int x, h, l;
+  bool own;             // holds words of its own (lanes 10 .. 15 are copies)
   int st;               // the state's words in L
   int wr;               // where the lane keeps word (x, 0); (x, y) is 10 y further
   int p[5], q[5];       // high and low operand of the rotation that yields word (x, y)
@@ -53,7 +48,9 @@ struct RowKeccak {
   uint32_t mlo, mhi;    // lanes that take the round constant's halves
   __device__ __forceinline__ RowKeccak(uint32_t *lds, int lane) {
     L = lds;
-    const int l = lane & 15, m = l < 10 ? l : l - 10;
+    l = lane & 15;
+    const int m = l < 10 ? l : l - 10;
+    own = l < 10;
     x = m >> 1;
     h = m & 1;
     st = 50 * ((lane >> 4) & 3);
@@ -80,17 +77,16 @@ struct RowKeccak {
   // 8-byte word index of register y, and the 32-bit word of it that this lane holds
   __device__ __forceinline__ int word(int y) const { return 5 * y + x; }
   __device__ __forceinline__ int half_word(int y) const { return 2 * word(y) + h; }
+  // whether `v` holds on a lane of the state
+  __device__ __forceinline__ bool any(bool v) const { return (__ballot(v) >> (st / 50 * 16) & 0xFFFFu) != 0; }
 };
 
-__device__ __forceinline__ void keccak_f_row(uint32_t a[5], const RowKeccak &k) {
+__device__ __forceinline__ void keccak_f_coop(uint32_t a[5], const RowKeccak &k) {
 #pragma unroll 1
   for (int ir = 0; ir < 24; ir++) {
     const uint32_t c = xor3(xor3(a[0], a[1], a[2]), a[3], a[4]);
-    const uint32_t cm = row_dpp<0x112>(c);  // lane l - 2
-    // lane l + 2; lanes 8 .. 11 from lane l - 8
-    const uint32_t cp =
-        (uint32_t)__builtin_amdgcn_update_dpp((int)row_dpp<0x102>(c), (int)c, 0x118, 0xF, 0x4, false);
-    const uint32_t r = __builtin_amdgcn_alignbit(cp, pair_swap(cp), 31);
+    uint32_t cm;
+    const uint32_t r = row_theta(c, cm);
 #pragma unroll
     for (int y = 0; y < 5; y++) k.L[k.wr + 10 * y] = xor3(a[y], cm, r);
     wave_sync();
@@ -107,13 +103,13 @@ __device__ __forceinline__ void keccak_f_row(uint32_t a[5], const RowKeccak &k) 
 // SHAKE256 absorption of a LEN-byte string (LEN a multiple of 8) given by its
 // 32-bit words: word(i) is called for 4 i < LEN only.  The next block's words
 // are requested before the current one is permuted.
-template <int LEN, class W>
-__device__ __forceinline__ void shake256_absorb_row(uint32_t a[5], const RowKeccak &k, W word) {
+template <int LEN, class E, class W>
+__device__ __forceinline__ void shake256_absorb_coop(uint32_t a[E::NR], const E &k, W word) {
   static_assert(LEN % 8 == 0, "whole 8-byte words");
   constexpr int RATE = 136, NBLK = LEN / RATE + 1;
-  auto fetch = [&](uint32_t v[4], int blk) {
+  auto fetch = [&](uint32_t v[E::NA], int blk) {
 #pragma unroll
-    for (int y = 0; y < 4; y++) {
+    for (int y = 0; y < E::NA; y++) {
       const int w = k.word(y), pos = blk * RATE + 8 * w;
       v[y] = w < RATE / 8 && pos < LEN ? word(blk * (RATE / 4) + k.half_word(y)) : 0u;
       if (w < RATE / 8 && pos == LEN && !k.h) v[y] = 0x1Fu;                     // suffix 1111 + first pad bit
@@ -121,56 +117,55 @@ __device__ __forceinline__ void shake256_absorb_row(uint32_t a[5], const RowKecc
     }
   };
 #pragma unroll
-  for (int y = 0; y < 5; y++) a[y] = 0;
-  uint32_t v[4];
+  for (int y = 0; y < E::NR; y++) a[y] = 0;
+  uint32_t v[E::NA];
   fetch(v, 0);
 #pragma unroll 1
   for (int blk = 0; blk < NBLK; blk++) {
 #pragma unroll
-    for (int y = 0; y < 4; y++) a[y] ^= v[y];
+    for (int y = 0; y < E::NA; y++) a[y] ^= v[y];
     if (blk + 1 < NBLK) fetch(v, blk + 1);
-    keccak_f_row(a, k);
+    keccak_f_coop(a, k);
   }
 }
 
 // SHAKE256 absorption of X = prefix || M (msg_words.h): pre[y] is the lane's
 // prefix word of register y where word(y) < PB / 8.
-template <int PB>
-__device__ __forceinline__ void absorb_prefix_msg_row(uint32_t a[5], const RowKeccak &k, const uint32_t pre[2],
+template <int PB, class E>
+__device__ __forceinline__ void absorb_prefix_msg_coop(uint32_t a[E::NR], const E &k, const uint32_t pre[E::ND],
                                                       const uint8_t *msg, uint64_t mlen) {
   using Plan = MwPlan<PB>;
   const Plan pl(msg, mlen);
-  uint32_t lo[4], hi[4];
+  uint32_t lo[E::NA], hi[E::NA];
   auto fetch = [&](uint64_t blk) {
 #pragma unroll
-    for (int y = 0; y < 4; y++) {
+    for (int y = 0; y < E::NA; y++) {
       lo[y] = hi[y] = 0;
       if (k.word(y) < MW_RATE / 8) mw_fetch_one(pl, blk, k.half_word(y), lo[y], hi[y]);
     }
   };
-  uint32_t p0 = pre[0], p1 = pre[1];
+  const uint32_t p0 = pre[0], p1 = pre[E::ND - 1];
 #pragma unroll
-  for (int y = 0; y < 5; y++) a[y] = 0;
+  for (int y = 0; y < E::NR; y++) a[y] = 0;
   fetch(0);
   for (uint64_t blk = 0; blk < pl.nblk; blk++) {
 #pragma unroll
-    for (int y = 0; y < 4; y++)
+    for (int y = 0; y < E::NA; y++)
       if (k.word(y) < MW_RATE / 8)
         a[y] ^= mw_word_one(pl, blk, k.half_word(y), y == 0 ? p0 : p1, lo[y], hi[y]);
     if (blk + 1 < pl.nblk) fetch(blk + 1);
-    keccak_f_row(a, k);
+    keccak_f_coop(a, k);
   }
 }
 
 // SampleInBall on a row whose state holds the first SHAKE256 block of ctilde;
-// c: 256 bytes, bw: 34 words, both LDS, 4-byte aligned
+// c: 256 bytes, bw: 34 words (the wavefront form needs none), both LDS, 4-byte aligned
 template <int TAU>
-__device__ __forceinline__ void sample_in_ball_row(uint32_t a[5], const RowKeccak &k, int lane, int8_t *c,
-                                                   uint32_t *bw) {
+__device__ __forceinline__ void sample_in_ball_coop(uint32_t a[5], const RowKeccak &k, int8_t *c, uint32_t *bw) {
   auto stage = [&]() {
-    if ((lane & 15) < 10) {
+    if (k.own) {
 #pragma unroll
-      for (int y = 0; y < 4; y++)
+      for (int y = 0; y < RowKeccak::NA; y++)
         if (k.word(y) < RATE256 / 8) bw[k.half_word(y)] = a[y];
     }
     wave_sync();
@@ -178,7 +173,7 @@ __device__ __forceinline__ void sample_in_ball_row(uint32_t a[5], const RowKecca
   stage();
   uint32_t *cw = (uint32_t *)c;
 #pragma unroll
-  for (int w = 0; w < N / 64; w++) cw[16 * w + (lane & 15)] = 0;
+  for (int w = 0; w < N / 64; w++) cw[16 * w + k.l] = 0;
   wave_sync();
   const uint8_t *bytes = (const uint8_t *)bw;
   uint64_t signs = (uint64_t)bw[0] | ((uint64_t)bw[1] << 32);
@@ -188,14 +183,14 @@ __device__ __forceinline__ void sample_in_ball_row(uint32_t a[5], const RowKecca
     for (;;) {
       if (pos == RATE256) {
         wave_sync();
-        keccak_f_row(a, k);
+        keccak_f_coop(a, k);
         stage();
         pos = 0;
       }
       b = bytes[pos++];
       if (b <= i) break;
     }
-    if ((lane & 15) == 0) {
+    if (k.l == 0) {
       c[i] = c[b];
       c[b] = (int8_t)(1 - 2 * (int)(signs & 1));
     }
@@ -203,122 +198,149 @@ __device__ __forceinline__ void sample_in_ball_row(uint32_t a[5], const RowKecca
   }
 }
 
-// ctilde = H(mu || w1) and c = SampleInBall(ctilde) on a row (as
-// dev_challenge_pair); ctilde_out: CT / 4 words
-template <int LV>
-__device__ __forceinline__ void dev_challenge_row(const uint8_t *mu, const uint8_t *w1, const RowKeccak &k, int lane,
-                                                  uint32_t *ctilde_out, int8_t *c, uint32_t *bw) {
+// ctilde = H(mu || w1) and c = SampleInBall(ctilde) (as dev_challenge_pair); ctilde_out: CT / 4 words
+template <int LV, class E>
+__device__ __forceinline__ void dev_challenge_coop(const uint8_t *mu, const uint8_t *w1, const E &k,
+                                                   uint32_t *ctilde_out, int8_t *c, uint32_t *bw) {
   constexpr int CW = P<LV>::CT / 8;  // 8-byte words of ctilde
-  uint32_t a[5];
-  shake256_absorb_row<P<LV>::MUW1>(a, k, [&](int i) {
+  uint32_t a[E::NR];
+  shake256_absorb_coop<P<LV>::MUW1>(a, k, [&](int i) {
     return i < 16 ? ((const uint32_t *)mu)[i] : ((const uint32_t *)w1)[i - 16];
   });
 #pragma unroll
-  for (int y = 0; y < 5; y++) {
+  for (int y = 0; y < E::NR; y++) {
     const int w = k.word(y);
     if (w < CW) {
-      if ((lane & 15) < 10) ctilde_out[k.half_word(y)] = a[y];
+      if (k.own) ctilde_out[k.half_word(y)] = a[y];
     } else {
       a[y] = w == CW && !k.h ? 0x1Fu : 0u;
     }
     if (w == RATE256 / 8 - 1 && k.h) a[y] ^= 0x80u << 24;
   }
-  keccak_f_row(a, k);
-  sample_in_ball_row<Lv<LV>::TAU>(a, k, lane, c, bw);
+  keccak_f_coop(a, k);
+  sample_in_ball_coop<Lv<LV>::TAU>(a, k, c, bw);
 }
 
-// as dev_prep_pair (kernels.h) on a row; L: the wavefront's ROW_LDS words
-template <int LV, bool INTERNAL>
-__device__ __forceinline__ void dev_prep_row(uint32_t t, uint32_t *L, int lane, const uint8_t *sk,
-                                             const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
+// as dev_prep_pair (kernels.h)
+template <int LV, bool INTERNAL, class E>
+__device__ __forceinline__ void dev_prep_coop(uint32_t t, const E &k, const uint8_t *sk, const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
                                              const uint8_t *rnd, const Ws &ws, uint32_t *err) {
-  const int l = lane & 15;
-  const RowKeccak k(L, lane);
   const size_t key = key_idx ? key_idx[t] : t;
   const uint32_t *skw = (const uint32_t *)(sk + key * P<LV>::SK);
   const uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
   uint64_t mlen = 0;
   if (o1 >= o0) mlen = o1 - o0;
-  else if (l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
-  uint32_t pre[2];
+  else if (k.l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
+  uint32_t pre[E::ND];
 #pragma unroll
-  for (int y = 0; y < 2; y++) pre[y] = k.word(y) < P<LV>::TRB / 8 ? skw[16 + k.half_word(y)] : 0u;
-  uint32_t a[5];
-  absorb_prefix_msg_row<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
+  for (int y = 0; y < E::ND; y++) pre[y] = k.word(y) < P<LV>::TRB / 8 ? skw[16 + k.half_word(y)] : 0u;
+  uint32_t a[E::NR];
+  absorb_prefix_msg_coop<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
   uint32_t *muw = (uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
   uint32_t *rp = (uint32_t *)(ws.rhop + (size_t)t * 64);
   // mu also to LDS, from where it is absorbed at another place
 #pragma unroll
-  for (int y = 0; y < 2; y++)
-    if (l < 10 && k.word(y) < 8) {
+  for (int y = 0; y < E::ND; y++)
+    if (k.own && k.word(y) < 8) {
       muw[k.half_word(y)] = a[y];
-      L[k.st + k.half_word(y)] = a[y];
+      k.L[k.st + k.half_word(y)] = a[y];
     }
   wave_sync();
   const bool round3_rnd = !Lv<LV>::MLDSA && rnd;  // rho' is the task's rnd itself
   constexpr int MU0 = Lv<LV>::MLDSA ? 8 : 4;      // word of mu in K || rnd || mu, K || mu
-  uint32_t b[5];
+  uint32_t b[E::NR];
 #pragma unroll
-  for (int y = 0; y < 5; y++) {
+  for (int y = 0; y < E::NR; y++) {
     const int w = k.word(y), i = k.half_word(y);
     b[y] = 0;
     if (w < 4) b[y] = skw[8 + i];
     else if (w < MU0) b[y] = rnd ? ((const uint32_t *)(rnd + (size_t)t * 32))[i - 8] : 0u;
-    else if (w < MU0 + 8) b[y] = L[k.st + i - 2 * MU0];
+    else if (w < MU0 + 8) b[y] = k.L[k.st + i - 2 * MU0];
     if (w == MU0 + 8 && !k.h) b[y] ^= 0x1Fu;
     if (w == RATE256 / 8 - 1 && k.h) b[y] ^= 0x80u << 24;
   }
   wave_sync();
-  if (!round3_rnd) keccak_f_row(b, k);
+  if (!round3_rnd) keccak_f_coop(b, k);
 #pragma unroll
-  for (int y = 0; y < 2; y++)
-    if (l < 10 && k.word(y) < 8)
+  for (int y = 0; y < E::ND; y++)
+    if (k.own && k.word(y) < 8)
       rp[k.half_word(y)] = round3_rnd ? ((const uint32_t *)(rnd + (size_t)t * 64))[k.half_word(y)] : b[y];
-  if (l == 0) {
+  if (k.l == 0) {
     ws.kappa[t] = 0;
     ws.active0[t] = t;
   }
 }
 
-// as dev_hash_pair on a row
-template <int LV, bool INTERNAL>
-__device__ __forceinline__ void dev_hash_row(uint32_t t, uint32_t *L, int lane, const uint8_t *pk,
-                                             const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
-                                             const Ws &ws, uint32_t *err) {
+// as dev_hash_pair
+template <int LV, bool INTERNAL, class E>
+__device__ __forceinline__ void dev_hash_coop(uint32_t t, const E &k, const uint8_t *pk, const uint32_t *key_idx,
+                                              const uint8_t *msg, const uint64_t *msg_off, const Ws &ws,
+                                              uint32_t *err) {
   using PP = P<LV>;
-  const int l = lane & 15;
-  const RowKeccak k(L, lane);
   const size_t key = key_idx ? key_idx[t] : t;
-  uint32_t a[5], pre[2];
+  uint32_t a[E::NR], pre[E::ND];
   if (ws.tr) {
     const uint32_t *tg = (const uint32_t *)(ws.tr + key * PP::TRB);
 #pragma unroll
-    for (int y = 0; y < 2; y++) pre[y] = k.word(y) < PP::TRB / 8 ? tg[k.half_word(y)] : 0u;
+    for (int y = 0; y < E::ND; y++) pre[y] = k.word(y) < PP::TRB / 8 ? tg[k.half_word(y)] : 0u;
   } else {
     const uint32_t *pkr = (const uint32_t *)(pk + key * PP::PK);
-    shake256_absorb_row<PP::PK>(a, k, [&](int i) { return pkr[i]; });
+    shake256_absorb_coop<PP::PK>(a, k, [&](int i) { return pkr[i]; });
     // the lane's words of the digest are its words of the prefix
-    pre[0] = a[0];
-    pre[1] = a[1];
+#pragma unroll
+    for (int y = 0; y < E::ND; y++) pre[y] = a[y];
   }
   const uint64_t o0 = msg_off[t], o1 = msg_off[t + 1];
   uint64_t mlen = 0;
   if (o1 >= o0) mlen = o1 - o0;
-  else if (l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
-  absorb_prefix_msg_row<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
+  else if (k.l == 0) atomicOr(err, 1u);  // decreasing msg_off: message treated as empty
+  absorb_prefix_msg_coop<mu_prefix_bytes<LV, INTERNAL>()>(a, k, pre, msg + o0, mlen);
   uint32_t *muw = (uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
 #pragma unroll
-  for (int y = 0; y < 2; y++)
-    if (l < 10 && k.word(y) < 8) muw[k.half_word(y)] = a[y];
+  for (int y = 0; y < E::ND; y++)
+    if (k.own && k.word(y) < 8) muw[k.half_word(y)] = a[y];
 }
 
-// ---- kernels: one-wavefront workgroups of 32 lane pairs or four rows ----
+// c = SampleInBall(ctilde) of task t
+template <int LV, class E>
+__device__ __forceinline__ void dev_ball_coop(const uint8_t *ctilde, const E &k, int8_t *c, uint32_t *bw) {
+  uint32_t a[E::NR];
+#pragma unroll
+  for (int y = 0; y < E::NR; y++) {
+    const int w = k.word(y);
+    a[y] = w < P<LV>::CT / 8 ? (uint32_t)load_le_bytes(ctilde + 4 * k.half_word(y), 4) : w == P<LV>::CT / 8 && !k.h ? 0x1Fu : 0u;
+    if (w == RATE256 / 8 - 1 && k.h) a[y] ^= 0x80u << 24;
+  }
+  keccak_f_coop(a, k);
+  sample_in_ball_coop<Lv<LV>::TAU>(a, k, c, bw);
+}
+// the dense challenge from LDS to a 16-byte aligned global row
+template <class E>
+__device__ __forceinline__ void store_c_coop(const int8_t *c, int8_t *dst, const E &k) {
+  wave_sync();
+  if constexpr (E::LANES == 64) {
+    ((uint32_t *)dst)[k.l] = ((const uint32_t *)c)[k.l];
+  } else {
+    const uint32_t *cw = (const uint32_t *)c + 4 * k.l;
+    ((int4 *)dst)[k.l] = make_int4(cw[0], cw[1], cw[2], cw[3]);
+  }
+}
+
+// ---- kernels: one-wavefront workgroups of 32 lane pairs, four rows or one state ----
 // mu needs one permutation per 136 message bytes in series, whatever the chip
 // does beside it: up to 31 for 4 KB, and Verify's tr = H(pk) 10 / 15 / 20 before
-// them.  A batch that leaves room gives every task a row.  Larger ones take
-// lane pairs: beside ExpandA rows would cost it more than they gain (level-3
-// Verify, 10,000 tasks of up to 4 KB: 555-697 us with rows for the messages of
-// more than 2 KB against 551).
+// them.  A batch that leaves room gives every task a row or a wavefront.  Larger
+// ones take lane pairs: beside ExpandA rows would cost it more than they gain
+// (level-3 Verify, 10,000 tasks of up to 4 KB: 555-697 us with rows for the
+// messages of more than 2 KB against 551).
+constexpr uint32_t ROW_STATES = 4096;
+#define DIL_COOP_TASK(E)                                           \
+  __shared__ uint32_t L[KECCAK_LDS];                               \
+  __builtin_amdgcn_s_setprio(3);                                   \
+  const uint32_t t = blockIdx.x * E::STATES + threadIdx.x / E::LANES; \
+  if (t >= count) return; /* a whole state */                      \
+  const E k(L, threadIdx.x);
+
 template <int LV, bool INTERNAL>
 __global__ void __launch_bounds__(64) sg_prep_k(const uint8_t *sk, const uint32_t *key_idx,
                                                     const uint8_t *msg, const uint64_t *msg_off, const uint8_t *rnd, Ws ws, uint32_t count, uint32_t *err) {
@@ -326,14 +348,11 @@ __global__ void __launch_bounds__(64) sg_prep_k(const uint8_t *sk, const uint32_
   const uint32_t t = blockIdx.x * 32 + (threadIdx.x >> 1);
   if (t < count) dev_prep_pair<LV, INTERNAL>(t, threadIdx.x & 1, sk, key_idx, msg, msg_off, rnd, ws, err);
 }
-template <int LV, bool INTERNAL>
-__global__ void __launch_bounds__(64) sg_prep_row_k(const uint8_t *sk, const uint32_t *key_idx,
+template <int LV, bool INTERNAL, class E>
+__global__ void __launch_bounds__(64) sg_prep_coop_k(const uint8_t *sk, const uint32_t *key_idx,
                                                     const uint8_t *msg, const uint64_t *msg_off, const uint8_t *rnd, Ws ws, uint32_t count, uint32_t *err) {
-  __shared__ uint32_t L[ROW_LDS];
-  __builtin_amdgcn_s_setprio(3);
-  const int lane = threadIdx.x;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t < count) dev_prep_row<LV, INTERNAL>(t, L, lane, sk, key_idx, msg, msg_off, rnd, ws, err);
+  DIL_COOP_TASK(E)
+  dev_prep_coop<LV, INTERNAL>(t, k, sk, key_idx, msg, msg_off, rnd, ws, err);
 }
 template <int LV, bool INTERNAL>
 __global__ void __launch_bounds__(64) vf_hash_k(const uint8_t *pk, const uint32_t *key_idx,
@@ -342,51 +361,63 @@ __global__ void __launch_bounds__(64) vf_hash_k(const uint8_t *pk, const uint32_
   const uint32_t t = blockIdx.x * 32 + (threadIdx.x >> 1);
   if (t < count) dev_hash_pair<LV, INTERNAL>(t, threadIdx.x & 1, pk, key_idx, msg, msg_off, ws, err);
 }
-template <int LV, bool INTERNAL>
-__global__ void __launch_bounds__(64) vf_hash_row_k(const uint8_t *pk, const uint32_t *key_idx,
+template <int LV, bool INTERNAL, class E>
+__global__ void __launch_bounds__(64) vf_hash_coop_k(const uint8_t *pk, const uint32_t *key_idx,
                                                     const uint8_t *msg, const uint64_t *msg_off, Ws ws, uint32_t count, uint32_t *err) {
-  __shared__ uint32_t L[ROW_LDS];
-  __builtin_amdgcn_s_setprio(3);
-  const int lane = threadIdx.x;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t < count) dev_hash_row<LV, INTERNAL>(t, L, lane, pk, key_idx, msg, msg_off, ws, err);
+  DIL_COOP_TASK(E)
+  dev_hash_coop<LV, INTERNAL>(t, k, pk, key_idx, msg, msg_off, ws, err);
 }
 
-// as vf_final_k, one row per task
-template <int LV>
-__global__ void __launch_bounds__(64) vf_final_row_k(const uint8_t *sig, Ws ws, int32_t *verdict, uint32_t count) {
-  __shared__ uint32_t L[ROW_LDS];
-  const int lane = threadIdx.x, l = lane & 15;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t >= count) return;  // a whole row
-  const RowKeccak k(L, lane);
+// as vf_prep_k
+template <int LV, class E>
+__global__ void __launch_bounds__(64) vf_prep_coop_k(const uint8_t *sig, Ws ws, uint32_t count) {
+  __shared__ __align__(16) int8_t cl[E::STATES][C_ROW];
+  __shared__ uint32_t bb[E::STATES][RATE256 / 4];
+  DIL_COOP_TASK(E)
+  const int p = threadIdx.x / E::LANES;
+  dev_ball_coop<LV>(sig + (size_t)t * P<LV>::SIG, k, cl[p], bb[p]);
+  store_c_coop(cl[p], ws.cpoly + (size_t)t * N, k);
+}
+// as vf_final_k
+template <int LV, class E>
+__global__ void __launch_bounds__(64) vf_final_coop_k(const uint8_t *sig, Ws ws, int32_t *verdict, uint32_t count) {
+  DIL_COOP_TASK(E)
   const uint32_t *row = (const uint32_t *)(ws.muw1 + (size_t)t * muw1_stride<LV>());
-  uint32_t a[5];
-  shake256_absorb_row<P<LV>::MUW1>(a, k, [&](int i) { return row[i]; });
+  uint32_t a[E::NR];
+  shake256_absorb_coop<P<LV>::MUW1>(a, k, [&](int i) { return row[i]; });
   const uint8_t *sg = sig + (size_t)t * P<LV>::SIG;
   bool diff = false;
 #pragma unroll
-  for (int y = 0; y < 2; y++)
-    if (l < 10 && k.word(y) < P<LV>::CT / 8) diff |= (uint32_t)load_le_bytes(sg + 4 * k.half_word(y), 4) != a[y];
-  const uint64_t m = __ballot(diff) >> (lane & 48) & 0xFFFFu;
-  if (l == 0) verdict[t] = (ws.flag[t] && m == 0) ? 1 : 0;
+  for (int y = 0; y < E::ND; y++)
+    if (k.own && k.word(y) < P<LV>::CT / 8) diff |= (uint32_t)load_le_bytes(sg + 4 * k.half_word(y), 4) != a[y];
+  diff = k.any(diff);
+  if (k.l == 0) verdict[t] = (ws.flag[t] && !diff) ? 1 : 0;
 }
 
-// tr = H(pk) (TRB bytes) to out rows, one row per key
-template <int LV>
-__global__ void __launch_bounds__(64) tr_row_k(const uint8_t *pk, uint8_t *out, size_t out_stride, uint32_t count) {
-  __shared__ uint32_t L[ROW_LDS];
-  const int lane = threadIdx.x, l = lane & 15;
-  const uint32_t t = blockIdx.x * 4 + (lane >> 4);
-  if (t >= count) return;  // a whole row
-  const RowKeccak k(L, lane);
+// as sg_chal_k
+template <int LV, class E>
+__global__ void __launch_bounds__(64) sg_chal_coop_k(Ws ws, const uint32_t *active, uint32_t count) {
+  __shared__ __align__(16) int8_t cl[E::STATES][C_ROW];
+  __shared__ uint32_t bb[E::STATES][RATE256 / 4];
+  DIL_COOP_TASK(E)
+  const int p = threadIdx.x / E::LANES;
+  const uint32_t task = active[t];
+  const uint8_t *row = ws.muw1 + (size_t)task * muw1_stride<LV>();
+  dev_challenge_coop<LV>(row, row + 64, k, (uint32_t *)(ws.ctilde + (size_t)task * CT_STRIDE), cl[p], bb[p]);
+  store_c_coop(cl[p], ws.cpoly + (size_t)task * N, k);
+}
+
+// tr = H(pk) (TRB bytes) to out rows, one state per key
+template <int LV, class E>
+__global__ void __launch_bounds__(64) tr_coop_k(const uint8_t *pk, uint8_t *out, size_t out_stride, uint32_t count) {
+  DIL_COOP_TASK(E)
   const uint32_t *p = (const uint32_t *)(pk + (size_t)t * P<LV>::PK);
-  uint32_t a[5];
-  shake256_absorb_row<P<LV>::PK>(a, k, [&](int i) { return p[i]; });
+  uint32_t a[E::NR];
+  shake256_absorb_coop<P<LV>::PK>(a, k, [&](int i) { return p[i]; });
   uint32_t *o = (uint32_t *)(out + (size_t)t * out_stride);
 #pragma unroll
-  for (int y = 0; y < 2; y++)
-    if (l < 10 && k.word(y) < P<LV>::TRB / 8) o[k.half_word(y)] = a[y];
+  for (int y = 0; y < E::ND; y++)
+    if (k.own && k.word(y) < P<LV>::TRB / 8) o[k.half_word(y)] = a[y];
 }
 // the same on a lane pair, for batches that fill the chip
 template <int LV>
@@ -401,5 +432,40 @@ __global__ void __launch_bounds__(64) tr_pair_k(const uint8_t *pk, uint8_t *out,
 #pragma unroll
   for (int w = 0; w < P<LV>::TRB / 8; w++) o[2 * w + half] = a[w];
 }
+
+// the squeezed stream of one mask polynomial
+template <int LV, class E>
+__device__ __forceinline__ void dev_expand_mask_coop(const uint8_t *rhop, uint32_t nonce, const E &k, uint8_t *out) {
+  constexpr int WPB = RATE256 / 4, NWORD = N * P<LV>::ZBITS / 32, NBLK = (NWORD + WPB - 1) / WPB;
+  const uint32_t *rw = (const uint32_t *)rhop;
+  uint32_t *o = (uint32_t *)out;
+  uint32_t a[E::NR];
+#pragma unroll
+  for (int y = 0; y < E::NR; y++) {
+    const int w = k.word(y);
+    a[y] = w < 8 ? rw[k.half_word(y)] : 0u;
+    if (w == 8 && !k.h) a[y] = (nonce & 0xFFFFu) | (0x1Fu << 16);
+    if (w == RATE256 / 8 - 1 && k.h) a[y] = 0x80u << 24;
+  }
+#pragma unroll 1
+  for (int blk = 0; blk < NBLK; blk++) {
+    keccak_f_coop(a, k);
+#pragma unroll
+    for (int y = 0; y < E::NA; y++)
+      if (k.own && k.word(y) < RATE256 / 8 && blk * WPB + k.half_word(y) < NWORD)
+        o[blk * WPB + k.half_word(y)] = a[y];
+  }
+}
+
+// as expand_mask_k
+template <int LV, class E>
+__global__ void __launch_bounds__(64) expand_mask_coop_k(Ws ws, const uint32_t *active, uint32_t count) {
+  constexpr uint32_t ML = Lv<LV>::L;
+  DIL_COOP_TASK(E)
+  const uint32_t task = active[t / ML], i = t % ML;
+  dev_expand_mask_coop<LV>(ws.rhop + (size_t)task * 64, ws.kappa[task] + i, k,
+                           ws.y + ((size_t)task * ML + i) * P<LV>::YB);
+}
+#undef DIL_COOP_TASK
 
 }  // namespace dil

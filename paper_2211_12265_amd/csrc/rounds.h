@@ -53,25 +53,26 @@ __device__ __forceinline__ uint32_t round_task(const Group &gr, int r, uint32_t 
 
 // ExpandMask streams: a round of many has one lane each; as long as the chip
 // would hold at most one wavefront per SIMD, a stream gets a lane pair, and
-// with still fewer a 16-lane row.  A stream is five permutations one after
-// another and a lone wavefront's permutation takes 9.2 us on one lane, 6.8 us
-// on a pair and about half of that on a row, so the stage then lasts 51, 36 or
-// 20 us; beyond these counts the wider forms would queue for the SIMDs.
-constexpr uint32_t ROW_STATES = 4096, PAIR_STATES = 32768, ROW_CHALLENGES = 8192;
+// with still fewer a 16-lane row or a whole wavefront (two per SIMD).  A stream
+// is five permutations one after another and a lone wavefront's permutation
+// takes 9.2 us on one lane, 6.8 us on a pair, 3.8 us on a row and 2.5 us over
+// the wavefront; beyond these counts the wider forms would queue for the SIMDs.
+constexpr uint32_t PAIR_STATES = 32768, ROW_CHALLENGES = 8192;
 inline uint32_t mask_blocks(uint64_t streams, bool exact) {
   // 256-lane workgroups that the form of at most `streams` streams needs (exact: of that many)
   auto need = [](uint64_t n) -> uint64_t {
-    return n <= ROW_STATES ? (n + 15) / 16 : n <= PAIR_STATES ? (n + 127) / 128 : (n + 255) / 256;
+    return n <= WAVE_STATES ? (n + 3) / 4 : n <= ROW_STATES ? (n + 15) / 16 : n <= PAIR_STATES ? (n + 127) / 128 : (n + 255) / 256;
   };
   uint64_t b = need(streams);
   if (!exact) {
+    if (streams > WAVE_STATES) b = b > need(WAVE_STATES) ? b : need(WAVE_STATES);
     if (streams > ROW_STATES) b = b > need(ROW_STATES) ? b : need(ROW_STATES);
     if (streams > PAIR_STATES) b = b > need(PAIR_STATES) ? b : need(PAIR_STATES);
   }
   return (uint32_t)b;
 }
 
-// the squeezed stream of one candidate polynomial on a lane pair / a row
+// the squeezed stream of one candidate polynomial on a lane pair
 template <int LV>
 __device__ __forceinline__ void dev_expand_mask_pair(const uint8_t *rhop, uint32_t nonce, int half, uint8_t *out) {
   constexpr int WPB = RATE256 / 4, NWORD = N * P<LV>::ZBITS / 32, NBLK = (NWORD + WPB - 1) / WPB;
@@ -91,37 +92,13 @@ __device__ __forceinline__ void dev_expand_mask_pair(const uint8_t *rhop, uint32
   }
 }
 template <int LV>
-__device__ __forceinline__ void dev_expand_mask_row(const uint8_t *rhop, uint32_t nonce, const RowKeccak &k, int lane,
-                                                    uint8_t *out) {
-  constexpr int WPB = RATE256 / 4, NWORD = N * P<LV>::ZBITS / 32, NBLK = (NWORD + WPB - 1) / WPB;
-  const uint32_t *rw = (const uint32_t *)rhop;
-  uint32_t *o = (uint32_t *)out;
-  uint32_t a[5];
-#pragma unroll
-  for (int y = 0; y < 5; y++) {
-    const int w = k.word(y);
-    a[y] = w < 8 ? rw[k.half_word(y)] : 0u;
-    if (w == 8 && !k.h) a[y] = (nonce & 0xFFFFu) | (0x1Fu << 16);
-    if (w == RATE256 / 8 - 1 && k.h) a[y] = 0x80u << 24;
-  }
-#pragma unroll 1
-  for (int blk = 0; blk < NBLK; blk++) {
-    keccak_f_row(a, k);
-#pragma unroll
-    for (int y = 0; y < 4; y++)
-      if ((lane & 15) < 10 && k.word(y) < RATE256 / 8 && blk * WPB + k.half_word(y) < NWORD)
-        o[blk * WPB + k.half_word(y)] = a[y];
-  }
-}
-
-template <int LV>
 __global__ void __launch_bounds__(256) rd_mask_k(Ws ws, Group gr, int r) {
   constexpr uint32_t L = Lv<LV>::L;
-  __shared__ uint32_t rows[4][ROW_LDS];
+  __shared__ uint32_t kl[4][KECCAK_LDS];
   __builtin_amdgcn_s_setprio(2);
   const RoundState st = round_state(gr.cnt, gr.n, r);
   const uint32_t total = st.n * st.m * L;
-  const uint32_t lanes = total <= ROW_STATES ? 16 : total <= PAIR_STATES ? 2 : 1;
+  const uint32_t lanes = total <= WAVE_STATES ? 64 : total <= ROW_STATES ? 16 : total <= PAIR_STATES ? 2 : 1;
   const uint32_t id = (blockIdx.x * 256 + threadIdx.x) / lanes;
   if (id >= total) return;
   const uint32_t s = id / L, i = id - s * L, e = s / st.m;
@@ -132,9 +109,10 @@ __global__ void __launch_bounds__(256) rd_mask_k(Ws ws, Group gr, int r) {
     dev_expand_mask<LV>(rhop, kappa, (int)i, out);
   } else if (lanes == 2) {
     dev_expand_mask_pair<LV>(rhop, kappa + i, threadIdx.x & 1, out);
+  } else if (lanes == 16) {
+    dev_expand_mask_coop<LV>(rhop, kappa + i, RowKeccak(kl[threadIdx.x >> 6], threadIdx.x & 63), out);
   } else {
-    const int lane = threadIdx.x & 63;
-    dev_expand_mask_row<LV>(rhop, kappa + i, RowKeccak(rows[threadIdx.x >> 6], lane), lane, out);
+    dev_expand_mask_coop<LV>(rhop, kappa + i, WaveKeccak(kl[threadIdx.x >> 6], threadIdx.x & 63), out);
   }
 }
 
@@ -163,36 +141,47 @@ __global__ void __launch_bounds__(256) rd_w_k(Ws ws, Group gr, int r) {
                     lane);
 }
 
-// ctilde = H(mu || w1), c = SampleInBall(ctilde): two lanes per candidate, or a
-// 16-lane row as long as that takes at most one wavefront per SIMD (eight
-// permutations in series: 65 us on pairs)
+// ctilde = H(mu || w1), c = SampleInBall(ctilde): two lanes per candidate, a
+// 16-lane row as long as that takes at most two wavefronts per SIMD, or a
+// wavefront (eight permutations in series: 65 us on pairs, 43 on rows, 26 on
+// wavefronts)
 inline uint32_t chal_blocks(uint32_t cand) {
-  const uint32_t rows = (std::min(cand, ROW_CHALLENGES) + 3) / 4, pairs = (cand + 31) / 32;
-  return std::max(rows, pairs);
+  const uint32_t waves = std::min(cand, WAVE_STATES), rows = (std::min(cand, ROW_CHALLENGES) + 3) / 4,
+                 pairs = (cand + 31) / 32;
+  return std::max(waves, std::max(rows, pairs));
 }
 template <int LV>
 __global__ void __launch_bounds__(64) rd_chal_k(Ws ws, Group gr, int r) {
-  __shared__ int8_t cl[32][C_ROW];
+  __shared__ __align__(16) int8_t cl[32][C_ROW];
   __shared__ uint32_t bb[32][RATE256 / 4];
-  __shared__ uint32_t rows[ROW_LDS];
+  __shared__ uint32_t kl[KECCAK_LDS];
   __builtin_amdgcn_s_setprio(3);
   const RoundState st = round_state(gr.cnt, gr.n, r);
   const uint32_t total = st.n * st.m;
-  const bool row = total <= ROW_CHALLENGES;
-  const int lane = threadIdx.x, p = row ? lane >> 4 : lane >> 1;
-  const uint32_t s = blockIdx.x * (row ? 4 : 32) + p;
-  if (s >= total) return;  // a whole pair or row
+  const int lane = threadIdx.x, per = total <= WAVE_STATES ? 1 : total <= ROW_CHALLENGES ? 4 : 32;
+  const int p = per == 1 ? 0 : per == 4 ? lane >> 4 : lane >> 1;
+  const uint32_t s = blockIdx.x * per + p;
+  if (s >= total) return;  // a whole pair, row or wavefront
   const uint32_t task = round_task(gr, r, s / st.m);
   const uint8_t *mu = ws.muw1 + (size_t)task * muw1_stride<LV>();
   const uint8_t *w1 = gr.w1 + (size_t)s * Lv<LV>::K * P<LV>::W1B;
   uint32_t *ct = (uint32_t *)(gr.ct + (size_t)s * CT_STRIDE);
-  if (row) dev_challenge_row<LV>(mu, w1, RowKeccak(rows, lane), lane, ct, cl[p], bb[p]);
-  else dev_challenge_pair<LV>(mu, w1, lane & 1, ct, cl[p], bb[p]);
-  wave_sync();
-  const uint32_t *cw = (const uint32_t *)cl[p];
-  int4 *d = (int4 *)(gr.c + (size_t)s * N);
-  for (int v = row ? lane & 15 : lane & 1; v < N / 16; v += row ? 16 : 2)
-    d[v] = make_int4(cw[4 * v], cw[4 * v + 1], cw[4 * v + 2], cw[4 * v + 3]);
+  int8_t *c = gr.c + (size_t)s * N;
+  if (per == 1) {
+    const WaveKeccak k(kl, lane);
+    dev_challenge_coop<LV>(mu, w1, k, ct, cl[0], bb[0]);
+    store_c_coop(cl[0], c, k);
+  } else if (per == 4) {
+    const RowKeccak k(kl, lane);
+    dev_challenge_coop<LV>(mu, w1, k, ct, cl[p], bb[p]);
+    store_c_coop(cl[p], c, k);
+  } else {
+    dev_challenge_pair<LV>(mu, w1, lane & 1, ct, cl[p], bb[p]);
+    wave_sync();
+    const uint32_t *cw = (const uint32_t *)cl[p];
+    for (int v = lane & 1; v < N / 16; v += 2)
+      ((int4 *)c)[v] = make_int4(cw[4 * v], cw[4 * v + 1], cw[4 * v + 2], cw[4 * v + 3]);
+  }
 }
 
 // The checks.  Up to ROUND_SEQ nonces per task, each wavefront takes a task and
