@@ -187,7 +187,7 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.ctilde = take(staged, cap * CT_STRIDE);
   w.cpoly = (int8_t *)take(staged || form == WS_VERIFY, cap * 256);
   w.A = take(!keyset, cap * K * L * A_POLY);
-  w.s12 = (int32_t *)take(form == WS_KEYGEN, cap * (L + K) * 1024);
+  w.s12 = take(form == WS_KEYGEN, cap * (L + K) * S_POLY);
   w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
   w.y = take(staged, cap * L * P<LV>::YB);
   w.w = (int32_t *)take(staged, cap * K * 1024);
@@ -414,8 +414,8 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
   int rc = ws_carve<LV>(ctx, st, count, WS_KEYGEN, false, ws);
   if (rc) return rc;
   kg_seed_k<LV><<<blocks_for(count, 256), 256, 0, st>>>(seeds, pk, sk, ws, count);
-  expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, st>>>(pk, P<LV>::PK, nullptr, ws.A, count);
-  expand_s_k<LV><<<blocks_for((uint64_t)count * (K + L), 256), 256, 0, st>>>(ws, count);
+  const unsigned na = blocks_for((uint64_t)count * K * L, EA_WG), ns = blocks_for((uint64_t)count * (K + L), EA_WG);
+  kg_expand_k<LV><<<na + ns, EA_WG, 0, st>>>(pk, ws, count, na);
   kg_main_k<LV><<<count, 64, 0, st>>>(ws, pk, sk, count);
   launch_tr<LV>(st, pk, sk + 64, P<LV>::SK, count);
   LAUNCHCHK(ctx);

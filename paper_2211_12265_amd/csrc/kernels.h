@@ -24,7 +24,7 @@ struct Ws {
   uint8_t *ctilde;   // [cap][CT_STRIDE]
   int8_t *cpoly;     // [cap][256]  challenge c, dense
   uint8_t *A;        // [cap][K][L][A_POLY]  A-hat, 24 bits per coefficient (load_a)
-  int32_t *s12;      // KeyGen: s1, s2 centred, [cap][L+K][256]
+  uint8_t *s12;      // KeyGen: the streams of s1, s2, [cap][L+K][S_POLY]
   int8_t *sec;       // [cap][sec_bytes] Sign: s1, s2, t0 as int8 tiles (toeplitz.h)
   uint8_t *y;        // [cap][L][YB]  mask, as squeezed
   int32_t *w;        // [cap][K][256]  w = A y as dev_compute_w stores it
@@ -232,13 +232,13 @@ __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], uint8_t *o
 
 // ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk)
 template <int LV>
-__global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
-                                                  uint8_t *A, uint32_t count) {
+__device__ __forceinline__ void dev_expand_a(uint32_t block, const uint8_t *rho_src, size_t rho_stride,
+                                             const uint32_t *key_idx, uint8_t *A, uint32_t count, uint32_t *rows) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
-  uint64_t st = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  __shared__ uint32_t rows[EA_WG / 64][EA_ROWS * EA_ROW];
+  const int lane = threadIdx.x;
+  const uint64_t st = (uint64_t)block * EA_WG + lane;
   const bool valid = st < (uint64_t)count * K * L;
-  const uint64_t sl = valid ? st : 0;  // spare lanes absorb stream 0 and store nothing
+  const uint64_t sl = valid ? st : 0;
   uint32_t task = (uint32_t)(sl / (K * L));
   int ij = (int)(sl % (K * L));
   int i = ij / L, j = ij % L;
@@ -246,21 +246,31 @@ __global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size
   const uint64_t *rho = (const uint64_t *)(rho_src + key * rho_stride);
   uint32_t s[50];
   absorb_seed34(s, [&](int pos) { return rho[pos >> 3]; }, (uint32_t)j | ((uint32_t)i << 8));
-  const int lane = threadIdx.x & 63;
-  expand_a_squeeze_wave<true>(s, A + (size_t)(st - lane) * A_POLY, rows[threadIdx.x >> 6], lane, valid);
+  expand_a_squeeze_wave<true>(s, A + (size_t)(st - lane) * A_POLY, rows, lane, valid);
+}
+template <int LV>
+__global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
+                                                  uint8_t *A, uint32_t count) {
+  __shared__ uint32_t rows[EA_ROWS * EA_ROW];
+  dev_expand_a<LV>(blockIdx.x, rho_src, rho_stride, key_idx, A, count, rows);
 }
 
-// ExpandS: one lane per (task, r < L + K); centred coefficients to ws.s12
+// KeyGen's ExpandA and ExpandS, which need nothing of each other, in one launch:
+// the first nblk_a workgroups are ExpandA's, the others have one lane per (task,
+// r < L + K) of ExpandS and fill the SIMDs as those of ExpandA run out.
 template <int LV>
-__global__ void __launch_bounds__(256) expand_s_k(Ws ws, uint32_t count) {
+__global__ void __launch_bounds__(EA_WG) kg_expand_k(const uint8_t *pk, Ws ws, uint32_t count, uint32_t nblk_a) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
-  uint64_t st = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ uint32_t rows[EA_ROWS * EA_ROW];
+  if (blockIdx.x < nblk_a) {
+    dev_expand_a<LV>(blockIdx.x, pk, P<LV>::PK, nullptr, ws.A, count, rows);
+    return;
+  }
+  const uint64_t st = (uint64_t)(blockIdx.x - nblk_a) * EA_WG + threadIdx.x;
   if (st >= (uint64_t)count * (K + L)) return;
-  uint32_t task = (uint32_t)(st / (K + L));
-  int r = (int)(st % (K + L));
   uint32_t s[50];
-  absorb_seed66(s, ws.rhop + (size_t)task * 64, (uint32_t)r);
-  expand_s_squeeze<Lv<LV>::ETA>(s, ws.s12 + (size_t)st * N);
+  absorb_seed66(s, ws.rhop + st / (K + L) * 64, (uint32_t)(st % (K + L)));
+  expand_s_squeeze<Lv<LV>::ETA>(s, ws.s12 + st * S_POLY);
 }
 
 // LDS layout shared by the per-task polynomial kernels
@@ -282,6 +292,67 @@ __device__ __forceinline__ void to_consecutive(const int32_t x[16], uint32_t v[1
   for (int r = 0; r < 16; r++) v[r] = (uint32_t)y[r];
 }
 
+// The polynomial of an ExpandS stream by a 16-lane group: eta - s of its 256
+// coefficients as bytes in buf (LDS).  A lane takes 32 nibbles of the first 256
+// bytes, its place comes from the lanes before it; what is missing after them
+// (one polynomial of 500) from 16 bytes at a time.
+template <int ETA>
+__device__ __forceinline__ void dev_collect_s(const uint8_t *src, uint8_t *buf, int t) {
+  auto scan = [&](int c, int &total) {  // sum over the group's lanes before this one
+    int s = c;
+    s += (int)row_shr<1>((uint32_t)s);
+    s += (int)row_shr<2>((uint32_t)s);
+    s += (int)row_shr<4>((uint32_t)s);
+    s += (int)row_shr<8>((uint32_t)s);
+    total = __shfl(s, 15, 16);
+    return s - c;
+  };
+  auto put = [&](uint32_t w, uint32_t ok, int nibbles, int pos) {
+    uint32_t v[2] = {w & 0x0F0F0F0Fu, (w >> 4) & 0x0F0F0F0Fu};
+    if constexpr (ETA == 2)  // v mod 5 for v < 15; 13 v < 2^8
+      for (int q = 0; q < 2; q++) v[q] -= 5u * ((13u * v[q] >> 6) & 0x03030303u);
+#pragma unroll
+    for (int b = 0; b < nibbles; b++) {
+      const bool keep = (ok >> (4 * b)) & 1;
+      if (keep && pos < N) buf[pos] = (uint8_t)(v[b & 1] >> (8 * (b >> 1)));
+      pos += keep;
+    }
+    return pos;
+  };
+  const uint4 q = ((const uint4 *)src)[t];
+  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  uint32_t ok[4];
+  int c = 0, got;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    ok[i] = s_accepted<ETA>(w[i]);
+    c += __popc(ok[i]);
+  }
+  int pos = scan(c, got);
+#pragma unroll
+  for (int i = 0; i < 4; i++) pos = put(w[i], ok[i], 8, pos);
+  for (int o = 16 * 16; o < S_POLY && got < N; o += 16) {
+    const uint32_t b = src[o + t], k = s_accepted<ETA>(b) & 0x11u;
+    int more;
+    put(b, k, 2, got + scan(__popc(k), more));
+    got += more;
+  }
+  wave_sync();
+}
+// ... its packed coefficients' words (consecutive layout) and its coefficients (strided layout)
+template <int ETA>
+__device__ __forceinline__ void load_s(const uint8_t *buf, uint32_t v[16], int32_t x[16], int t) {
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const uint32_t w = ((const uint32_t *)buf)[4 * t + q];
+#pragma unroll
+    for (int b = 0; b < 4; b++) v[4 * q + b] = (w >> (8 * b)) & 0xFFu;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; r++) x[r] = ETA - (int32_t)buf[t + 16 * r];
+  wave_sync();
+}
+
 // KeyGen main: t = INTT(A * NTT(s1)) + s2, Power2Round, pack pk's t1 and sk's s1, s2, t0
 template <int LV>
 __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk, uint32_t count) {
@@ -295,16 +366,14 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
   int32_t *tr = lds.tr + g * NTT_LDS_GROUP;
   uint8_t *skb = (uint8_t *)lds.buf;
   uint8_t *pkb = (uint8_t *)pkbuf;
-  const int32_t *S = ws.s12 + (size_t)task * (K + L) * N;
+  const uint8_t *S = ws.s12 + (size_t)task * (K + L) * S_POLY;
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
   // s1: NTT into LDS, and pack eta - s into sk
   for (int j = g; j < L; j += 4) {
     int32_t x[16];
-    load_strided(x, S + j * N, t);
     uint32_t v[16];
-    to_consecutive(x, v, tr, t);
-#pragma unroll
-    for (int r = 0; r < 16; r++) v[r] = (uint32_t)(ETA - (int32_t)v[r]);
+    dev_collect_s<ETA>(S + j * S_POLY, (uint8_t *)tr, t);
+    load_s<ETA>((const uint8_t *)tr, v, x, t);
     pack16_to_lds<PP::EBITS>(v, skb + PP::OFF_S1 + j * PP::EB, t);
     ntt16(x, ftw, tr, t);
 #pragma unroll
@@ -327,11 +396,9 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
     for (int r = 0; r < 16; r++) x[r] = mont_reduce(acc[r]);
     intt16(x, itw, tr, t);
     int32_t s2[16];
-    load_strided(s2, S + (L + i) * N, t);
     uint32_t v[16];
-    to_consecutive(s2, v, tr, t);
-#pragma unroll
-    for (int r = 0; r < 16; r++) v[r] = (uint32_t)(ETA - (int32_t)v[r]);
+    dev_collect_s<ETA>(S + (L + i) * S_POLY, (uint8_t *)tr, t);
+    load_s<ETA>((const uint8_t *)tr, v, s2, t);
     pack16_to_lds<PP::EBITS>(v, skb + PP::OFF_S2 + i * PP::EB, t);
     int32_t t1[16], t0[16];
 #pragma unroll

@@ -106,6 +106,12 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// the value of the lane n before this one in its row of 16; zero for the first n
+template <int n>
+__device__ __forceinline__ uint32_t row_shr(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + n, 0xF, 0xF, true);
+}
+
 // ---- byte movement between global memory and LDS ----
 // Copy NB bytes from global (any alignment) into LDS words (4-aligned,
 // zero-padded to a whole word) with one wavefront.  Only aligned global words

@@ -110,32 +110,31 @@ __device__ __forceinline__ void load_mask(int32_t x[16], const uint8_t *row, int
   }
 }
 
-// ExpandS rejection sampling: nibbles (low then high) of the SHAKE256 stream;
-// eta = 2 keeps v < 15 -> 2 - (v mod 5); eta = 4 keeps v < 9 -> 4 - v.
+// ExpandS: the lane's SHAKE256 stream (absorbed and permuted once) stored as it
+// comes, S_POLY bytes apart: two blocks, or as many as hold 256 accepted nibbles
+// (eta = 2: v < 15, eta = 4: v < 9).  The readers pick them out (dev_collect_s):
+// one lane that tests 544 nibbles one after another and stores 256 words of its
+// own takes five times as long as its two permutations.  Two blocks are short of
+// 256 in one polynomial of 10^5 (eta = 4), four in fewer than one of 10^100.
+constexpr int S_BLOCKS = 4, S_POLY = S_BLOCKS * RATE256;
+static_assert(S_POLY % 16 == 0, "read 16 bytes at a time");
+// bit 0 of every accepted nibble of w
 template <int ETA>
-__device__ __forceinline__ void expand_s_squeeze(uint32_t s[50], int32_t *out) {
-  int ctr = 0;
-  for (;;) {
+__device__ __forceinline__ uint32_t s_accepted(uint32_t w) {
+  const uint32_t r = ETA == 2 ? w & (w >> 1) & (w >> 2) & (w >> 3) : (w >> 3) & (w | (w >> 1) | (w >> 2));
+  return ~r & 0x11111111u;
+}
+template <int ETA>
+__device__ __forceinline__ void expand_s_squeeze(uint32_t s[50], uint8_t *out) {
+  int got = 0;
+#pragma unroll 1
+  for (int blk = 0;; blk++) {
+    uint64_t *o = (uint64_t *)(out + blk * RATE256);
 #pragma unroll
-    for (int byte = 0; byte < RATE256; byte++) {
-      uint32_t bv = (s[byte >> 2] >> (8 * (byte & 3))) & 0xFFu;
+    for (int w = 0; w < RATE256 / 8; w++) o[w] = (uint64_t)s[2 * w + 1] << 32 | s[2 * w];
 #pragma unroll
-      for (int hlf = 0; hlf < 2; hlf++) {
-        uint32_t v = hlf ? (bv >> 4) : (bv & 15u);
-        bool ok;
-        int32_t coef;
-        if constexpr (ETA == 2) {
-          ok = v < 15u;
-          coef = 2 - (int32_t)(v - 5u * ((v * 13u) >> 6));  // v mod 5 for v < 15
-        } else {
-          ok = v < 9u;
-          coef = 4 - (int32_t)v;
-        }
-        if (ok && ctr < N) out[ctr] = coef;
-        ctr += ok;
-      }
-    }
-    if (ctr >= N) break;
+    for (int w = 0; w < RATE256 / 4; w++) got += __popc(s_accepted<ETA>(s[w]));
+    if (blk + 1 == S_BLOCKS || (blk > 0 && got >= N)) break;
     keccak_f(s);
   }
 }
