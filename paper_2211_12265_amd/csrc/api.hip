@@ -393,7 +393,7 @@ void launch_vf_prep(hipStream_t st, const uint8_t *sig, const Ws &ws, uint32_t c
 }
 template <int LV>
 void launch_vf_final(hipStream_t st, const uint8_t *sig, const Ws &ws, int32_t *verdict, uint32_t count) {
-  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+  if (!with_coop(count, ROW_ALONE, [&](auto *e, uint32_t wgs) {
         vf_final_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(sig, ws, verdict, count);
       }))
     vf_final_k<LV><<<blocks_for(2 * (uint64_t)count, 256), 256, 0, st>>>(sig, ws, verdict, count);
@@ -401,7 +401,7 @@ void launch_vf_final(hipStream_t st, const uint8_t *sig, const Ws &ws, int32_t *
 // tr = H(pk) of every row: a state or a lane pair per key
 template <int LV>
 void launch_tr(hipStream_t st, const uint8_t *pk, uint8_t *out, size_t stride, uint32_t count) {
-  if (!with_coop(count, ROW_STATES, [&](auto *e, uint32_t wgs) {
+  if (!with_coop(count, ROW_ALONE, [&](auto *e, uint32_t wgs) {
         tr_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(pk, out, stride, count);
       }))
     tr_pair_k<LV><<<blocks_for(2 * (uint64_t)count, 64), 64, 0, st>>>(pk, out, stride, count);
@@ -519,7 +519,7 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
         }))
       expand_mask_k<LV><<<blocks_for((uint64_t)nactive * L, 256), 256, 0, st>>>(ws, cur, nactive);
     sg_w_k<LV><<<nactive, 64, 0, st>>>(ws, cur, nactive);
-    if (!with_coop(nactive, ROW_CHALLENGES, [&](auto *e, uint32_t wgs) {
+    if (!with_coop(nactive, ROW_ALONE, [&](auto *e, uint32_t wgs) {
           sg_chal_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(ws, cur, nactive);
         }))
       sg_chal_k<LV><<<blocks_for(nactive, 64), 64, 0, st>>>(ws, cur, nactive);

@@ -15,10 +15,12 @@
 //   chi    the next two sheets from lanes l + 2, l + 4.
 // After chi lanes 0 .. 11 are valid, after theta lanes 2 .. 11, which hold every
 // sheet once and are the ones whose words are kept; the read-back makes all 16
-// valid again.  34 VALU and 15 LDS instructions per round against 120 VALU on a
+// valid again.  32 VALU and 16 LDS instructions per round against 120 VALU on a
 // lane pair (keccak_pair.h): 3.4 times the issue slots per state, half the time
-// per permutation of a lone wavefront (3.8 against 6.8 us): the mu chains of 2,503
-// messages of up to 4 KB 328 -> 176 us.
+// per permutation of a lone wavefront (3.1 against 6.8 us): the mu chains of 2,503
+// messages of up to 4 KB 328 -> 176 us.  4,096 states take 4.4 us per permutation,
+// 8,192 5.6, 10,240 6.8, where 320 wavefronts of pairs need no longer.  Round
+// constants from scalar loads instead of LDS: 3.8 us alone, 5.1 with 4,096 states.
 //
 // The functions after the two engines run on either (E: RowKeccak or
 // WaveKeccak, keccak_wave.h).
@@ -33,8 +35,10 @@ struct RowRot {
   static constexpr uint32_t v = row_rot(Y);
 };
 
-// the lane's constants; L: the wavefront's KECCAK_LDS words (four states of 50
-// words and a dump for unkept words)
+// the lane's constants; L: the wavefront's KECCAK_LDS words: four states of 50
+// words, ROW_ST apart, so that the accesses of two rows hit different banks, and
+// a dump for unkept words
+constexpr int ROW_ST = 54;
 struct RowKeccak {
   static constexpr int NR = 5, NA = 4, ND = 2;  // registers; those with words of the rate; with words 0 .. 9
   static constexpr int LANES = 16, STATES = 4;
@@ -45,7 +49,7 @@ struct RowKeccak {
   int wr;               // where the lane keeps word (x, 0); (x, y) is 10 y further
   int p[5], q[5];       // high and low operand of the rotation that yields word (x, y)
   uint32_t s[5];        // its amount
-  uint32_t mlo, mhi;    // lanes that take the round constant's halves
+  const uint32_t *rc;   // round constants
   __device__ __forceinline__ RowKeccak(uint32_t *lds, int lane) {
     L = lds;
     l = lane & 15;
@@ -53,15 +57,14 @@ struct RowKeccak {
     own = l < 10;
     x = m >> 1;
     h = m & 1;
-    st = 50 * ((lane >> 4) & 3);
-    wr = l >= 2 && l < 12 ? st + 2 * x + h : 200;
+    st = ROW_ST * ((lane >> 4) & 3);
+    wr = l >= 2 && l < 12 ? st + 2 * x + h : 4 * ROW_ST - 4;
     place<0>();
     place<1>();
     place<2>();
     place<3>();
     place<4>();
-    mlo = x == 0 && h == 0 ? ~0u : 0u;
-    mhi = x == 0 && h == 1 ? ~0u : 0u;
+    rc = kc_rc_lds<LANES>(L, l, x == 0, h);
   }
   // where register Y is read from: word (sx, sy) with (x, Y) = (sy, 2 sx + 3 sy)
   template <int Y>
@@ -78,12 +81,15 @@ struct RowKeccak {
   __device__ __forceinline__ int word(int y) const { return 5 * y + x; }
   __device__ __forceinline__ int half_word(int y) const { return 2 * word(y) + h; }
   // whether `v` holds on a lane of the state
-  __device__ __forceinline__ bool any(bool v) const { return (__ballot(v) >> (st / 50 * 16) & 0xFFFFu) != 0; }
+  __device__ __forceinline__ bool any(bool v) const { return (__ballot(v) >> (st / ROW_ST * 16) & 0xFFFFu) != 0; }
 };
 
 __device__ __forceinline__ void keccak_f_coop(uint32_t a[5], const RowKeccak &k) {
-#pragma unroll 1
+  const uint32_t *rc = k.rc;
+#pragma unroll 4
   for (int ir = 0; ir < 24; ir++) {
+    const uint32_t rcv = rc[0];
+    rc += 2;
     const uint32_t c = xor3(xor3(a[0], a[1], a[2]), a[3], a[4]);
     uint32_t cm;
     const uint32_t r = row_theta(c, cm);
@@ -96,7 +102,7 @@ __device__ __forceinline__ void keccak_f_coop(uint32_t a[5], const RowKeccak &k)
     wave_sync();
 #pragma unroll
     for (int y = 0; y < 5; y++) a[y] = chi3(b[y], row_dpp<0x102>(b[y]), row_dpp<0x104>(b[y]));
-    a[0] ^= (kKRC.lo[ir] & k.mlo) ^ (kKRC.hi[ir] & k.mhi);
+    a[0] ^= rcv;
   }
 }
 
@@ -333,7 +339,7 @@ __device__ __forceinline__ void store_c_coop(const int8_t *c, int8_t *dst, const
 // ones take lane pairs: beside ExpandA rows would cost it more than they gain
 // (level-3 Verify, 10,000 tasks of up to 4 KB: 555-697 us with rows for the
 // messages of more than 2 KB against 551).
-constexpr uint32_t ROW_STATES = 4096;
+constexpr uint32_t ROW_STATES = 4096, ROW_ALONE = 8192;  // beside ExpandA; with the chip to themselves
 #define DIL_COOP_TASK(E)                                           \
   __shared__ uint32_t L[KECCAK_LDS];                               \
   __builtin_amdgcn_s_setprio(3);                                   \

@@ -5,9 +5,9 @@
 //   theta  column parity by two lane swaps across the rows; the rest as on a row;
 //   rho, pi  through LDS; plane 4 is written by row 0 only and read by all rows;
 //   chi    as on a row.
-// A permutation of a lone wavefront takes 2.5 us against 3.8 us on a row, with
-// two wavefronts per SIMD (2,048 states) 3.4 us against 3.9 us; 4,096 states take
-// 5.1 us against 4.5 us, which is why rows take over above 2,048 (WAVE_STATES).
+// A permutation of a lone wavefront takes 2.5 us against 3.1 us on a row, 1,024
+// states 2.8 against 3.2 us and 2,048, two wavefronts per SIMD, 3.4 us on both;
+// 4,096 take 5.1 us against 4.4 us: rows take over above 2,048 (WAVE_STATES).
 // The mu chains of 613 messages of up to 6 KB take 124 us (rows 213, pairs 493).
 // Lone wavefronts wait for each instruction's result, the four rounds of one loop
 // step save a branch each (2.65 us without), and the round constants come from
@@ -35,11 +35,26 @@ __device__ __forceinline__ uint32_t row_theta(uint32_t c, uint32_t &cm) {
   return __builtin_amdgcn_alignbit(cp, pair_swap(cp), 31);
 }
 
-constexpr int KECCAK_LDS = 256;  // words of LDS per wavefront of either form
+constexpr int KECCAK_LDS = 352;  // words of LDS per wavefront of either form
+constexpr int KECCAK_RC = 256;   // of which the round constants, and as many zeros
+// Writes them with the LANES lanes of one state (the wavefront's other states may
+// not be there); where a lane that takes the constants' half h, or none, reads its own.
+template <int LANES>
+__device__ __forceinline__ const uint32_t *kc_rc_lds(uint32_t *lds, int l, bool takes, int h) {
+#pragma unroll
+  for (int i = 0; i < 48; i += LANES)
+    if (i + l < 48) {
+      const int w = i + l;
+      lds[KECCAK_RC + w] = w & 1 ? kKRC.hi[w >> 1] : kKRC.lo[w >> 1];
+      lds[KECCAK_RC + 48 + w] = 0;
+    }
+  wave_sync();
+  return lds + KECCAK_RC + (takes ? h : 48);
+}
 constexpr uint32_t WAVE_STATES = 2048;
 
 // the lane's constants; L: the wavefront's KECCAK_LDS words (50 of the state, a
-// dump for unkept words, 48 of round constants, 48 zeros)
+// dump for unkept words, the round constants)
 struct WaveKeccak {
   static constexpr int NR = 2, NA = 1, ND = 1;  // registers; those with words of the rate; with words 0 .. 9
   static constexpr int LANES = 64, STATES = 1;
@@ -52,7 +67,7 @@ struct WaveKeccak {
   uint32_t s0, s1;         // their amounts
   const uint32_t *rc;
   __device__ __forceinline__ WaveKeccak(uint32_t *lds, int lane) {
-    constexpr int DUMP = 50, RC = 160;
+    constexpr int DUMP = 50;
     L = lds;
     l = lane & 63;
     row = l >> 4;
@@ -66,12 +81,7 @@ struct WaveKeccak {
     constexpr uint32_t rot[5] = {row_rot(0), row_rot(1), row_rot(2), row_rot(3), row_rot(4)};
     place(row, row < 2 ? (row == 0 ? rot[0] : rot[1]) : (row == 2 ? rot[2] : rot[3]), p0, q0, s0);
     place(4, rot[4], p1, q1, s1);
-    if (l < 48) {
-      L[RC + l] = l & 1 ? kKRC.hi[l >> 1] : kKRC.lo[l >> 1];
-      L[RC + 48 + l] = 0;
-    }
-    rc = L + (x == 0 && row == 0 ? RC + h : RC + 48);
-    wave_sync();
+    rc = kc_rc_lds<LANES>(L, l, x == 0 && row == 0, h);
   }
   // where plane Y is read from: word (sx, x) with sx = x + 3 Y mod 5
   __device__ __forceinline__ void place(int Y, uint32_t rot, int &p, int &q, uint32_t &s) {

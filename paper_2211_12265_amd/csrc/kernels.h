@@ -353,18 +353,22 @@ __device__ __forceinline__ void load_s(const uint8_t *buf, uint32_t v[16], int32
   wave_sync();
 }
 
-// KeyGen main: t = INTT(A * NTT(s1)) + s2, Power2Round, pack pk's t1 and sk's s1, s2, t0
+// KeyGen main: t = INTT(A * NTT(s1)) + s2, Power2Round, pack pk's t1 and sk's
+// s1, s2, t0.  One wavefront per key; LDS holds only what the kernel writes of pk
+// and sk, which decides how many wavefronts a CU takes.
 template <int LV>
 __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk, uint32_t count) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, ETA = Lv<LV>::ETA;
-  __shared__ PolyLds<LV> lds;
-  __shared__ uint32_t pkbuf[PP::PK / 4 + 2];
-  uint32_t task = blockIdx.x;
+  constexpr int SKW = (PP::SK - PP::OFF_S1) / 4, PKW = (PP::PK - 32) / 4;
+  __shared__ int32_t trl[4 * NTT_LDS_GROUP];
+  __shared__ int32_t hat[L * HAT_POLY];
+  __shared__ uint32_t skbuf[SKW], pkbuf[PKW];
+  const uint32_t task = blockIdx.x;
   if (task >= count) return;
   int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
-  int32_t *tr = lds.tr + g * NTT_LDS_GROUP;
-  uint8_t *skb = (uint8_t *)lds.buf;
+  int32_t *tr = trl + g * NTT_LDS_GROUP;
+  uint8_t *skb = (uint8_t *)skbuf;
   uint8_t *pkb = (uint8_t *)pkbuf;
   const uint8_t *S = ws.s12 + (size_t)task * (K + L) * S_POLY;
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
@@ -374,10 +378,10 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
     uint32_t v[16];
     dev_collect_s<ETA>(S + j * S_POLY, (uint8_t *)tr, t);
     load_s<ETA>((const uint8_t *)tr, v, x, t);
-    pack16_to_lds<PP::EBITS>(v, skb + PP::OFF_S1 + j * PP::EB, t);
+    pack16_to_lds<PP::EBITS>(v, skb + j * PP::EB, t);
     ntt16(x, ftw, tr, t);
 #pragma unroll
-    for (int r = 0; r < 16; r++) lds.hat[hat_idx(j, t, r)] = x[r];
+    for (int r = 0; r < 16; r++) hat[hat_idx(j, t, r)] = x[r];
   }
   wave_sync();
   for (int i = g; i < K; i += 4) {
@@ -389,7 +393,7 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
       int32_t a[16];
       load_a(a, Ai + j * A_POLY, t);
 #pragma unroll
-      for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * lds.hat[hat_idx(j, t, r)];
+      for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * hat[hat_idx(j, t, r)];
     }
     int32_t x[16];
 #pragma unroll
@@ -399,7 +403,7 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
     uint32_t v[16];
     dev_collect_s<ETA>(S + (L + i) * S_POLY, (uint8_t *)tr, t);
     load_s<ETA>((const uint8_t *)tr, v, s2, t);
-    pack16_to_lds<PP::EBITS>(v, skb + PP::OFF_S2 + i * PP::EB, t);
+    pack16_to_lds<PP::EBITS>(v, skb + (PP::OFF_S2 - PP::OFF_S1) + i * PP::EB, t);
     int32_t t1[16], t0[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) {
@@ -411,16 +415,16 @@ __global__ void __launch_bounds__(64) kg_main_k(Ws ws, uint8_t *pk, uint8_t *sk,
       t0[r] = (1 << (D - 1)) - t0[r];
     }
     to_consecutive(t1, v, tr, t);
-    pack16_to_lds<10>(v, pkb + 32 + i * PP::T1B, t);
+    pack16_to_lds<10>(v, pkb + i * PP::T1B, t);
     to_consecutive(t0, v, tr, t);
-    pack16_to_lds<13>(v, skb + PP::OFF_T0 + i * PP::T0B, t);
+    pack16_to_lds<13>(v, skb + (PP::OFF_T0 - PP::OFF_S1) + i * PP::T0B, t);
   }
   wave_sync();
   // copy the packed regions out (pk[32..PK), sk[OFF_S1..SK)); rho, K, tr are written elsewhere
-  uint32_t *pkg = (uint32_t *)(pk + (size_t)task * PP::PK);
-  for (int w = 8 + lane; w < PP::PK / 4; w += 64) pkg[w] = pkbuf[w];
-  uint32_t *skg = (uint32_t *)(sk + (size_t)task * PP::SK);
-  for (int w = PP::OFF_S1 / 4 + lane; w < PP::SK / 4; w += 64) skg[w] = lds.buf[w];
+  uint32_t *pkg = (uint32_t *)(pk + (size_t)task * PP::PK + 32);
+  for (int w = lane; w < PKW; w += 64) pkg[w] = pkbuf[w];
+  uint32_t *skg = (uint32_t *)(sk + (size_t)task * PP::SK + PP::OFF_S1);
+  for (int w = lane; w < SKW; w += 64) skg[w] = skbuf[w];
 }
 
 // ------------------------------------------------------------------------

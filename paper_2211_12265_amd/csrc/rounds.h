@@ -55,9 +55,9 @@ __device__ __forceinline__ uint32_t round_task(const Group &gr, int r, uint32_t 
 // would hold at most one wavefront per SIMD, a stream gets a lane pair, and
 // with still fewer a 16-lane row or a whole wavefront (two per SIMD).  A stream
 // is five permutations one after another and a lone wavefront's permutation
-// takes 9.2 us on one lane, 6.8 us on a pair, 3.8 us on a row and 2.5 us over
+// takes 9.2 us on one lane, 6.8 us on a pair, 3.1 us on a row and 2.5 us over
 // the wavefront; beyond these counts the wider forms would queue for the SIMDs.
-constexpr uint32_t PAIR_STATES = 32768, ROW_CHALLENGES = 8192;
+constexpr uint32_t PAIR_STATES = 32768;
 inline uint32_t mask_blocks(uint64_t streams, bool exact) {
   // 256-lane workgroups that the form of at most `streams` streams needs (exact: of that many)
   auto need = [](uint64_t n) -> uint64_t {
@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(256) rd_w_k(Ws ws, Group gr, int r) {
 // wavefront (eight permutations in series: 65 us on pairs, 43 on rows, 26 on
 // wavefronts)
 inline uint32_t chal_blocks(uint32_t cand) {
-  const uint32_t waves = std::min(cand, WAVE_STATES), rows = (std::min(cand, ROW_CHALLENGES) + 3) / 4,
+  const uint32_t waves = std::min(cand, WAVE_STATES), rows = (std::min(cand, ROW_ALONE) + 3) / 4,
                  pairs = (cand + 31) / 32;
   return std::max(waves, std::max(rows, pairs));
 }
@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(64) rd_chal_k(Ws ws, Group gr, int r) {
   __builtin_amdgcn_s_setprio(3);
   const RoundState st = round_state(gr.cnt, gr.n, r);
   const uint32_t total = st.n * st.m;
-  const int lane = threadIdx.x, per = total <= WAVE_STATES ? 1 : total <= ROW_CHALLENGES ? 4 : 32;
+  const int lane = threadIdx.x, per = total <= WAVE_STATES ? 1 : total <= ROW_ALONE ? 4 : 32;
   const int p = per == 1 ? 0 : per == 4 ? lane >> 4 : lane >> 1;
   const uint32_t s = blockIdx.x * per + p;
   if (s >= total) return;  // a whole pair, row or wavefront
