@@ -165,9 +165,14 @@ __device__ __forceinline__ void absorb_prefix_msg_coop(uint32_t a[E::NR], const 
 }
 
 // SampleInBall on a row whose state holds the first SHAKE256 block of ctilde;
-// c: 256 bytes, bw: 34 words (the wavefront form needs none), both LDS, 4-byte aligned
+// c: 256 bytes, bw: 34 words (the wavefront form needs none), both LDS, 4-byte
+// aligned.  As on a wavefront, lane l follows the signs of steps l, l + 16, ...;
+// the rows take one byte each per step, whether they keep it or not, so that the
+// bytes are read ahead, four at a time.  (With the array in LDS a step waited for
+// the byte and for c[b]: the challenges of 8,192 candidates 64 us.)
 template <int TAU>
 __device__ __forceinline__ void sample_in_ball_coop(uint32_t a[5], const RowKeccak &k, int8_t *c, uint32_t *bw) {
+  constexpr int SLOTS = (TAU + 15) / 16;
   auto stage = [&]() {
     if (k.own) {
 #pragma unroll
@@ -180,28 +185,34 @@ __device__ __forceinline__ void sample_in_ball_coop(uint32_t a[5], const RowKecc
   uint32_t *cw = (uint32_t *)c;
 #pragma unroll
   for (int w = 0; w < N / 64; w++) cw[16 * w + k.l] = 0;
-  wave_sync();
-  const uint8_t *bytes = (const uint8_t *)bw;
-  uint64_t signs = (uint64_t)bw[0] | ((uint64_t)bw[1] << 32);
-  int pos = 8;
-  for (int i = N - TAU; i < N; i++) {
-    int b;
-    for (;;) {
-      if (pos == RATE256) {
-        wave_sync();
-        keccak_f_coop(a, k);
-        stage();
-        pos = 0;
-      }
-      b = bytes[pos++];
-      if (b <= i) break;
+  const uint64_t signs = (uint64_t)bw[0] | ((uint64_t)bw[1] << 32);
+  int at[SLOTS], i = N - TAU;
+#pragma unroll
+  for (int q = 0; q < SLOTS; q++) at[q] = -1;
+  for (int w = 2;; w++) {
+    if (w == RATE256 / 4) {
+      wave_sync();
+      keccak_f_coop(a, k);
+      stage();
+      w = 0;
     }
-    if (k.l == 0) {
-      c[i] = c[b];
-      c[b] = (int8_t)(1 - 2 * (int)(signs & 1));
+    const uint32_t v = bw[w];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int b = (int)((v >> (8 * j)) & 0xFFu);
+      const bool keep = b <= i && i < N;
+      const int from = keep ? b : N, step = keep ? i - (N - TAU) : N;
+#pragma unroll
+      for (int q = 0; q < SLOTS; q++) at[q] = step == 16 * q + k.l ? b : at[q] == from ? i : at[q];
+      i += keep;
     }
-    signs >>= 1;
+    if (!wave_any(i < N)) break;
   }
+  wave_sync();
+#pragma unroll
+  for (int q = 0; q < SLOTS; q++)
+    if (16 * q + k.l < TAU) c[at[q]] = (int8_t)(1 - 2 * (int)(signs >> (16 * q + k.l) & 1));
+  wave_sync();
 }
 
 // ctilde = H(mu || w1) and c = SampleInBall(ctilde) (as dev_challenge_pair); ctilde_out: CT / 4 words
