@@ -423,8 +423,8 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
 }
 
 // Resident key tables replace the per-task A-hat and secret tiles (no ExpandA,
-// no unpacking).  A caller's key_idx is read only once, by keys_check_k
-// (check_keys below), which writes a copy with every index inside the table
+// no unpacking).  A caller's key_idx is read only once, by begin_k
+// (begin_call below), which writes a copy with every index inside the table
 // to `checked`; every other kernel of the call reads that copy, which this
 // returns (nullptr when the call has no key_idx: task i uses row i).
 const uint32_t *use_keyset(Ws &ws, const dil_keyset *ks, const uint32_t *key_idx, uint32_t *checked) {
@@ -435,10 +435,13 @@ const uint32_t *use_keyset(Ws &ws, const dil_keyset *ks, const uint32_t *key_idx
   ws.kmap = key_idx ? checked : nullptr;
   return ws.kmap;
 }
-void check_keys(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, uint32_t *checked, uint32_t count,
-                hipStream_t st) {
-  if (ks && key_idx)
-    keys_check_k<<<blocks_for(count, 256), 256, 0, st>>>(key_idx, ks->nkeys, checked, count, ctx->dev_stats + 9);
+// The launch that begins a call, if it needs one: na words at a and nb at b to zero, key indices to check
+void begin_call(dil_ctx *ctx, uint32_t *a, int na, uint32_t *b, int nb, const dil_keyset *ks, const uint32_t *key_idx,
+                uint32_t *checked, uint32_t count, hipStream_t st) {
+  const bool keys = ks && key_idx;
+  if (keys || na || nb)
+    begin_k<<<keys ? blocks_for(count, 256) : 1, 256, 0, st>>>(a, na, b, nb, keys ? key_idx : nullptr,
+                                                               keys ? ks->nkeys : 0, checked, count, ctx->dev_stats + 9);
 }
 
 // The hash kernels in the form for `count` tasks and the context's message form:
@@ -497,7 +500,7 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
   int rc = ws_carve<LV>(ctx, st, count, WS_SIGN_STAGED, ks != nullptr, ws, 0, nullptr, 1, &kid);
   if (rc) return rc;
   if (ks) {
-    check_keys(ctx, ks, key_idx, kid, count, st);
+    begin_call(ctx, nullptr, 0, nullptr, 0, ks, key_idx, kid, count, st);
     key_idx = use_keyset(ws, ks, key_idx, kid);
   }
   HIPCHK(ctx, hipMemsetAsync(ws.counters, 0, 16 * 4, st));
@@ -657,8 +660,7 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
   hipEvent_t *evs = ctx->timing ? ctx->ev[ctx->ev_count % dil_ctx::RING] : nullptr;
   if (evs) HIPCHK(ctx, hipEventRecord(evs[0], st));
   rc = enqueue(ctx, key, st, [&](hipStream_t s) {
-    zero_words_k<<<1, 256, 0, s>>>(base.cnt, (int)(rp.groups * ROUND_WORDS), ctx->dev_stats, 8);
-    check_keys(ctx, ks, key_in, kid, count, s);
+    begin_call(ctx, base.cnt, (int)(rp.groups * ROUND_WORDS), ctx->dev_stats, 8, ks, key_in, kid, count, s);
     if (!ks) {
       int r2 = fork_side(ctx, s, 1);
       if (r2) return r2;
@@ -728,8 +730,7 @@ int sign_persistent(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, co
   hipEvent_t *evs = ctx->timing ? ctx->ev[ctx->ev_count % dil_ctx::RING] : nullptr;
   if (evs) HIPCHK(ctx, hipEventRecord(evs[0], st));
   rc = enqueue(ctx, key, st, [&](hipStream_t s) {
-    zero_words_k<<<1, 64, 0, s>>>(ws.counters, 16, ctx->dev_stats, 8);
-    check_keys(ctx, ks, key_in, kid, count, s);
+    begin_call(ctx, ws.counters, 16, ctx->dev_stats, 8, ks, key_in, kid, count, s);
     int r2 = sign_setup<LV>(ctx, ws, sk, key_idx, msg, msg_off, count, s, ks, ctx->dev_stats + 8, true, rnd);
     if (r2) return r2;
     LAUNCHCHK(ctx);
@@ -788,6 +789,19 @@ void launch_vf_hash(const dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_i
 }
 
 template <int LV>
+void launch_vf_front(const dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg,
+                     const uint64_t *msg_off, const uint8_t *sig, const Ws &ws, uint32_t count, uint32_t *err,
+                     hipStream_t st) {
+  if constexpr (Lv<LV>::MLDSA) {
+    if (ctx->mldsa_internal) {
+      vf_front_k<LV, true><<<2 * count, 64, 0, st>>>(pk, key_idx, msg, msg_off, sig, ws, count, err);
+      return;
+    }
+  }
+  vf_front_k<LV, false><<<2 * count, 64, 0, st>>>(pk, key_idx, msg, msg_off, sig, ws, count, err);
+}
+
+template <int LV>
 int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
                 const uint8_t *sig, int32_t *verdict, uint32_t count, hipStream_t st,
                 const dil_keyset *ks = nullptr) {
@@ -802,8 +816,13 @@ int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const 
                       (uint64_t)sig, (uint64_t)verdict, count, (uint64_t)ks, (uint64_t)ctx->ws_mem, 0, 0, 0, 0,
                       (uint64_t)ctx->mldsa_internal};
   rc = enqueue(ctx, key, st, [&](hipStream_t s) {
-    zero_words_k<<<1, 64, 0, s>>>(ws.counters, 16, nullptr, 0);
-    check_keys(ctx, ks, key_in, kid, count, s);
+    begin_call(ctx, nullptr, 0, nullptr, 0, ks, key_in, kid, count, s);
+    if (ks && count <= FRONT_TASKS) {
+      launch_vf_front<LV>(ctx, pk, key_idx, msg, msg_off, sig, ws, count, ctx->dev_stats + 8, s);
+      launch_vf_final<LV>(s, sig, ws, verdict, count);
+      LAUNCHCHK(ctx);
+      return DIL_OK;
+    }
     // Three independent fronts: the tr / mu hash chain (needed only by the
     // final hash), ExpandA, and SampleInBall + hint decoding.  Outside the
     // staged form the first two run on side streams and are joined where
@@ -1202,11 +1221,14 @@ int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_
   ws.t1s = nullptr;
   ws.tr = nullptr;
   const uint32_t *kidx = use_keyset(ws, ks, key_idx, kid);
-  zero_words_k<<<1, 64, 0, st>>>(ws.counters, 16, nullptr, 0);
-  check_keys(ctx, ks, key_idx, kid, count, st);
-  launch_vf_hash<LV>(ctx, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG, st);
-  launch_vf_prep<LV>(st, sig, ws, count);
-  vf_main_k<LV><<<count, 64, 0, st>>>(ks->pk, kidx, sig, ws, count);
+  begin_call(ctx, nullptr, 0, nullptr, 0, ks, key_idx, kid, count, st);
+  if (count <= FRONT_TASKS) {
+    launch_vf_front<LV>(ctx, ks->pk, kidx, msg, msg_off, sig, ws, count, ctx->dev_stats + ERR_WORD_MSG, st);
+  } else {
+    launch_vf_hash<LV>(ctx, ks->pk, kidx, msg, msg_off, ws, count, ctx->dev_stats + ERR_WORD_MSG, st);
+    launch_vf_prep<LV>(st, sig, ws, count);
+    vf_main_k<LV><<<count, 64, 0, st>>>(ks->pk, kidx, sig, ws, count);
+  }
   launch_vf_final<LV>(st, sig, ws, verdict, count);
   LAUNCHCHK(ctx);
   return DIL_OK;

@@ -395,6 +395,32 @@ __global__ void __launch_bounds__(64) vf_prep_coop_k(const uint8_t *sig, Ws ws, 
   dev_ball_coop<LV>(sig + (size_t)t * P<LV>::SIG, k, cl[p], bb[p]);
   store_c_coop(cl[p], ws.cpoly + (size_t)t * N, k);
 }
+// The fronts of a small Verify that has its tables: workgroups 0 .. count - 1 hash
+// mu, the others sample the challenge and do the main part, a wavefront each.  In
+// one launch because the hash chain, 45 permutations for 6 KB, leaves the chip
+// nearly idle: 333 messages at ML-DSA-87 took 155 us with three launches
+// in series, 128 with one.
+constexpr uint32_t FRONT_TASKS = WAVE_STATES / 2;  // above, the two would queue for LDS
+template <int LV, bool INTERNAL>
+__global__ void __launch_bounds__(64, 3)
+    vf_front_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *msg, const uint64_t *msg_off,
+               const uint8_t *sig, Ws ws, uint32_t count, uint32_t *err) {
+  __shared__ VfLds<LV> lds;
+  static_assert(sizeof lds.zh >= 4 * KECCAK_LDS && sizeof lds.region >= N, "the sponge's words, the challenge");
+  const int lane = threadIdx.x;
+  const WaveKeccak k((uint32_t *)lds.zh, lane);
+  if (blockIdx.x < count) {
+    __builtin_amdgcn_s_setprio(3);
+    dev_hash_coop<LV, INTERNAL>(blockIdx.x, k, pk, key_idx, msg, msg_off, ws, err);
+    return;
+  }
+  const uint32_t task = blockIdx.x - count;
+  dev_ball_coop<LV>(sig + (size_t)task * P<LV>::SIG, k, (int8_t *)lds.region, nullptr);
+  const uint32_t cw = lds.region[lane];
+  wave_sync();
+  dev_vf_main<LV>(task, cw, lds, pk, key_idx, sig, ws);
+}
+
 // as vf_final_k
 template <int LV, class E>
 __global__ void __launch_bounds__(64) vf_final_coop_k(const uint8_t *sig, Ws ws, int32_t *verdict, uint32_t count) {

@@ -69,13 +69,18 @@ __global__ void zero_words_k(uint32_t *a, int na, uint32_t *b, int nb) {
     for (int i = threadIdx.x; i < nb; i += blockDim.x) b[i] = 0;
 }
 
-// Key-table calls: copy key_idx into the workspace with every index outside
-// the table replaced by row 0 and the error word set, so no later kernel reads
-// past the table; the host reports the error at its next check.
-__global__ void __launch_bounds__(256) keys_check_k(const uint32_t *key_idx, uint32_t nkeys, uint32_t *out,
-                                                   uint32_t count, uint32_t *err) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
+// The first launch of a call: zeroes two word arrays (workgroup 0) and, in
+// key-table calls (key_idx set), copies key_idx into the workspace with every
+// index outside the table replaced by row 0 and the error word set, so no later
+// kernel reads past the table; the host reports the error at its next check.
+__global__ void __launch_bounds__(256) begin_k(uint32_t *a, int na, uint32_t *b, int nb, const uint32_t *key_idx,
+                                               uint32_t nkeys, uint32_t *out, uint32_t count, uint32_t *err) {
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < na; i += 256) a[i] = 0;
+    for (int i = threadIdx.x; i < nb; i += 256) b[i] = 0;
+  }
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (!key_idx || i >= count) return;
   uint32_t k = key_idx[i];
   if (k >= nkeys) {
     k = 0;
@@ -989,30 +994,34 @@ __device__ __forceinline__ bool dev_decode_hints(const uint8_t *hb, uint32_t *hm
   return bad;
 }
 
-// w1' = UseHint(h, INTT(A NTT(z)) - c t1 2^d), packed after mu; z norm check and
-// hint decoding.  One wavefront per task.  c t1 comes from the matrix cores
-// (toeplitz.h) after the INTT, which leaves two NTT passes of four polynomials
-// per four rows: NTT(c) and NTT(t1 2^d) ran as two more.
+// LDS of the main part of Verify.  The signature's bytes are dead once z and the
+// hints are unpacked; the copies of the challenge and the packed w1' rows take
+// their place.
 template <int LV>
-__global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *sig, Ws ws,
-                                                uint32_t count) {
+struct VfLds {
+  static constexpr int SIGW = P<LV>::SIG / 4 + 3, W1W = Lv<LV>::K * P<LV>::W1B / 4 + 1, TW = TOEP_WORDS + 132;
+  __align__(16) int32_t trl[4 * NTT_LDS_GROUP];
+  int32_t zh[Lv<LV>::L * HAT_POLY];
+  __align__(16) uint32_t region[SIGW > TW + W1W ? SIGW : TW + W1W];
+  uint32_t hm[8 * Lv<LV>::K];
+};
+// w1' = UseHint(h, INTT(A NTT(z)) - c t1 2^d), packed after mu; z norm check and
+// hint decoding.  One wavefront per task; cw: the lane's word of the dense
+// challenge.  c t1 comes from the matrix cores (toeplitz.h) after the INTT, which
+// leaves two NTT passes of four polynomials per four rows: NTT(c) and
+// NTT(t1 2^d) ran as two more (level 3, 10,000 tasks: 128 us, now 106).
+template <int LV>
+__device__ __forceinline__ void dev_vf_main(uint32_t task, uint32_t cw, VfLds<LV> &lds, const uint8_t *pk,
+                                            const uint32_t *key_idx, const uint8_t *sig, const Ws &ws) {
   using PP = P<LV>;
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L, BETA = Lv<LV>::BETA;
   constexpr int32_t G1 = Lv<LV>::GAMMA1;
-  // The signature's bytes are dead once z and the hints are unpacked; the
-  // copies of the challenge and the packed w1' rows take their place.
-  constexpr int SIGW = PP::SIG / 4 + 3, W1W = K * PP::W1B / 4 + 1, TW = TOEP_WORDS + 132;
-  __shared__ __align__(16) int32_t trl[4 * NTT_LDS_GROUP];
-  __shared__ int32_t zh[L * HAT_POLY];
-  __shared__ __align__(16) uint32_t region[SIGW > TW + W1W ? SIGW : TW + W1W];
-  __shared__ uint32_t hm[8 * K];
-  uint32_t *const sigw = region, *const ct = region, *const w1b = region + TW;
-  uint32_t task = blockIdx.x;
-  if (task >= count) return;
+  int32_t *const trl = lds.trl, *const zh = lds.zh;
+  uint32_t *const region = lds.region, *const hm = lds.hm;
+  uint32_t *const sigw = region, *const ct = region, *const w1b = region + VfLds<LV>::TW;
   int lane = threadIdx.x, g = lane >> 4, t = lane & 15;
   int32_t *tr = trl + g * NTT_LDS_GROUP;
   const size_t key = key_idx ? key_idx[task] : task;
-  const uint32_t cw = ((const uint32_t *)(ws.cpoly + (size_t)task * N))[lane];
   const uint8_t *A = ws.A + kix(ws, task) * K * L * A_POLY;
   g2l_bytes<PP::SIG>(sig + (size_t)task * PP::SIG, sigw, lane);
   if (lane < 2) sigw[PP::SIG / 4 + 1 + lane] = 0;
@@ -1088,6 +1097,15 @@ __global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4) vf_main_k(const uin
   uint32_t *dst = (uint32_t *)(ws.muw1 + (size_t)task * muw1_stride<LV>() + 64);
   for (int w = lane; w < K * PP::W1B / 4; w += 64) dst[w] = w1b[w];
   if (lane == 0) ws.flag[task] = !bad;
+}
+template <int LV>
+__global__ void __launch_bounds__(64, Lv<LV>::K > 4 ? 3 : 4)
+    vf_main_k(const uint8_t *pk, const uint32_t *key_idx, const uint8_t *sig, Ws ws, uint32_t count) {
+  __shared__ VfLds<LV> lds;
+  const uint32_t task = blockIdx.x;
+  if (task >= count) return;
+  const uint32_t cw = ((const uint32_t *)(ws.cpoly + (size_t)task * N))[threadIdx.x];
+  dev_vf_main<LV>(task, cw, lds, pk, key_idx, sig, ws);
 }
 
 // ctilde' = H(mu || w1'), verdict; two lanes per task (keccak_pair.h), the
