@@ -73,7 +73,9 @@ extern "C" {
 /* Execution forms for Sign (dil_ctx_set_mode):
  *   DIL_MODE_STAGED      one kernel launch per pipeline stage, host-driven
  *                        rejection loop over the still-active tasks (the host
- *                        synchronises once per loop round).
+ *                        synchronises once per loop round; a few hundred
+ *                        tasks or less take all stages in one launch, up to 64
+ *                        loop rounds at a time).
  *   DIL_MODE_PERSISTENT  fused persistent kernel with a device-side work queue
  *                        (asynchronous; no host round trips). */
 #define DIL_MODE_STAGED 0

@@ -513,8 +513,18 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
   int rounds = 0;
   while (nactive > 0) {
     if (++rounds > 4096) return fail(ctx, DIL_EHIP, "sign loop did not terminate");
+    HIPCHK(ctx, hipMemsetAsync(ws.counters, 0, 8, st));
+    if ((uint64_t)nactive * L <= FEW_STREAMS) {
+      sg_few_k<LV><<<nactive, 64 * L, 0, st>>>(ws, sig, cur, nactive, nxt);
+      LAUNCHCHK(ctx);
+      HIPCHK(ctx, hipMemcpyAsync(ctx->host_counters, ws.counters, 8, hipMemcpyDeviceToHost, st));
+      HIPCHK(ctx, hipStreamSynchronize(st));
+      nactive = ctx->host_counters[0];
+      evaluated += ctx->host_counters[1];
+      std::swap(cur, nxt);
+      continue;
+    }
     evaluated += nactive;
-    HIPCHK(ctx, hipMemsetAsync(ws.counters, 0, 4, st));
     // a round ends on the host: few tasks make it as long as its chains of permutations
     const uint32_t streams = std::min<uint64_t>((uint64_t)nactive * L, UINT32_MAX);
     if (!with_coop(streams, ROW_STATES, [&](auto *e, uint32_t wgs) {
@@ -609,13 +619,17 @@ void launch_mask(const Ws &ws, const Group &gr, int r, hipStream_t s) {
   const uint64_t streams = (uint64_t)launch_candidates(gr, r) * Lv<LV>::L;
   rd_mask_k<LV><<<mask_blocks(streams, r == 0), 256, 0, s>>>(ws, gr, r);
 }
-// The rest of the round.
+// The rest of the round (few: with its masks).
 template <int LV>
-void launch_round(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int r, hipStream_t s) {
+void launch_round(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int r, bool few, hipStream_t s) {
   const uint32_t cand = launch_candidates(gr, r);
   const uint32_t wgs = r == 0 && round_nonces(gr.n) <= ROUND_SEQ ? blocks_for(gr.n, 4) : gr.n;
-  rd_w_k<LV><<<blocks_for(cand, 4), 256, 0, s>>>(ws, gr, r);
-  rd_chal_k<LV><<<chal_blocks(cand), 64, 0, s>>>(ws, gr, r);
+  if (few) {
+    rd_cand_k<LV><<<cand, 64 * Lv<LV>::L, 0, s>>>(ws, gr, r);
+  } else {
+    rd_w_k<LV><<<blocks_for(cand, 4), 256, 0, s>>>(ws, gr, r);
+    rd_chal_k<LV><<<chal_blocks(cand), 64, 0, s>>>(ws, gr, r);
+  }
   rd_check_k<LV><<<wgs, 256, 0, s>>>(ws, gr, sig, r, ctx->dev_stats);
 }
 // The finishing launch after `rounds` rounds.
@@ -647,6 +661,7 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
   const RoundPlan rp = round_plan(count);
   const uint32_t *key_in = key_idx;
   if (ks) key_idx = use_keyset(ws, ks, key_idx, kid);
+  const bool few = count <= CAND_TASKS;
   auto group = [&](uint32_t g) {
     Group gr = base;
     gr.first = g * rp.size;
@@ -670,7 +685,7 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     if (!ks)
       expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, ctx->side[0]>>>(sk, P<LV>::SK, key_idx,
                                                                                          ws.A, count);
-    launch_mask<LV>(ws, group(0), 0, s);
+    if (!few) launch_mask<LV>(ws, group(0), 0, s);
     if (!ks) {
       sg_secret_k<LV><<<count, 64, 0, s>>>(sk, key_idx, ws, count);
       int r2 = join_side(ctx, s, 1);
@@ -685,8 +700,8 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     const Group gr = group(g);
     const int rounds = round_count<LV>(gr.n);
     for (int r = 0; r < rounds; r++) {
-      if (g + r > 0) launch_mask<LV>(ws, gr, r, st);
-      launch_round<LV>(ctx, ws, gr, sig, r, st);
+      if (g + r > 0 && !few) launch_mask<LV>(ws, gr, r, st);
+      launch_round<LV>(ctx, ws, gr, sig, r, few, st);
     }
     launch_finish<LV>(ctx, ws, gr, sig, rounds, st);
   }

@@ -567,7 +567,10 @@ __device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t ka
 // The fences of the NTT's LDS transposes keep the compiler from hoisting these
 // loads by itself, which leaves each load's latency exposed; requesting them
 // early costs 12 registers per lane, which only the l = 4 loop kernels have.
-template <int LV, bool PAD = true, bool EARLY = false, class TW>
+// NG: 16-lane groups that share the work; with more than a wavefront's four, all
+// wavefronts of the workgroup meet at two barriers, and the packed HighBits(w)
+// stay in w1buf.
+template <int LV, bool PAD = true, bool EARLY = false, int NG = 4, class TW>
 __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A, int32_t *w_out, uint8_t *w1_out,
                                               int32_t *hat, int32_t *tr, uint32_t *w1buf, const TW &ftw,
                                               const TW &itw, int lane) {
@@ -578,15 +581,16 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A
   if constexpr (EARLY) {
     if (g < K) an.load(A + (size_t)g * L * A_POLY, t);
   }
-  for (int j = g; j < L; j += 4) {
+  for (int j = g; j < L; j += NG) {
     int32_t x[16];
     load_mask<PP::ZBITS, Lv<LV>::GAMMA1>(x, y + j * PP::YB, t);
     ntt16<TW, PAD>(x, ftw, tr, t);
 #pragma unroll
     for (int r = 0; r < 16; r++) hat[hat_idx(j, t, r)] = x[r];
   }
-  wave_sync();
-  for (int i = g; i < K; i += 4) {
+  if constexpr (NG > 4) __syncthreads();
+  else wave_sync();
+  for (int i = g; i < K; i += NG) {
     const uint8_t *Ai = A + (size_t)i * L * A_POLY;
     int64_t acc[16];
 #pragma unroll
@@ -596,7 +600,7 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A
         int32_t a[16];
         an.get(a);
         if (j + 1 < L) an.load(Ai + (j + 1) * A_POLY, t);
-        else if (i + 4 < K) an.load(A + (size_t)(i + 4) * L * A_POLY, t);
+        else if (i + NG < K) an.load(A + (size_t)(i + NG) * L * A_POLY, t);
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[r] += (int64_t)a[r] * hat[hat_idx(j, t, r)];
       }
@@ -624,9 +628,13 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A
     to_consecutive<PAD>(w1, v, tr, t);
     pack16_to_lds<PP::W1BITS>(v, (uint8_t *)w1buf + i * PP::W1B, t);
   }
-  wave_sync();
-  uint32_t *dst = (uint32_t *)w1_out;
-  for (int w = lane; w < K * PP::W1B / 4; w += 64) dst[w] = w1buf[w];
+  if constexpr (NG > 4) {
+    __syncthreads();
+  } else {
+    wave_sync();
+    uint32_t *dst = (uint32_t *)w1_out;
+    for (int w = lane; w < K * PP::W1B / 4; w += 64) dst[w] = w1buf[w];
+  }
 }
 
 // SampleInBall on the lane's SHAKE256(ctilde) stream, into a per-lane 256-byte

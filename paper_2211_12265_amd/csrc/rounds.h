@@ -238,4 +238,110 @@ __global__ void __launch_bounds__(256, 3) rd_check_k(Ws ws, Group gr, uint8_t *s
   if (threadIdx.x == 0 && seq) atomicAdd((unsigned long long *)&stats[6], (unsigned long long)seq);
 }
 
+// ---- one candidate by one workgroup of l wavefronts ----
+// With few candidates every stage is one chain on a nearly idle chip, and what
+// counts is the length of the chains and of the way between them: mask
+// polynomial i on wavefront i, w on eight 16-lane groups of two wavefronts (one
+// pass of each transform instead of two at l > 4), the challenge on the first one,
+// with the packed HighBits(w) still in LDS.
+template <int LV>
+struct CandLds {
+  uint32_t kl[Lv<LV>::L][KECCAK_LDS];
+  union {
+    struct {
+      int32_t hat[Lv<LV>::L * HAT_POLY];
+      int32_t tr[8 * NTT_LDS_GROUP];
+      uint32_t w1buf[Lv<LV>::K * P<LV>::W1B / 4 + 1];
+    };
+    CheckLds<LV> ck;
+  };
+  __align__(16) int8_t c[N];
+  uint32_t ct[P<LV>::CT / 4];
+  int ok;
+};
+// y to y_out, w to w_out, ctilde and c to lds; k: the wavefront's engine on its
+// lds.kl.  All wavefronts call; only the first may read ct and c without a barrier.
+template <int LV>
+__device__ __forceinline__ void dev_candidate(const uint8_t *rhop, uint32_t kappa, const uint8_t *A, const uint8_t *mu,
+                                              uint8_t *y_out, int32_t *w_out, const WaveKeccak &k, CandLds<LV> &lds) {
+  static_assert(Lv<LV>::L >= 2, "two wavefronts for w");
+  const int tid = threadIdx.x, wave = tid >> 6, t = tid & 15;
+  dev_expand_mask_coop<LV>(rhop, kappa + wave, k, y_out + wave * P<LV>::YB);
+  __syncthreads();
+  if (wave < 2) {
+    const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
+    dev_compute_w<LV, true, true, 8>(y_out, A, w_out, nullptr, lds.hat, lds.tr + (tid >> 4) * NTT_LDS_GROUP, lds.w1buf,
+                                     ftw, itw, tid);
+  } else {  // its two barriers
+    __syncthreads();
+    __syncthreads();
+  }
+  if (wave == 0) dev_challenge_coop<LV>(mu, (const uint8_t *)lds.w1buf, k, lds.ct, lds.c, nullptr);
+}
+
+// Masks, w and challenges of a round of at most CAND_TASKS tasks, whose
+// candidates (64 per task) then have a workgroup each: 49 us for one task of
+// level 3, 63 us in three launches (and their gaps).
+constexpr uint32_t CAND_TASKS = 8;
+template <int LV>
+__global__ void __launch_bounds__(64 * Lv<LV>::L) rd_cand_k(Ws ws, Group gr, int r) {
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
+  __shared__ __align__(16) CandLds<LV> lds;
+  const RoundState st = round_state(gr.cnt, gr.n, r);
+  const uint32_t s = blockIdx.x;
+  if (s >= st.n * st.m) return;
+  const uint32_t e = s / st.m, task = round_task(gr, r, e);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const WaveKeccak k(lds.kl[wave], lane);
+  dev_candidate<LV>(ws.rhop + (size_t)task * 64, (st.first + (s - e * st.m)) * L, ws.A + kix(ws, task) * K * L * A_POLY,
+                    ws.muw1 + (size_t)task * muw1_stride<LV>(), gr.y + (size_t)s * L * P<LV>::YB,
+                    gr.w + (size_t)s * K * N, k, lds);
+  if (wave != 0) return;
+  wave_sync();
+  if (lane < P<LV>::CT / 4) ((uint32_t *)(gr.ct + (size_t)s * CT_STRIDE))[lane] = lds.ct[lane];
+  store_c_coop(lds.c, gr.c + (size_t)s * N, k);
+}
+
+// The staged form's loop for the tasks of a list that are few enough for a
+// workgroup each: up to FEW_TRIES nonces, in order, until one passes.  A round in
+// four launches and a wait of the host took 83 us with a few tasks left, a nonce
+// here takes 50 (level 3; 1,000 tasks 3000 -> 2170 us).  Two wavefronts per SIMD:
+// with three dev_check spills (2,230 us; level 5 2,000 against 1,850).
+constexpr uint32_t FEW_TRIES = 64, FEW_STREAMS = WAVE_STATES;
+template <int LV>
+__global__ void __launch_bounds__(64 * Lv<LV>::L, 2) sg_few_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,
+                                                            uint32_t *next_active) {
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
+  __shared__ __align__(16) CandLds<LV> lds;
+  if (blockIdx.x >= nactive) return;
+  const uint32_t task = active[blockIdx.x];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const WaveKeccak k(lds.kl[wave], lane);
+  uint8_t *y = ws.y + (size_t)task * L * P<LV>::YB;
+  int32_t *w = ws.w + (size_t)task * K * N;
+  const uint32_t kappa = ws.kappa[task];
+  uint32_t tries = 0;
+  bool done;
+  do {
+    dev_candidate<LV>(ws.rhop + (size_t)task * 64, kappa + tries * L, ws.A + kix(ws, task) * K * L * A_POLY,
+                      ws.muw1 + (size_t)task * muw1_stride<LV>(), y, w, k, lds);
+    tries++;
+    if (wave == 0) {
+      wave_sync();
+      const bool ok = dev_check<LV>(lds.c, lds.ct, y, w, ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.ck, lane);
+      if (ok) l2g_bytes(lds.ck.sigbuf, P<LV>::SIG, sig + (size_t)task * P<LV>::SIG, lane, 64);
+      if (lane == 0) lds.ok = ok;
+    }
+    __syncthreads();
+    done = lds.ok;
+  } while (!done && tries < FEW_TRIES);
+  if (threadIdx.x == 0) {
+    atomicAdd(&ws.counters[1], tries);
+    if (!done) {
+      ws.kappa[task] = kappa + tries * L;
+      next_active[atomicAdd(&ws.counters[0], 1u)] = task;
+    }
+  }
+}
+
 }  // namespace dil
