@@ -218,8 +218,8 @@ int dil_verify_batch(dil_ctx *ctx, int level, const uint8_t *pk, const uint32_t 
 /* ---- Resident key tables (serving) ----
  * A key table keeps n_keys key rows of one level on the device together with
  * what Sign and Verify would otherwise recompute per call: A-hat = ExpandA(rho)
- * (Alg. 1-3), NTT(s1), NTT(s2), NTT(t0) (Alg. 2) when secret keys are given,
- * NTT(t1 2^d) and tr = H(pk) (Alg. 3) when public keys are given.  pk and sk
+ * (Alg. 1-3), s1, s2, t0 (Alg. 2) as int8 matrix tiles when secret keys are given,
+ * t1 as such a tile and tr = H(pk) (Alg. 3) when public keys are given.  pk and sk
  * are device arrays of n_keys rows (either may be NULL, not both; when both are
  * given row i of each must be one key pair).  The table owns copies of the rows
  * and may be used from any context on the same device, concurrently for

@@ -191,7 +191,9 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
   w.y = take(staged, cap * L * P<LV>::YB);
   w.w = (int32_t *)take(staged, cap * K * 1024);
-  w.hmask = (uint32_t *)take(form == WS_VERIFY, cap * K * 32);
+  // held no longer (hint bits), but counted: the largest batch that dil_verify_keyset_noalloc
+  // accepts follows from this layout
+  take(form == WS_VERIFY, cap * K * 32);
   w.flag = (int32_t *)take(form == WS_VERIFY, cap * 4);
   w.kappa = (uint32_t *)take(sign, cap * 4);
   w.active0 = (uint32_t *)take(sign, cap * 4);

@@ -28,7 +28,6 @@ struct Ws {
   int8_t *sec;       // [cap][sec_bytes] Sign: s1, s2, t0 as int8 tiles (toeplitz.h)
   uint8_t *y;        // [cap][L][YB]  mask, as squeezed
   int32_t *w;        // [cap][K][256]  w = A y as dev_compute_w stores it
-  uint32_t *hmask;   // [cap][K][8]   verify: hint bits
   uint32_t *kappa;   // [cap]
   int32_t *flag;     // [cap]
   uint32_t *active0, *active1;  // [cap] task lists

@@ -9,8 +9,9 @@
 //              written to global memory and read back inside the kernel);
 //   variant 1  unpacking merged into the NTT: the coefficients go from the
 //              staged key bytes straight into registers (unpadded transpose);
-//   variant 0  as 1 with the padded, bank-conflict-free transpose -- the code
-//              path of sg_secret_k, which the Sign setup runs.
+//   variant 0  as 1 with the padded, bank-conflict-free transpose.
+// Sign itself no longer transforms t0: its product with the challenge runs on
+// the matrix cores (toeplitz.h).
 // Every form writes NTT(t0) reduced to [0, q) in natural slot order
 // (t0_hat[task][i][j] = slot j of polynomial i), the same words for all four.
 #pragma once

@@ -279,7 +279,7 @@ class Context:
 
 
 class KeySet:
-    """Device-resident key table of one level (A-hat, NTT'd secrets, NTT(t1 2^d), tr kept on the GPU)."""
+    """Device-resident key table of one level (A-hat, secrets and t1 as matrix tiles, tr kept on the GPU)."""
 
     def __init__(self, ctx: Context, level: int, pk=None, sk=None, stream=None):
         self.lib = ctx.lib
