@@ -385,6 +385,16 @@ bool with_coop(uint32_t count, uint32_t max_rows, F f) {
 }
 #define DIL_ENGINE(e) std::remove_pointer_t<decltype(e)>
 
+// ExpandA of `count` rows
+template <int LV>
+void launch_expand_a(hipStream_t st, const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx, uint8_t *A,
+                     uint32_t count) {
+  const uint64_t streams = (uint64_t)count * Lv<LV>::K * Lv<LV>::L;
+  if (streams <= WAVE_STATES)
+    expand_a_wave_k<LV><<<(unsigned)streams, 64, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
+  else
+    expand_a_k<LV><<<blocks_for(streams, EA_WG), EA_WG, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
+}
 // Verify's challenges and last kernel: a state each, or a lane / a lane pair per task
 template <int LV>
 void launch_vf_prep(hipStream_t st, const uint8_t *sig, const Ws &ws, uint32_t count) {
@@ -415,9 +425,17 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
   Ws ws;
   int rc = ws_carve<LV>(ctx, st, count, WS_KEYGEN, false, ws);
   if (rc) return rc;
-  kg_seed_k<LV><<<blocks_for(count, 256), 256, 0, st>>>(seeds, pk, sk, ws, count);
-  const unsigned na = blocks_for((uint64_t)count * K * L, EA_WG), ns = blocks_for((uint64_t)count * (K + L), EA_WG);
-  kg_expand_k<LV><<<na + ns, EA_WG, 0, st>>>(pk, ws, count, na);
+  if (!with_coop(count, ROW_ALONE, [&](auto *e, uint32_t wgs) {
+        kg_seed_coop_k<LV, DIL_ENGINE(e)><<<wgs, 64, 0, st>>>(seeds, pk, sk, ws, count);
+      }))
+    kg_seed_k<LV><<<blocks_for(count, 256), 256, 0, st>>>(seeds, pk, sk, ws, count);
+  const uint64_t streams = (uint64_t)count * (K * L + K + L);
+  if (streams <= WAVE_STATES) {
+    kg_expand_wave_k<LV><<<(unsigned)streams, 64, 0, st>>>(pk, ws, count);
+  } else {
+    const unsigned na = blocks_for((uint64_t)count * K * L, EA_WG), ns = blocks_for((uint64_t)count * (K + L), EA_WG);
+    kg_expand_k<LV><<<na + ns, EA_WG, 0, st>>>(pk, ws, count, na);
+  }
   kg_main_k<LV><<<count, 64, 0, st>>>(ws, pk, sk, count);
   launch_tr<LV>(st, pk, sk + 64, P<LV>::SK, count);
   LAUNCHCHK(ctx);
@@ -485,7 +503,7 @@ int sign_setup(dil_ctx *ctx, Ws &ws, const uint8_t *sk, const uint32_t *key_idx,
   launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, err, st);
   if (!ks) {
     hipStream_t s1 = concurrent ? ctx->side[0] : st, s2 = concurrent ? ctx->side[1] : st;
-    expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, s1>>>(sk, P<LV>::SK, key_idx, ws.A, count);
+    launch_expand_a<LV>(s1, sk, P<LV>::SK, key_idx, ws.A, count);
     sg_secret_k<LV><<<count, 64, 0, s2>>>(sk, key_idx, ws, count);
   }
   if (concurrent) return join_side(ctx, st);
@@ -685,8 +703,7 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     // the hashes are few wavefronts in long chains: they take their places before ExpandA fills the SIMDs
     launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, ctx->dev_stats + 8, s);
     if (!ks)
-      expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, ctx->side[0]>>>(sk, P<LV>::SK, key_idx,
-                                                                                         ws.A, count);
+      launch_expand_a<LV>(ctx->side[0], sk, P<LV>::SK, key_idx, ws.A, count);
     if (!few) launch_mask<LV>(ws, group(0), 0, s);
     if (!ks) {
       sg_secret_k<LV><<<count, 64, 0, s>>>(sk, key_idx, ws, count);
@@ -854,8 +871,7 @@ int verify_impl(dil_ctx *ctx, const uint8_t *pk, const uint32_t *key_idx, const 
     hipStream_t s_hash = conc ? ctx->side[1] : s, s_ea = conc ? ctx->side[0] : s;
     launch_vf_hash<LV>(ctx, pk, key_idx, msg, msg_off, ws, count, ctx->dev_stats + 8, s_hash);
     if (!ks)
-      expand_a_k<LV><<<blocks_for((uint64_t)count * K * L, EA_WG), EA_WG, 0, s_ea>>>(pk, P<LV>::PK, key_idx, ws.A,
-                                                                                count);
+      launch_expand_a<LV>(s_ea, pk, P<LV>::PK, key_idx, ws.A, count);
     launch_vf_prep<LV>(s, sig, ws, count);
     if (conc) {
       int r2 = join_one(ctx, s, 0);
@@ -909,14 +925,13 @@ int keyset_build(dil_ctx *ctx, dil_keyset *ks, const uint8_t *pk, const uint8_t 
     ks->t1s = (int8_t *)take(n * TILE_BYTES);
     HIPCHK(ctx, hipMemcpyAsync(ks->pk, pk, n * PP::PK, hipMemcpyDeviceToDevice, st));
   }
-  unsigned nb = blocks_for(n * K * L, EA_WG);
   if (sk) {
-    expand_a_k<LV><<<nb, EA_WG, 0, st>>>(ks->sk, PP::SK, nullptr, ks->A, ks->nkeys);
+    launch_expand_a<LV>(st, ks->sk, PP::SK, nullptr, ks->A, ks->nkeys);
     Ws w{};
     w.sec = ks->sec;
     sg_secret_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->sk, nullptr, w, ks->nkeys);
   } else {
-    expand_a_k<LV><<<nb, EA_WG, 0, st>>>(ks->pk, PP::PK, nullptr, ks->A, ks->nkeys);
+    launch_expand_a<LV>(st, ks->pk, PP::PK, nullptr, ks->A, ks->nkeys);
   }
   if (pk) {
     ks_pk_k<LV><<<ks->nkeys, 64, 0, st>>>(ks->pk, ks->t1s, ks->nkeys);

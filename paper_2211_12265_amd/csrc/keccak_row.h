@@ -509,6 +509,128 @@ __global__ void __launch_bounds__(64) expand_mask_coop_k(Ws ws, const uint32_t *
   dev_expand_mask_coop<LV>(ws.rhop + (size_t)task * 64, ws.kappa[task] + i, k,
                            ws.y + ((size_t)task * ML + i) * P<LV>::YB);
 }
+
+// ---- KeyGen's seeds and the expansions of few keys, a wavefront per stream ----
+// ExpandA of one polynomial: at most 2,048 of them leave a lane's five
+// permutations (46 us one after another) alone on the chip.  The candidates of a
+// block are tested on 56 lanes and placed by a ballot.
+struct ExpandLds {
+  uint32_t kl[KECCAK_LDS], blk[RATE128 / 4 + 1];
+  uint8_t poly[A_POLY];
+};
+__device__ __forceinline__ void dev_expand_a_wave(const uint32_t *rho, uint32_t ij, uint8_t *out, const WaveKeccak &k,
+                                                  ExpandLds &lds) {
+  uint32_t a[2];
+#pragma unroll
+  for (int y = 0; y < 2; y++) {
+    const int w = k.word(y);
+    a[y] = w < 4 ? rho[k.half_word(y)] : w == 4 && !k.h ? ij | 0x1Fu << 16 : 0u;
+    if (w == RATE128 / 8 - 1 && k.h) a[y] ^= 0x80u << 24;
+  }
+  const bool cand = k.l < EA_CAND;
+  const int wi = cand ? (3 * k.l) >> 2 : 0;
+  const uint32_t sh = cand ? 8u * (uint32_t)((3 * k.l) & 3) : 0u;
+  for (int ctr = 0; ctr < N;) {
+    keccak_f_coop(a, k);
+    if (k.own) {
+      lds.blk[k.half_word(0)] = a[0];
+      if (k.row == 0 && k.word(1) < RATE128 / 8) lds.blk[k.half_word(1)] = a[1];
+    }
+    wave_sync();
+    const uint32_t v = __builtin_amdgcn_alignbit(lds.blk[wi + 1], lds.blk[wi], sh) & 0x7FFFFFu;
+    const bool ok = cand && v < (uint32_t)Q;
+    const uint64_t m = __ballot(ok);
+    const int pos =
+        ctr + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (ok && pos < N) {
+      lds.poly[3 * pos] = (uint8_t)v;
+      lds.poly[3 * pos + 1] = (uint8_t)(v >> 8);
+      lds.poly[3 * pos + 2] = (uint8_t)(v >> 16);
+    }
+    ctr += (int)__popcll(m);
+    wave_sync();
+  }
+#pragma unroll
+  for (int q = 0; q < A_POLY / 256; q++) ((uint32_t *)out)[64 * q + k.l] = ((const uint32_t *)lds.poly)[64 * q + k.l];
+}
+// as expand_a_k
+template <int LV>
+__global__ void __launch_bounds__(64) expand_a_wave_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
+                                                      uint8_t *A, uint32_t count) {
+  constexpr uint32_t KL = Lv<LV>::K * Lv<LV>::L;
+  __shared__ __align__(16) ExpandLds lds;
+  const uint32_t task = blockIdx.x / KL, ij = blockIdx.x % KL;
+  if (task >= count) return;
+  const WaveKeccak k(lds.kl, threadIdx.x);
+  const size_t key = key_idx ? key_idx[task] : task;
+  dev_expand_a_wave((const uint32_t *)(rho_src + key * rho_stride), ij % Lv<LV>::L | ij / Lv<LV>::L << 8,
+                    A + (size_t)blockIdx.x * A_POLY, k, lds);
+}
+// as kg_expand_k, ExpandS's streams after ExpandA's
+template <int LV>
+__global__ void __launch_bounds__(64) kg_expand_wave_k(const uint8_t *pk, Ws ws, uint32_t count) {
+  constexpr uint32_t K = Lv<LV>::K, L = Lv<LV>::L, KL = K * L;
+  __shared__ __align__(16) ExpandLds lds;
+  const WaveKeccak k(lds.kl, threadIdx.x);
+  if (blockIdx.x < count * KL) {
+    const uint32_t task = blockIdx.x / KL, ij = blockIdx.x % KL;
+    dev_expand_a_wave((const uint32_t *)(pk + (size_t)task * P<LV>::PK), ij % L | ij / L << 8,
+                      ws.A + (size_t)blockIdx.x * A_POLY, k, lds);
+    return;
+  }
+  const uint32_t st = blockIdx.x - count * KL;
+  if (st >= count * (K + L)) return;
+  const uint32_t *rw = (const uint32_t *)(ws.rhop + (size_t)(st / (K + L)) * 64);
+  uint32_t *o = (uint32_t *)(ws.s12 + (size_t)st * S_POLY);
+  uint32_t a[2];
+#pragma unroll
+  for (int y = 0; y < 2; y++) {
+    const int w = k.word(y);
+    a[y] = w < 8 ? rw[k.half_word(y)] : w == 8 && !k.h ? st % (K + L) | 0x1Fu << 16 : 0u;
+    if (w == RATE256 / 8 - 1 && k.h) a[y] = 0x80u << 24;
+  }
+  int got = 0;
+  for (int blk = 0; blk < S_BLOCKS && (blk < 2 || got < N); blk++) {
+    keccak_f_coop(a, k);
+    const bool mine = k.own && k.word(0) < RATE256 / 8;
+    if (mine) o[blk * (RATE256 / 4) + k.half_word(0)] = a[0];
+    int c = mine ? (int)__popc(s_accepted<Lv<LV>::ETA>(a[0])) : 0;  // at most 8 a lane
+#pragma unroll
+    for (int bit = 0; bit < 4; bit++) got += (int)__popcll(__ballot((c >> bit) & 1)) << bit;
+  }
+}
+// as kg_seed_k
+template <int LV, class E>
+__global__ void __launch_bounds__(64) kg_seed_coop_k(const uint8_t *seeds, uint8_t *pk, uint8_t *sk, Ws ws,
+                                                     uint32_t count) {
+  DIL_COOP_TASK(E)
+  const uint8_t *sd = seeds + 32 * (size_t)t;
+  uint32_t a[E::NR];
+#pragma unroll
+  for (int y = 0; y < E::NR; y++) {
+    const int w = k.word(y);
+    a[y] = w < 4 ? (uint32_t)load_le_bytes(sd + 4 * k.half_word(y), 4) : 0u;
+    if (w == 4 && !k.h)
+      a[y] = Lv<LV>::MLDSA ? (uint32_t)Lv<LV>::K | (uint32_t)Lv<LV>::L << 8 | 0x1Fu << 16 : 0x1Fu;
+    if (w == RATE256 / 8 - 1 && k.h) a[y] = 0x80u << 24;
+  }
+  keccak_f_coop(a, k);
+  uint32_t *pkw = (uint32_t *)(pk + (size_t)t * P<LV>::PK), *skw = (uint32_t *)(sk + (size_t)t * P<LV>::SK);
+  uint32_t *rw = (uint32_t *)(ws.rhop + (size_t)t * 64);
+#pragma unroll
+  for (int y = 0; y < E::NA; y++) {
+    const int i = k.half_word(y);
+    if (!k.own || i >= 32) continue;
+    if (i < 8) {
+      pkw[i] = a[y];
+      skw[i] = a[y];
+    } else if (i < 24) {
+      rw[i - 8] = a[y];
+    } else {
+      skw[i - 16] = a[y];  // K at sk bytes 32..63
+    }
+  }
+}
 #undef DIL_COOP_TASK
 
 }  // namespace dil
