@@ -1515,7 +1515,10 @@ int dil_expand_a_batch(dil_ctx *ctx, const uint8_t *seeds34, int32_t *out, uint6
   if (!seeds34 || !out) return fail(ctx, DIL_EINVAL, "null buffer");
   if (count > (uint64_t)UINT32_MAX) return fail(ctx, DIL_EINVAL, "count above 2^32 - 1");
   hipSetDevice(ctx->device);
-  expand_a_seed_k<<<blocks_for(count, EA_WG), EA_WG, 0, (hipStream_t)stream>>>(seeds34, out, count);
+  if (count <= WAVE_STATES)
+    expand_a_seed_wave_k<<<(unsigned)count, 64, 0, (hipStream_t)stream>>>(seeds34, out, (uint32_t)count);
+  else
+    expand_a_seed_k<<<blocks_for(count, EA_WG), EA_WG, 0, (hipStream_t)stream>>>(seeds34, out, count);
   LAUNCHCHK(ctx);
   return DIL_OK;
 }

@@ -516,15 +516,18 @@ __global__ void __launch_bounds__(64) expand_mask_coop_k(Ws ws, const uint32_t *
 // block are tested on 56 lanes and placed by a ballot.
 struct ExpandLds {
   uint32_t kl[KECCAK_LDS], blk[RATE128 / 4 + 1];
-  uint8_t poly[A_POLY];
+  __align__(4) uint8_t poly[4 * N];
 };
-__device__ __forceinline__ void dev_expand_a_wave(const uint32_t *rho, uint32_t ij, uint8_t *out, const WaveKeccak &k,
+// rho(i): word i of the seed; out: A_POLY bytes, or 256 words (not PACKED)
+template <bool PACKED, class R>
+__device__ __forceinline__ void dev_expand_a_wave(R rho, uint32_t ij, uint8_t *out, const WaveKeccak &k,
                                                   ExpandLds &lds) {
+  constexpr int POLY = PACKED ? A_POLY : 4 * N;
   uint32_t a[2];
 #pragma unroll
   for (int y = 0; y < 2; y++) {
     const int w = k.word(y);
-    a[y] = w < 4 ? rho[k.half_word(y)] : w == 4 && !k.h ? ij | 0x1Fu << 16 : 0u;
+    a[y] = w < 4 ? rho(k.half_word(y)) : w == 4 && !k.h ? ij | 0x1Fu << 16 : 0u;
     if (w == RATE128 / 8 - 1 && k.h) a[y] ^= 0x80u << 24;
   }
   const bool cand = k.l < EA_CAND;
@@ -543,15 +546,19 @@ __device__ __forceinline__ void dev_expand_a_wave(const uint32_t *rho, uint32_t 
     const int pos =
         ctr + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     if (ok && pos < N) {
-      lds.poly[3 * pos] = (uint8_t)v;
-      lds.poly[3 * pos + 1] = (uint8_t)(v >> 8);
-      lds.poly[3 * pos + 2] = (uint8_t)(v >> 16);
+      if constexpr (PACKED) {
+        lds.poly[3 * pos] = (uint8_t)v;
+        lds.poly[3 * pos + 1] = (uint8_t)(v >> 8);
+        lds.poly[3 * pos + 2] = (uint8_t)(v >> 16);
+      } else {
+        ((uint32_t *)lds.poly)[pos] = v;
+      }
     }
     ctr += (int)__popcll(m);
     wave_sync();
   }
 #pragma unroll
-  for (int q = 0; q < A_POLY / 256; q++) ((uint32_t *)out)[64 * q + k.l] = ((const uint32_t *)lds.poly)[64 * q + k.l];
+  for (int q = 0; q < POLY / 256; q++) ((uint32_t *)out)[64 * q + k.l] = ((const uint32_t *)lds.poly)[64 * q + k.l];
 }
 // as expand_a_k
 template <int LV>
@@ -563,8 +570,18 @@ __global__ void __launch_bounds__(64) expand_a_wave_k(const uint8_t *rho_src, si
   if (task >= count) return;
   const WaveKeccak k(lds.kl, threadIdx.x);
   const size_t key = key_idx ? key_idx[task] : task;
-  dev_expand_a_wave((const uint32_t *)(rho_src + key * rho_stride), ij % Lv<LV>::L | ij / Lv<LV>::L << 8,
+  const uint32_t *rho = (const uint32_t *)(rho_src + key * rho_stride);
+  dev_expand_a_wave<true>([&](int i) { return rho[i]; }, ij % Lv<LV>::L | ij / Lv<LV>::L << 8,
                     A + (size_t)blockIdx.x * A_POLY, k, lds);
+}
+// as expand_a_seed_k
+__global__ void __launch_bounds__(64) expand_a_seed_wave_k(const uint8_t *seeds, int32_t *out, uint32_t count) {
+  __shared__ __align__(16) ExpandLds lds;
+  if (blockIdx.x >= count) return;
+  const WaveKeccak k(lds.kl, threadIdx.x);
+  const uint8_t *sd = seeds + 34 * (size_t)blockIdx.x;
+  dev_expand_a_wave<false>([&](int i) { return (uint32_t)load_le_bytes(sd + 4 * i, 4); },
+                           (uint32_t)sd[32] | ((uint32_t)sd[33] << 8), (uint8_t *)(out + (size_t)blockIdx.x * N), k, lds);
 }
 // as kg_expand_k, ExpandS's streams after ExpandA's
 template <int LV>
@@ -574,7 +591,8 @@ __global__ void __launch_bounds__(64) kg_expand_wave_k(const uint8_t *pk, Ws ws,
   const WaveKeccak k(lds.kl, threadIdx.x);
   if (blockIdx.x < count * KL) {
     const uint32_t task = blockIdx.x / KL, ij = blockIdx.x % KL;
-    dev_expand_a_wave((const uint32_t *)(pk + (size_t)task * P<LV>::PK), ij % L | ij / L << 8,
+    const uint32_t *rho = (const uint32_t *)(pk + (size_t)task * P<LV>::PK);
+    dev_expand_a_wave<true>([&](int i) { return rho[i]; }, ij % L | ij / L << 8,
                       ws.A + (size_t)blockIdx.x * A_POLY, k, lds);
     return;
   }

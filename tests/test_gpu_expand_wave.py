@@ -49,3 +49,18 @@ def test_counts_where_the_expansions_change(level, count):
 def test_third_block(level):
     _run(level, np.stack([np.frombuffer(struct.pack("<Q", i) + bytes(24), dtype=np.uint8)
                           for i in THIRD_BLOCK[level]]))
+
+
+@pytest.mark.parametrize("count", [1, 3, 2048, 2049])
+def test_expand_a_primitive(count):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2211_12265_amd import dilithium as dl
+    seeds = workload.random_bytes("test/expand_a_wave", count, (count, 34))
+    want = oracle.expand_a_polys(seeds)
+    out = torch.zeros((count, 256), dtype=torch.int32, device="cuda")
+    ctx = dl.Context(0)
+    ctx.expand_a(torch.from_numpy(seeds).cuda(), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), want)
+    ctx.close()
