@@ -390,7 +390,7 @@ template <int LV>
 void launch_expand_a(hipStream_t st, const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx, uint8_t *A,
                      uint32_t count) {
   const uint64_t streams = (uint64_t)count * Lv<LV>::K * Lv<LV>::L;
-  if (streams <= WAVE_STATES)
+  if (streams <= EXPAND_BESIDE)
     expand_a_wave_k<LV><<<(unsigned)streams, 64, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
   else
     expand_a_k<LV><<<blocks_for(streams, EA_WG), EA_WG, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
@@ -430,7 +430,7 @@ int keygen_impl(dil_ctx *ctx, const uint8_t *seeds, uint8_t *pk, uint8_t *sk, ui
       }))
     kg_seed_k<LV><<<blocks_for(count, 256), 256, 0, st>>>(seeds, pk, sk, ws, count);
   const uint64_t streams = (uint64_t)count * (K * L + K + L);
-  if (streams <= WAVE_STATES) {
+  if (streams <= EXPAND_ALONE) {
     kg_expand_wave_k<LV><<<(unsigned)streams, 64, 0, st>>>(pk, ws, count);
   } else {
     const unsigned na = blocks_for((uint64_t)count * K * L, EA_WG), ns = blocks_for((uint64_t)count * (K + L), EA_WG);
@@ -1515,7 +1515,7 @@ int dil_expand_a_batch(dil_ctx *ctx, const uint8_t *seeds34, int32_t *out, uint6
   if (!seeds34 || !out) return fail(ctx, DIL_EINVAL, "null buffer");
   if (count > (uint64_t)UINT32_MAX) return fail(ctx, DIL_EINVAL, "count above 2^32 - 1");
   hipSetDevice(ctx->device);
-  if (count <= WAVE_STATES)
+  if (count <= EXPAND_ALONE)
     expand_a_seed_wave_k<<<(unsigned)count, 64, 0, (hipStream_t)stream>>>(seeds34, out, (uint32_t)count);
   else
     expand_a_seed_k<<<blocks_for(count, EA_WG), EA_WG, 0, (hipStream_t)stream>>>(seeds34, out, count);

@@ -511,9 +511,13 @@ __global__ void __launch_bounds__(64) expand_mask_coop_k(Ws ws, const uint32_t *
 }
 
 // ---- KeyGen's seeds and the expansions of few keys, a wavefront per stream ----
-// ExpandA of one polynomial: at most 2,048 of them leave a lane's five
-// permutations (46 us one after another) alone on the chip.  The candidates of a
-// block are tested on 56 lanes and placed by a ballot.
+// ExpandA of one polynomial: few of them leave a lane's five permutations (46 us
+// one after another) alone on the chip.  The candidates of a block are tested on
+// 56 lanes and placed by a ballot.  2,048 / 4,096 / 8,192 polynomials take 20 / 28 /
+// 46 us this way, 59 each on lanes; beside the hash chains of Sign and Verify, which
+// it delays above 4,096 (273 level-3 tasks of up to 4 KB, 8,190 polynomials: Verify
+// 178 -> 183 us; 100 of 32 bytes, 3,000: 127 -> 98), the line lies there.
+constexpr uint32_t EXPAND_BESIDE = 4096, EXPAND_ALONE = 8192;
 struct ExpandLds {
   uint32_t kl[KECCAK_LDS], blk[RATE128 / 4 + 1];
   __align__(4) uint8_t poly[4 * N];

@@ -1,4 +1,5 @@
-"""ExpandA and ExpandS on a wavefront per stream (at most 2048 streams) and KeyGen's seeds on the wide forms,
+"""ExpandA and ExpandS on a wavefront per stream (at most 4096 polynomials beside
+hash chains, 8192 streams alone) and KeyGen's seeds on the wide forms,
 at the counts on both sides of the line, the smallest call, and seeds whose ExpandS streams need a third
 block (found by search).  KeyGen, Sign and Verify equal the oracle; the last two expand A from their own rows."""
 import struct
@@ -40,7 +41,9 @@ def _run(level, seeds):
 
 
 @pytest.mark.parametrize("level,count", [(2, 1), (65, 1), (87, 1), (2, 85), (44, 86), (44, 128), (2, 129), (3, 49),
-                                         (65, 50), (3, 68), (65, 69), (5, 28), (87, 29), (87, 36), (5, 37)])
+                                         (65, 50), (3, 68), (65, 69), (5, 28), (87, 29), (87, 36), (5, 37),
+                                         (2, 256), (44, 257), (3, 136), (65, 137), (2, 341), (44, 342), (3, 199),
+                                         (65, 200), (5, 73), (87, 74), (5, 115), (87, 116)])
 def test_counts_where_the_expansions_change(level, count):
     _run(level, workload.keygen_seeds(count, seed=1100 + level))
 
@@ -51,7 +54,7 @@ def test_third_block(level):
                           for i in THIRD_BLOCK[level]]))
 
 
-@pytest.mark.parametrize("count", [1, 3, 2048, 2049])
+@pytest.mark.parametrize("count", [1, 3, 2048, 2049, 8192, 8193])
 def test_expand_a_primitive(count):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
