@@ -791,9 +791,6 @@ def main():
         kname = kbase + " (persistent Sign rejection-loop kernel)"
         sched_str = args.schedule if not tuning else \
             f"{tuning['best']['waves']},{tuning['best']['hmax']},{tuning['best']['grid']}"
-        if sched_str == "4,0,0":
-            kbase = f"rd_*_k<{level}>"
-            kname = kbase + " (Sign in rounds: masks, w, challenges and checks of every round)"
         rec = stored_traffic(kbase, level, n, args.msg_dist, sched_str)
         if rec:
             kextra["traffic_detail"] = {"fetch_bytes": rec["fetch_bytes"], "write_bytes": rec["write_bytes"],

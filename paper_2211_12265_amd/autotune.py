@@ -14,10 +14,7 @@ wastes work on iterations after the first valid one; large hmax wastes none
 but leaves the GPU underfilled for small batches.  The best point depends on
 the batch size, the level and the GPU, so it is measured: every candidate runs
 the caller's own batch (Sign is deterministic, so every candidate produces the
-same signatures) and the fastest median wins.  The automatic form, Sign in
-rounds (waves 4, hmax 0, grid 0), is one of the candidates; for 10,000 tasks it
-is the fastest at every level (1080 us against 1250 with the best loop kernel
-schedule at level 2, 1885 against 2420 at level 5).
+same signatures) and the fastest median wins.
 """
 from __future__ import annotations
 
@@ -101,8 +98,6 @@ def tune_sign(ctx, level: int, run, resident_groups: Optional[int] = None, reps:
             ctx.set_param("persist.waves", w)
             res = resident_groups or ctx.persist_capacity(level)[0]
             cands += [(w, h, grid) for h, grid in candidates(level, count, res, w)]
-        if 4 in waves:
-            cands.append((4, 0, 0))
     best_ms = {}
     stats = {}
     for _ in range(max(1, rounds)):
