@@ -627,7 +627,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-tune", action="store_true", help="skip the schedule autotuner")
     ap.add_argument("--tune", action="store_true",
-                    help="re-run the autotuner even if a schedule is recorded for this workload")
+                    help="time the loop kernel with the schedule of an autotuner run instead of Sign in rounds")
     ap.add_argument("--tune-reps", type=int, default=3)
     ap.add_argument("--tune-rounds", type=int, default=1)
     ap.add_argument("--record-schedule", default="",
@@ -733,17 +733,17 @@ def main():
     tuning = None
     schedule_src = None
     from paper_2211_12265_amd import autotune
-    cached = autotune.cached_schedule(level, n, args.msg_dist)
     if args.schedule:
         w, h, g = (int(x) for x in args.schedule.split(","))
         autotune.apply_schedule(ctx, {"waves": w, "hmax": h, "grid": g})
         args.waves = w
         schedule_src = "command line"
-    elif args.mode == "persistent" and cached and not args.tune and not args.no_tune and not args.waves:
-        autotune.apply_schedule(ctx, cached)
-        args.waves = cached["waves"]
-        args.schedule = f"{cached['waves']},{cached['hmax']},{cached['grid']}"
-        schedule_src = "autotuner (recorded)"
+    elif args.mode == "persistent" and not args.tune and not args.no_tune and not args.waves:
+        # Sign in rounds, what a persistent context does with no schedule set; the recorded
+        # schedules are the loop kernel's best
+        args.waves = 4
+        args.schedule = "4,0,0"
+        schedule_src = "automatic"
     elif args.mode == "persistent" and not args.no_tune:
         # the ML-DSA levels are built in the four-wavefront shape only
         tuning = autotune.tune_sign(ctx, level, lambda: ctx.sign(level, sk, g_msg, g_off, sig), count=n,
@@ -791,6 +791,9 @@ def main():
         kname = kbase + " (persistent Sign rejection-loop kernel)"
         sched_str = args.schedule if not tuning else \
             f"{tuning['best']['waves']},{tuning['best']['hmax']},{tuning['best']['grid']}"
+        if sched_str == "4,0,0":
+            kbase = f"rd_*_k<{level}>"
+            kname = kbase + " (Sign in rounds: masks, w, challenges and checks of every round)"
         rec = stored_traffic(kbase, level, n, args.msg_dist, sched_str)
         if rec:
             kextra["traffic_detail"] = {"fetch_bytes": rec["fetch_bytes"], "write_bytes": rec["write_bytes"],
