@@ -385,13 +385,23 @@ bool with_coop(uint32_t count, uint32_t max_rows, F f) {
 }
 #define DIL_ENGINE(e) std::remove_pointer_t<decltype(e)>
 
-// ExpandA of `count` rows
+// ExpandA of `count` rows.  Beside the masks of Sign (beside_masks), a launch that
+// fits the SIMDs at once (two to five wavefronts on each) takes 256-lane
+// workgroups, which put one wavefront on every SIMD of a CU: one-wavefront
+// workgroups among the masks' leave some SIMDs with twice the work of others
+// (Sign of 10,000 at level 2 1095 -> 1052 us, at level 3, 32 bytes, 1751 -> 1726).
+// Larger launches refill a SIMD at every wavefront's end, for which small
+// workgroups are better (level 5 1868 against 1886 us); smaller ones see no
+// difference (5,000 at ML-DSA-44 733 and 737 us).
+constexpr uint64_t EA_EVEN_MIN = 2 * 65536, EA_EVEN_MAX = 5 * 65536;
 template <int LV>
 void launch_expand_a(hipStream_t st, const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx, uint8_t *A,
-                     uint32_t count) {
+                     uint32_t count, bool beside_masks = false) {
   const uint64_t streams = (uint64_t)count * Lv<LV>::K * Lv<LV>::L;
   if (streams <= EXPAND_BESIDE)
     expand_a_wave_k<LV><<<(unsigned)streams, 64, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
+  else if (beside_masks && streams > EA_EVEN_MIN && streams <= EA_EVEN_MAX)
+    expand_a_k<LV, 256><<<blocks_for(streams, 256), 256, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
   else
     expand_a_k<LV><<<blocks_for(streams, EA_WG), EA_WG, 0, st>>>(rho_src, rho_stride, key_idx, A, count);
 }
@@ -703,7 +713,7 @@ int sign_rounds(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
     // the hashes are few wavefronts in long chains: they take their places before ExpandA fills the SIMDs
     launch_prep<LV>(ctx, sk, key_idx, msg, msg_off, rnd, ws, count, ctx->dev_stats + 8, s);
     if (!ks)
-      launch_expand_a<LV>(ctx->side[0], sk, P<LV>::SK, key_idx, ws.A, count);
+      launch_expand_a<LV>(ctx->side[0], sk, P<LV>::SK, key_idx, ws.A, count, true);
     if (!few) launch_mask<LV>(ws, group(0), 0, s);
     if (!ks) {
       sg_secret_k<LV><<<count, 64, 0, s>>>(sk, key_idx, ws, count);

@@ -128,9 +128,4 @@ __device__ __forceinline__ int32_t mont_mul(int32_t a, int32_t b) { return mont_
 // canonical representative in [0, q) of x in (-q, q): as unsigned words the
 // smaller of x and x + q
 __device__ __forceinline__ int32_t canon(int32_t x) { return (int32_t)min((uint32_t)x, (uint32_t)(x + Q)); }
-// canonical representative of x in [-q, 2q)
-__device__ __forceinline__ int32_t canon_near(int32_t x) {
-  const uint32_t v = (uint32_t)canon(x);
-  return (int32_t)min(v, v - (uint32_t)Q);
-}
 }  // namespace dil

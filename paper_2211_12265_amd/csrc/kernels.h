@@ -234,13 +234,14 @@ __device__ __forceinline__ void expand_a_squeeze_wave(uint32_t s[50], uint8_t *o
   }
 }
 
-// ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk)
-template <int LV>
+// ExpandA: one lane per (task, i, j); rho read from rows of `rho_src` (pk or sk).
+// WG: lanes per workgroup; rows: EA_ROWS * EA_ROW words per wavefront.
+template <int LV, int WG>
 __device__ __forceinline__ void dev_expand_a(uint32_t block, const uint8_t *rho_src, size_t rho_stride,
                                              const uint32_t *key_idx, uint8_t *A, uint32_t count, uint32_t *rows) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
-  const int lane = threadIdx.x;
-  const uint64_t st = (uint64_t)block * EA_WG + lane;
+  const int lane = threadIdx.x & 63;
+  const uint64_t st = (uint64_t)block * WG + threadIdx.x;
   const bool valid = st < (uint64_t)count * K * L;
   const uint64_t sl = valid ? st : 0;
   uint32_t task = (uint32_t)(sl / (K * L));
@@ -250,13 +251,14 @@ __device__ __forceinline__ void dev_expand_a(uint32_t block, const uint8_t *rho_
   const uint64_t *rho = (const uint64_t *)(rho_src + key * rho_stride);
   uint32_t s[50];
   absorb_seed34(s, [&](int pos) { return rho[pos >> 3]; }, (uint32_t)j | ((uint32_t)i << 8));
-  expand_a_squeeze_wave<true>(s, A + (size_t)(st - lane) * A_POLY, rows, lane, valid);
+  expand_a_squeeze_wave<true>(s, A + (size_t)(st - lane) * A_POLY, rows + (threadIdx.x >> 6) * EA_ROWS * EA_ROW, lane,
+                              valid);
 }
-template <int LV>
-__global__ void __launch_bounds__(EA_WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
+template <int LV, int WG = EA_WG>
+__global__ void __launch_bounds__(WG) expand_a_k(const uint8_t *rho_src, size_t rho_stride, const uint32_t *key_idx,
                                                   uint8_t *A, uint32_t count) {
-  __shared__ uint32_t rows[EA_ROWS * EA_ROW];
-  dev_expand_a<LV>(blockIdx.x, rho_src, rho_stride, key_idx, A, count, rows);
+  __shared__ uint32_t rows[WG / 64 * EA_ROWS * EA_ROW];
+  dev_expand_a<LV, WG>(blockIdx.x, rho_src, rho_stride, key_idx, A, count, rows);
 }
 
 // KeyGen's ExpandA and ExpandS, which need nothing of each other, in one launch:
@@ -267,7 +269,7 @@ __global__ void __launch_bounds__(EA_WG) kg_expand_k(const uint8_t *pk, Ws ws, u
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   __shared__ uint32_t rows[EA_ROWS * EA_ROW];
   if (blockIdx.x < nblk_a) {
-    dev_expand_a<LV>(blockIdx.x, pk, P<LV>::PK, nullptr, ws.A, count, rows);
+    dev_expand_a<LV, EA_WG>(blockIdx.x, pk, P<LV>::PK, nullptr, ws.A, count, rows);
     return;
   }
   const uint64_t st = (uint64_t)(blockIdx.x - nblk_a) * EA_WG + threadIdx.x;

@@ -25,12 +25,6 @@ __device__ __forceinline__ void decompose(int32_t r, int32_t &r1, int32_t &r0) {
   r1 = (int32_t)a1;
   r0 = a0;
 }
-template <int LV>
-__device__ __forceinline__ int32_t highbits(int32_t r) {
-  int32_t r1, r0;
-  decompose<LV>(r, r1, r0);
-  return r1;
-}
 // A-hat as ExpandA squeezes it: 24 bits per coefficient, of which bit 23 is not
 // part of the value.  768 instead of 1024 bytes per polynomial; the kernels that
 // read A-hat once per task wait for these bytes (10,000 tasks of level 5: 430
@@ -90,10 +84,6 @@ __device__ __forceinline__ int32_t use_hint(int32_t h, int32_t r) {
 __device__ __forceinline__ void power2round(int32_t r, int32_t &r1, int32_t &r0) {
   r1 = (r + (1 << (D - 1)) - 1) >> D;
   r0 = r - (r1 << D);
-}
-// ||x||_inf >= B for canonical x (B < q/2): centred value c has |c| >= B iff B <= x <= q - B
-__device__ __forceinline__ bool norm_ge(int32_t x, int32_t B) {
-  return (uint32_t)(x - B) <= (uint32_t)(Q - 2 * B);
 }
 // centred representative of a canonical value
 __device__ __forceinline__ int32_t centred(int32_t x) { return x > (Q - 1) / 2 ? x - Q : x; }

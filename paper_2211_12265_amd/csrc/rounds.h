@@ -20,7 +20,7 @@
 // call, loop kernel / rounds: 10,000 tasks at level 2 1465 / 1199 us, at level 5
 // (32 to 4096-byte messages) 2844 / 2031 us; 2,503 hedged ML-DSA-65 1328 / 911
 // us; 613 tasks on resident level-2 keys 834 / 460 us, one on a level-3 key
-// 271 / 126 us.  With the kernels as they are now the rounds take 1085, 1870,
+// 271 / 126 us.  With the kernels as they are now the rounds take 1052, 1870,
 // 810, 340 and 87 us.
 #pragma once
 #include <algorithm>
