@@ -622,7 +622,7 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A
     for (int r = 0; r < 16; r++) {
       int32_t r0;
       decompose<LV>(canon(x[r]), w1[r], r0);
-      x[r] = pack_low<LV>(w1[r], r0);
+      x[r] = pack_low(w1[r], r0);
     }
     store_slots(x, w_out + i * N, t);
     uint32_t v[16];
@@ -746,8 +746,9 @@ __device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctild
       if (hz) load_mask<PP::ZBITS, G1>(yv, y + p * PP::YB, t);
       if (hr) load_slots(wv, w + p * N, t);
     }
-    // |z| < gamma1 - beta and |r0| < gamma2 - beta, as offset maxima
-    uint32_t zm = 0, rm = 0;
+    // |z| < gamma1 - beta, as an offset maximum, and |r0| < gamma2 - beta from the extremes of w - c s2
+    uint32_t zm = 0;
+    int32_t wmax = 0, wmin = 0;
     auto half = [&](auto I0c) {
       constexpr int I0 = decltype(I0c)::value;
       v4i acc[8];
@@ -762,8 +763,9 @@ __device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctild
       if (hr) {
 #pragma unroll
         for (int r = 0; r < 8; r++) {
-          wv[I0 + r] -= 2 * acc[r][1];  // 2 LowBits(w - c s2) + [HighBits != 0], if the check passes
-          rm = max(rm, (uint32_t)((wv[I0 + r] >> 1) + (G2 - BETA - 1)));
+          wv[I0 + r] -= acc[r][1] * (1 << LOW_SHIFT);  // high bits of w, low part minus c s2
+          wmax = max(wmax, wv[I0 + r]);
+          wmin = min(wmin, wv[I0 + r]);
           ct0[I0 + r] = acc[r][2] + 64 * acc[r][3];
         }
       }
@@ -771,7 +773,18 @@ __device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctild
     half(std::integral_constant<int, 0>{});
     __builtin_amdgcn_sched_barrier(0);  // or both halves' reads are hoisted and their registers held at once
     half(std::integral_constant<int, 8>{});
-    if (wave_any(zm > 2u * (G1 - BETA - 1) || rm > 2u * (G2 - BETA - 1))) return false;
+    if (wave_any(zm > 2u * (G1 - BETA - 1))) return false;
+    if (wave_any(low_fails<G2, BETA>(wmax) || low_fails<G2, BETA>(wmin))) {
+      if (!wave_any(low_beyond<G2, BETA>(wmax) || low_beyond<G2, BETA>(wmin))) return false;
+      // a key row with s2 beyond eta (lowbits.h)
+      bool fails = false;
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        wv[r] = low_carry<G2, PP::M_HB>(wv[r]);
+        fails |= low_fails<G2, BETA>(wv[r]);
+      }
+      if (wave_any(hr && fails)) return false;
+    }
     if (T + 1 < sec_tiles<LV>()) toep_load(s, sec + (T + 1) * TILE_BYTES, lane);
     bool bad = false;
     if (hr) {
@@ -779,7 +792,7 @@ __device__ __forceinline__ bool dev_check(const int8_t *c, const uint32_t *ctild
 #pragma unroll
       for (int r = 0; r < 16; r++) {
         bad |= (uint32_t)(ct0[r] + (G2 - 1)) > 2u * (G2 - 1);
-        const bool h = hint_of<LV>((wv[r] >> 1) + ct0[r], wv[r] & 1);
+        const bool h = hint_of<G2>(low_part(wv[r]) + ct0[r], low_high(wv[r]));
         const uint64_t m = __ballot(h);
         const uint32_t m16 = (uint32_t)(m >> (16 * g)) & 0xFFFFu;
         if (t == 0) lds.hmask[p][r] = (uint16_t)m16;
@@ -875,9 +888,11 @@ __global__ void __launch_bounds__(64) sg_chal_k(Ws ws, const uint32_t *active, u
   store_c_row(c, ws.cpoly + (size_t)task * N);
 }
 
-// checks; accept -> signature row of the task, reject -> kappa += l and next round
+// checks; accept -> signature row of the task, reject -> kappa += l and next round.
+// Left alone, the compiler adds AGPRs for dev_check's accumulators (174 registers at
+// level 2); in 126 / 128 / 144 nothing spills.
 template <int LV>
-__global__ void __launch_bounds__(64) sg_check_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,
+__global__ void __launch_bounds__(64, Lv<LV>::K > 6 ? 2 : 3) sg_check_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,
                                                  uint32_t *next_active) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   __shared__ __align__(16) CheckLds<LV> lds;

@@ -3,6 +3,7 @@
 // Every function works on canonical coefficients in [0, q) unless noted.
 #pragma once
 #include "common.h"
+#include "lowbits.h"
 
 namespace dil {
 
@@ -55,22 +56,6 @@ __device__ __forceinline__ void load_a(int32_t a[16], const uint8_t *poly, int t
   p.get(a);
 }
 
-// One word per coefficient of w for the checks of Alg. 2: 2 LowBits(w) + [HighBits(w) != 0].
-// They need no more than that.  r ~ HighBits 2 gamma2 + LowBits (mod q), and for
-// |x| < gamma2 the pair (HighBits(r), x) is the decomposition of HighBits(r) 2 gamma2 + x.
-// So with |c s2| <= beta, |LowBits(w - c s2)| < gamma2 - beta if and only if
-// |LowBits(w) - c s2| < gamma2 - beta, and then w - c s2 keeps w's high bits.
-// Adding c t0 (|c t0| < gamma2) to such a low part gives u with |u| < 2 gamma2,
-// and the high bits change if and only if u leaves (-gamma2, gamma2]; the one
-// exception is u = -gamma2 with high bits 0, which Decompose maps to 0 again
-// (r = q - gamma2).
-template <int LV>
-__device__ __forceinline__ int32_t pack_low(int32_t r1, int32_t r0) { return 2 * r0 + (r1 != 0); }
-template <int LV>
-__device__ __forceinline__ bool hint_of(int32_t u, int32_t nonzero_high) {
-  constexpr int32_t G2 = Lv<LV>::GAMMA2;
-  return u > G2 || u - nonzero_high < -G2;
-}
 template <int LV>
 __device__ __forceinline__ int32_t use_hint(int32_t h, int32_t r) {
   constexpr int32_t M = (Q - 1) / (2 * Lv<LV>::GAMMA2);
