@@ -540,12 +540,15 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
   uint32_t nactive = count;
   uint32_t *cur = ws.active0, *nxt = ws.active1;
   uint64_t evaluated = 0;
-  int rounds = 0;
+  uint32_t rounds = 0;  // nonces that every task still active has had
+  constexpr uint32_t MOST_ROUNDS = 4096;
   while (nactive > 0) {
-    if (++rounds > 4096) return fail(ctx, DIL_EHIP, "sign loop did not terminate");
+    if (rounds >= MOST_ROUNDS) return fail(ctx, DIL_EHIP, "sign loop did not terminate");
     HIPCHK(ctx, hipMemsetAsync(ws.counters, 0, 8, st));
     if ((uint64_t)nactive * L <= FEW_STREAMS) {
-      sg_few_k<LV><<<nactive, 64 * L, 0, st>>>(ws, sig, cur, nactive, nxt);
+      const uint32_t most = std::min(FEW_TRIES, MOST_ROUNDS - rounds);
+      sg_few_k<LV><<<nactive, 64 * L, 0, st>>>(ws, sig, cur, nactive, nxt, most);
+      rounds += most;
       LAUNCHCHK(ctx);
       HIPCHK(ctx, hipMemcpyAsync(ctx->host_counters, ws.counters, 8, hipMemcpyDeviceToHost, st));
       HIPCHK(ctx, hipStreamSynchronize(st));
@@ -554,6 +557,7 @@ int sign_staged(dil_ctx *ctx, const uint8_t *sk, const uint32_t *key_idx, const 
       std::swap(cur, nxt);
       continue;
     }
+    rounds++;
     evaluated += nactive;
     // a round ends on the host: few tasks make it as long as its chains of permutations
     const uint32_t streams = std::min<uint64_t>((uint64_t)nactive * L, UINT32_MAX);

@@ -304,14 +304,14 @@ __global__ void __launch_bounds__(64 * Lv<LV>::L) rd_cand_k(Ws ws, Group gr, int
 }
 
 // The staged form's loop for the tasks of a list that are few enough for a
-// workgroup each: up to FEW_TRIES nonces, in order, until one passes.  A round in
+// workgroup each: up to `most` nonces (at most FEW_TRIES), in order, until one passes.  A round in
 // four launches and a wait of the host took 83 us with a few tasks left, a nonce
 // here takes 50 (level 3; 1,000 tasks 3000 -> 2170 us).  Two wavefronts per SIMD:
 // with three dev_check spills (2,230 us; level 5 2,000 against 1,850).
 constexpr uint32_t FEW_TRIES = 64, FEW_STREAMS = WAVE_STATES;
 template <int LV>
 __global__ void __launch_bounds__(64 * Lv<LV>::L, 2) sg_few_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,
-                                                            uint32_t *next_active) {
+                                                            uint32_t *next_active, uint32_t most) {
   constexpr int K = Lv<LV>::K, L = Lv<LV>::L;
   __shared__ __align__(16) CandLds<LV> lds;
   if (blockIdx.x >= nactive) return;
@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(64 * Lv<LV>::L, 2) sg_few_k(Ws ws, uint8_t *si
     }
     __syncthreads();
     done = lds.ok;
-  } while (!done && tries < FEW_TRIES);
+  } while (!done && tries < most);
   if (threadIdx.x == 0) {
     atomicAdd(&ws.counters[1], tries);
     if (!done) {
