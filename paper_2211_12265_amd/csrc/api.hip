@@ -133,7 +133,10 @@ constexpr int persist_slots(int waves) {
 // another's matrix work, measured 5-40% slower: the later rounds of a group are
 // latency-bound whatever its size.)
 constexpr uint32_t ROUND_GROUP = 16384;
-constexpr unsigned FINISH_GRID = 64;  // workgroups of the finishing launch
+// Workgroups of the finishing launch (Resume in persist.h): two per CU, as the loop
+// kernel takes, in no more scratch than a call of the loop kernel has (level 2, 1,000
+// tasks on a key table: 320 MB; 370).
+constexpr unsigned FINISH_GRID = 512;
 struct RoundPlan {
   uint32_t groups, size, cap;
 };

@@ -91,7 +91,12 @@ __device__ __forceinline__ int claim_tasks(uint32_t *queue, uint32_t count, uint
 
 // Where the finishing launch of Sign in rounds (rounds.h) starts: the unsigned
 // tasks' list and count, the next nonce index of each and the work queue.
-// list = nullptr: all tasks of the call from nonce 0.
+// list = nullptr: all tasks of the call from nonce 0.  Most launches find none or one
+// task, which then needs a few more nonces: a first batch of `tail` slots per task.
+// But a key row whose t0 makes most candidates fail leaves many tasks that need
+// many: they are spread over all workgroups, and batches grow to all G slots (4,000
+// tasks of such level-2 keys, 61 nonces on average: 7.6 ms in the loop kernel from the
+// start, 16.7 after rounds with 64 workgroups and short batches only, 5.9 now).
 struct Resume {
   const uint32_t *list, *cnt;
   uint32_t *queue;
@@ -366,6 +371,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
   uint32_t first = 0;
   if constexpr (RESUME) {
     const RoundState st = round_state(rs.cnt, rs.n0, rs.rounds);
+    if (blockIdx.x >= st.n) return;  // nothing for this workgroup: mostly none is left at all
     count = st.n;
     first = st.first;
     queue = rs.queue;
@@ -384,7 +390,11 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
   for (uint32_t batch = 0;; batch++) {
     if (tid == 0) {
       int nh = lds.nheld;
-      const int hmax = (int)(sched & 0xFFu), tail = (int)(sched >> 8);
+      int hmax = (int)(sched & 0xFFu), tail = (int)(sched >> 8);
+      if constexpr (RESUME) {
+        hmax = min(hmax, (int)((count + gridDim.x - 1) / gridDim.x));  // spread over the workgroups
+        tail = min(tail << min(batch, 2u), G);
+      }
       const int had = nh;
       if (!lds.queue_empty && nh < hmax) nh = claim_tasks(queue, count, (uint32_t)(hmax - nh), nh, lds.h_task,
                                                           lds.h_next, lds.queue_empty);
@@ -394,7 +404,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
           lds.h_next[h] = first;
         }
       lds.nheld = nh;
-      const int want = TAIL ? sched_slots(nh, G, W, lds.queue_empty, tail) : G;
+      const int want = TAIL ? sched_slots(nh, G, W, RESUME ? 1 : lds.queue_empty, tail) : G;
       const int ns = CONTIG ? sched_assign_contig(nh, want, lds.h_next, lds.h_win, lds.s_h, lds.s_att)
                             : sched_assign(nh, want, lds.h_next, lds.h_win, lds.s_h, lds.s_att);
       lds.nslots = ns;
