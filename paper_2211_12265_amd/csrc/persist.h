@@ -398,13 +398,15 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
       const int had = nh;
       if (!lds.queue_empty && nh < hmax) nh = claim_tasks(queue, count, (uint32_t)(hmax - nh), nh, lds.h_task,
                                                           lds.h_next, lds.queue_empty);
-      if constexpr (RESUME)
+      if constexpr (RESUME) {
         for (int h = had; h < nh; h++) {
           lds.h_task[h] = rs.list[lds.h_task[h]];
           lds.h_next[h] = first;
         }
+        if ((uint64_t)hmax * gridDim.x >= count) lds.queue_empty = 1;  // the first claims take all
+      }
       lds.nheld = nh;
-      const int want = TAIL ? sched_slots(nh, G, W, RESUME ? 1 : lds.queue_empty, tail) : G;
+      const int want = TAIL ? sched_slots(nh, G, W, lds.queue_empty, tail) : G;
       const int ns = CONTIG ? sched_assign_contig(nh, want, lds.h_next, lds.h_win, lds.s_h, lds.s_att)
                             : sched_assign(nh, want, lds.h_next, lds.h_win, lds.s_h, lds.s_att);
       lds.nslots = ns;
