@@ -133,10 +133,24 @@ constexpr int persist_slots(int waves) {
 // another's matrix work, measured 5-40% slower: the later rounds of a group are
 // latency-bound whatever its size.)
 constexpr uint32_t ROUND_GROUP = 16384;
-// Workgroups of the finishing launch (Resume in persist.h): two per CU, as the loop
-// kernel takes, in no more scratch than a call of the loop kernel has (level 2, 1,000
-// tasks on a key table: 320 MB; 370).
-constexpr unsigned FINISH_GRID = 512;
+// The finishing launch (Resume in persist.h) of a group of n tasks: workgroups and the
+// slots of each.  The candidates' memory is its scratch: it goes to one workgroup per CU
+// first, then to all slots of a batch, then to a second workgroup (1,000 level-2 tasks
+// of 1,400 nonces, 8,192 candidates: 122 ms on 512 workgroups, 89 on 256, 77 on 128;
+// 4,000 level-5 tasks of 500, 16,000 candidates: 80, 106, 175).
+struct FinishShape {
+  uint32_t grid, slots;
+};
+template <int LV>
+FinishShape finish_shape(uint32_t n) {
+  constexpr uint32_t W = 4, G = PCfgW<LV, 4>::G, CUS = 256;
+  const uint32_t cands = round_candidates(n);
+  FinishShape f;
+  f.slots = std::min(G, cands / std::min(n, CUS) / W * W);
+  f.grid = std::min({n, 2 * CUS, cands / f.slots});
+  return f;
+}
+static_assert(ROUND_KNEE / 256 >= 4 && ROUND_NONCES_MAX >= 4, "at least one slot per wavefront");
 struct RoundPlan {
   uint32_t groups, size, cap;
 };
@@ -212,22 +226,21 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
     p.stage = take(waves > 1, si.stage_size(grid));
   }
   if (rounds) {
-    // the finishing launch of a group uses the candidates' memory for its batches
     const RoundPlan rp = round_plan((uint32_t)cap);
     uint32_t *cnt = (uint32_t *)take(true, (size_t)rp.groups * ROUND_WORDS * 4);
-    const ScratchIdx si{(size_t)persist_slots<LV>(4), (size_t)L, (size_t)K, w1_stride<LV>(), sig_stride<LV>()};
     // sized for the largest group a smaller call could have, so that a reservation covers it
     const uint32_t gmax = (uint32_t)std::min<size_t>(cap, ROUND_GROUP);
-    const size_t fg = std::min<size_t>(FINISH_GRID, gmax), cands = round_candidates(gmax);
+    const size_t cands = round_candidates(gmax);
+    static_assert(P<LV>::W1B * K % 256 == 0, "rows of w1 as the loop kernel strides them");
     Group g{};
     g.cap = rp.cap;
     g.cnt = cnt;
     for (uint32_t *&l : g.list) l = (uint32_t *)take(true, (size_t)gmax * 4);
-    g.y = take(true, std::max(cands * L, si.y_size(fg) / N) * P<LV>::YB);
-    g.w = (int32_t *)take(true, std::max(cands * K * N, si.w_size(fg)) * sizeof(int32_t));
-    g.w1 = take(true, std::max(cands * K * P<LV>::W1B, si.w1_size(fg)));
+    g.y = take(true, cands * L * P<LV>::YB);
+    g.w = (int32_t *)take(true, cands * K * N * sizeof(int32_t));
+    g.w1 = take(true, cands * K * P<LV>::W1B);
     g.ct = take(true, cands * CT_STRIDE);
-    g.c = (int8_t *)take(true, std::max(cands * N, si.stage_size(fg)));
+    g.c = (int8_t *)take(true, cands * N);
     if (group) *group = g;
   }
   if (ws) *ws = w;
@@ -676,15 +689,14 @@ void launch_round(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int
 // The finishing launch after `rounds` rounds.
 template <int LV>
 void launch_finish(dil_ctx *ctx, const Ws &ws, const Group &gr, uint8_t *sig, int rounds, hipStream_t s) {
-  PScr sc;
+  PScr sc{};
   sc.y = gr.y;
   sc.w = gr.w;
   sc.w1 = gr.w1;
-  sc.stage = (uint8_t *)gr.c;
-  const Resume rs{gr.list[rounds & 1], gr.cnt, gr.cnt + ROUNDS_MAX + 1, gr.n, rounds};
+  const FinishShape f = finish_shape<LV>(gr.n);
+  const Resume rs{gr.list[rounds & 1], gr.cnt, gr.cnt + ROUNDS_MAX + 1, gr.n, rounds, (int)f.slots};
   constexpr uint32_t HELD = 4, TAIL_SLOTS = 20;
-  sg_persistw_k<LV, 4, true, true, true><<<std::min<unsigned>(FINISH_GRID, gr.n), 256, 0, s>>>(
-      ws, sc, sig, 0, HELD | TAIL_SLOTS << 8, ctx->dev_stats, rs);
+  sg_persistw_k<LV, 4, true, true, true><<<f.grid, 256, 0, s>>>(ws, sc, sig, 0, HELD | TAIL_SLOTS << 8, ctx->dev_stats, rs);
 }
 
 // mu / rho' and the rounds on the caller's stream; ExpandA of all tasks runs on

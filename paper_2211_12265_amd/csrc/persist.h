@@ -31,7 +31,7 @@ struct PScr {
   uint8_t *y;    // [P][G][L][YB]
   int32_t *w;    // [P][G][K][256]
   uint8_t *w1;   // [P][G][K * W1B rounded to 256]
-  uint8_t *stage; // multi-wave kernels only: [P][G][SIG rounded to 256]
+  uint8_t *stage; // multi-wave kernels only, not with Resume: [P][G][SIG rounded to 256]
 };
 
 template <int LV>
@@ -90,18 +90,19 @@ __device__ __forceinline__ int claim_tasks(uint32_t *queue, uint32_t count, uint
 }
 
 // Where the finishing launch of Sign in rounds (rounds.h) starts: the unsigned
-// tasks' list and count, the next nonce index of each and the work queue.
-// list = nullptr: all tasks of the call from nonce 0.  Most launches find none or one
-// task, which then needs a few more nonces: a first batch of `tail` slots per task.
-// But a key row whose t0 makes most candidates fail leaves many tasks that need
-// many: they are spread over all workgroups, and batches grow to all G slots (4,000
-// tasks of such level-2 keys, 61 nonces on average: 7.6 ms in the loop kernel from the
-// start, 16.7 after rounds with 64 workgroups and short batches only, 5.9 now).
+// tasks' list and count, the next nonce index of each, the work queue, and the slots
+// per batch (a multiple of the wavefronts) for which each workgroup has scratch.
+// Most launches find none or one task, which then needs a few more nonces: a first
+// batch of `tail` slots per task.  But a key row whose t0 makes most candidates fail
+// leaves many tasks that need many: they are spread over all workgroups, and
+// batches grow to all slots (4,000 tasks of such level-2 keys, 61 nonces on average: 7.6
+// ms in the loop kernel from the start, 16.7 after rounds with 64 workgroups and short
+// batches only, 7.1 now).
 struct Resume {
   const uint32_t *list, *cnt;
   uint32_t *queue;
   uint32_t n0;
-  int rounds;
+  int rounds, slots;
 };
 
 // the scratch offsets of a workgroup shape with G slots per batch
@@ -355,9 +356,11 @@ __device__ __forceinline__ void copy_sig_row(const uint32_t *src, uint8_t *dst, 
 template <int LV, int NW, bool PAD = true, bool TAIL = false, bool RESUME = false>
 __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count,
                                                      uint32_t sched, uint32_t *stats, Resume rs) {
-  constexpr int K = Lv<LV>::K, L = Lv<LV>::L, G = PCfgW<LV, NW>::G, W = NW;
+  constexpr int K = Lv<LV>::K, L = Lv<LV>::L, GMAX = PCfgW<LV, NW>::G, W = NW;
+  const int G = RESUME ? rs.slots : GMAX;
   constexpr bool CONTIG = NW == 4 && L == 4 && PAD;  // contiguous slot ranges per wavefront
-  static_assert(G <= 64, "the winner search takes one slot per lane");
+  static_assert(GMAX <= 64, "the winner search takes one slot per lane");
+  static_assert(!RESUME || (P<LV>::SIG + 3) / 4 <= K * N, "a signature fits its slot's w");
   static_assert(!CONTIG || PCfgW<LV, NW>::GW * L <= 64, "a wavefront's own slots take one ExpandMask lane per stream");
   __shared__ __align__(16) PersistWLds<LV, NW> lds;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, t = lane & 15;
@@ -366,7 +369,8 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
   uint8_t *yb = sc.y + ybytes<LV>(si.y(wg, 0, 0));
   int32_t *wb = sc.w + si.w(wg, 0, 0);
   uint8_t *w1b = sc.w1 + si.w1(wg, 0);
-  uint8_t *stg = sc.stage + si.stage(wg, 0);
+  // slot s's signature (RESUME: where its w was, which nothing reads once it has passed)
+  auto staged = [&](int s) { return RESUME ? (uint32_t *)(wb + si.w(0, s, 0)) : (uint32_t *)(sc.stage + si.stage(wg, s)); };
   uint32_t *queue = ws.counters;
   uint32_t first = 0;
   if constexpr (RESUME) {
@@ -474,7 +478,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
                               ws.sec + kix(ws, task) * sec_bytes<LV>(), lds.u[wave].ck, lane);
       if (ok) {
         const uint32_t *sb = lds.u[wave].ck.sigbuf;
-        uint32_t *dst = (uint32_t *)(stg + si.stage(0, s));
+        uint32_t *dst = staged(s);
         for (int w = lane; w < (P<LV>::SIG + 3) / 4; w += 64) dst[w] = sb[w];
         if (lane == 0) atomicMin(&lds.h_win[h], lds.s_att[s]);
       }
@@ -492,8 +496,7 @@ __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint
       const uint64_t hit = __ballot(lane < ns && lds.s_h[lane] == h && lds.s_att[lane] == win);
       if (hit == 0) continue;
       const int s = (int)__builtin_ctzll(hit);
-      copy_sig_row<P<LV>::SIG>((const uint32_t *)(stg + si.stage(0, s)),
-                               sig + (size_t)lds.h_task[h] * P<LV>::SIG, lane);
+      copy_sig_row<P<LV>::SIG>(staged(s), sig + (size_t)lds.h_task[h] * P<LV>::SIG, lane);
     }
     __syncthreads();
     if (tid == 0)
