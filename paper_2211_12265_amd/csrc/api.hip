@@ -194,12 +194,9 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
     off += (bytes + 255) & ~(size_t)255;
     return r;
   };
-  const size_t muw1_stride = ((size_t)P<LV>::MUW1 + 255) & ~(size_t)255;
   Ws w{};
-  w.cap = cap;
-  w.muw1_stride = muw1_stride;
   w.counters = (uint32_t *)take(true, 16 * 4);
-  w.muw1 = take(sign || form == WS_VERIFY, cap * muw1_stride);
+  w.muw1 = take(sign || form == WS_VERIFY, cap * muw1_stride<LV>());
   w.rhop = take(sign || form == WS_KEYGEN, cap * 64);
   w.ctilde = take(staged, cap * CT_STRIDE);
   w.cpoly = (int8_t *)take(staged || form == WS_VERIFY, cap * 256);

@@ -32,8 +32,6 @@ struct Ws {
   int32_t *flag;     // [cap]
   uint32_t *active0, *active1;  // [cap] task lists
   uint32_t *counters;           // [8]: next active count, error flags, attempts
-  size_t cap;
-  size_t muw1_stride;
   // Resident key tables: when kmap is set, A, sec (and t1s, tr) are
   // indexed by key row kmap[task] instead of by task.
   const uint32_t *kmap;
@@ -56,7 +54,7 @@ constexpr int mu_prefix_bytes() {
 __device__ __forceinline__ size_t kix(const Ws &ws, uint32_t task) { return ws.kmap ? ws.kmap[task] : task; }
 
 template <int LV>
-__device__ __forceinline__ size_t muw1_stride() {
+__host__ __device__ __forceinline__ size_t muw1_stride() {
   return ((size_t)P<LV>::MUW1 + 255) & ~(size_t)255;
 }
 

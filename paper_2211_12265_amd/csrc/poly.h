@@ -70,8 +70,6 @@ __device__ __forceinline__ void power2round(int32_t r, int32_t &r1, int32_t &r0)
   r1 = (r + (1 << (D - 1)) - 1) >> D;
   r0 = r - (r1 << D);
 }
-// centred representative of a canonical value
-__device__ __forceinline__ int32_t centred(int32_t x) { return x > (Q - 1) / 2 ? x - Q : x; }
 
 // ---- wave-level helpers (one task per wavefront) ----
 __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0; }

@@ -31,15 +31,6 @@ __device__ __forceinline__ void shake_absorb(uint32_t s[50], uint64_t len, W wor
   }
 }
 
-// word source for one contiguous byte string (any alignment)
-struct SrcBytes {
-  const uint8_t *p;
-  uint64_t len;
-  __device__ __forceinline__ uint64_t operator()(uint64_t pos) const {
-    uint64_t n = len - pos;
-    return load_le_bytes(p + pos, n >= 8 ? 8 : (int)n);
-  }
-};
 // ---- single-block absorption of the short fixed-size sampler seeds ----
 // seed = 32-byte rho (word source) || two nonce bytes, SHAKE128
 template <class W>
