@@ -205,9 +205,6 @@ size_t ws_layout(uint8_t *base, size_t cap, int form, bool keyset, size_t grid, 
   w.sec = (int8_t *)take(sign && !keyset, cap * sec_bytes<LV>());
   w.y = take(staged, cap * L * P<LV>::YB);
   w.w = (int32_t *)take(staged, cap * K * 1024);
-  // held no longer (hint bits), but counted: the largest batch that dil_verify_keyset_noalloc
-  // accepts follows from this layout
-  take(form == WS_VERIFY, cap * K * 32);
   w.flag = (int32_t *)take(form == WS_VERIFY, cap * 4);
   w.kappa = (uint32_t *)take(sign, cap * 4);
   w.active0 = (uint32_t *)take(sign, cap * 4);
@@ -1269,7 +1266,10 @@ template <int LV>
 int verify_keyset_noalloc_impl(dil_ctx *ctx, const dil_keyset *ks, const uint32_t *key_idx, const uint8_t *msg,
                                const uint64_t *msg_off, const uint8_t *sig, int32_t *verdict, uint32_t count,
                                hipStream_t st) {
-  const size_t need = ws_layout<LV>(nullptr, count, WS_VERIFY, true, 0, 1, nullptr, nullptr, nullptr);
+  // 32 bytes per task and row of w1 more than the layout, which held hint bits when the
+  // largest accepted counts became part of the interface
+  const size_t need = ws_layout<LV>(nullptr, count, WS_VERIFY, true, 0, 1, nullptr, nullptr, nullptr) +
+                      (((size_t)count * Lv<LV>::K * 32 + 255) & ~(size_t)255);
   if (need > NOALLOC_SCRATCH_BYTES) {
     char t[160];
     snprintf(t, sizeof t, "count %u needs %zu bytes of scratch, above the %zu-byte maximum", count, need,
