@@ -569,7 +569,8 @@ __device__ __forceinline__ void dev_expand_mask(const uint8_t *rhop, uint32_t ka
 // NG: 16-lane groups that share the work; with more than a wavefront's four, all
 // wavefronts of the workgroup meet at two barriers, and the packed HighBits(w)
 // stay in w1buf.
-template <int LV, bool PAD = true, bool EARLY = false, int NG = 4, class TW>
+// TOGETHER: as in load_mask.
+template <int LV, bool PAD = true, bool EARLY = false, int NG = 4, bool TOGETHER = true, class TW>
 __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A, int32_t *w_out, uint8_t *w1_out,
                                               int32_t *hat, int32_t *tr, uint32_t *w1buf, const TW &ftw,
                                               const TW &itw, int lane) {
@@ -582,7 +583,7 @@ __device__ __forceinline__ void dev_compute_w(const uint8_t *y, const uint8_t *A
   }
   for (int j = g; j < L; j += NG) {
     int32_t x[16];
-    load_mask<PP::ZBITS, Lv<LV>::GAMMA1>(x, y + j * PP::YB, t);
+    load_mask<PP::ZBITS, Lv<LV>::GAMMA1, TOGETHER>(x, y + j * PP::YB, t);
     ntt16<TW, PAD>(x, ftw, tr, t);
 #pragma unroll
     for (int r = 0; r < 16; r++) hat[hat_idx(j, t, r)] = x[r];

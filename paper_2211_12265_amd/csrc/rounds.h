@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(256) rd_w_k(Ws ws, Group gr, int r) {
   const uint32_t task = round_task(gr, r, s / st.m);
   const Tw ftw = ntt_lane_tw(t), itw = intt_lane_tw(t);
   RoundWLds<LV> &l = lds[wave];
-  dev_compute_w<LV, true, true>(gr.y + (size_t)s * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * A_POLY, gr.w + (size_t)s * K * N,
+  dev_compute_w<LV, true, true, 4, false>(gr.y + (size_t)s * L * P<LV>::YB, ws.A + kix(ws, task) * K * L * A_POLY, gr.w + (size_t)s * K * N,
                     gr.w1 + (size_t)s * K * P<LV>::W1B, l.hat, l.tr + (lane >> 4) * NTT_LDS_GROUP, l.w1buf, ftw, itw,
                     lane);
 }

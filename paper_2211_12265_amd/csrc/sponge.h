@@ -90,15 +90,24 @@ __device__ __forceinline__ void expand_mask_squeeze(uint32_t s[50], uint8_t *out
 // words, after field t.  Every field is fetched as the two words it may span;
 // the second word of a row's last field is the one after the row (its bits are
 // not used), so a row is followed by at least four more bytes of its memory.
-template <int B, int32_t GAMMA1>
+// TOGETHER: all words are requested before the first field is cut out.  Left alone, in
+// kernels near their register limit the compiler waits for each pair of words before
+// it requests the next (loop kernel, 10,000 tasks of levels 2 / 3 / 5, mean of six
+// batches: 1212 / 2188 / 2242 us, with it 1045 / 1880 / 1920; where the registers leave
+// room, as in rd_w_k, it asks for them early enough by itself).
+template <int B, int32_t GAMMA1, bool TOGETHER = false>
 __device__ __forceinline__ void load_mask(int32_t x[16], const uint8_t *row, int t) {
   const uint32_t *w = (const uint32_t *)row + ((B * t) >> 5);
   const int sh = (B * t) & 31;
+  uint32_t lo[16], hi[16];
 #pragma unroll
   for (int r = 0; r < 16; r++) {
-    const uint32_t lo = w[r * (B / 2)], hi = w[r * (B / 2) + 1];
-    x[r] = GAMMA1 - (int32_t)(__builtin_amdgcn_alignbit(hi, lo, sh) & ((1u << B) - 1u));
+    lo[r] = w[r * (B / 2)];
+    hi[r] = w[r * (B / 2) + 1];
   }
+  if constexpr (TOGETHER) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int r = 0; r < 16; r++) x[r] = GAMMA1 - (int32_t)(__builtin_amdgcn_alignbit(hi[r], lo[r], sh) & ((1u << B) - 1u));
 }
 
 // ExpandS: the lane's SHAKE256 stream (absorbed and permuted once) stored as it
