@@ -76,8 +76,15 @@ extern "C" {
  *                        synchronises once per loop round; a few hundred
  *                        tasks or less take all stages in one launch, up to 64
  *                        loop rounds at a time).
- *   DIL_MODE_PERSISTENT  fused persistent kernel with a device-side work queue
- *                        (asynchronous; no host round trips). */
+ *   DIL_MODE_PERSISTENT  asynchronous, no host round trips.  With every
+ *                        "persist.*" knob below at its default: rounds, one
+ *                        launch per stage over all candidates of a round, task
+ *                        lists and counts kept on the device, what is left
+ *                        after the last round finished by the loop kernel.
+ *                        With any of them set: the loop kernel alone, one
+ *                        persistent launch with a device-side work queue
+ *                        (14 to 24% slower than rounds at 10,000 tasks).  The
+ *                        signatures are the same. */
 #define DIL_MODE_STAGED 0
 #define DIL_MODE_PERSISTENT 1
 
@@ -91,7 +98,10 @@ int dil_ctx_destroy(dil_ctx *ctx);
 /* Select the Sign execution form (DIL_MODE_*). */
 int dil_ctx_set_mode(dil_ctx *ctx, int mode);
 /* Tuning knobs (0 = automatic):
- *   "persist.grid"  workgroups launched by the persistent Sign kernel;
+ *   "persist.grid"  workgroups launched by the persistent Sign kernel
+ *                   (setting this, "persist.hmax", "persist.tail",
+ *                   "persist.waves" or "persist.pad" to anything but its
+ *                   default selects that kernel instead of rounds);
  *   "persist.hmax"  tasks one workgroup holds at a time (1..slots per batch);
  *   "persist.waves" wavefronts per persistent workgroup: 1 (64 / l candidate
  *                   slots per batch), 2 or 4 (default; W * (64 / l) slots,
@@ -99,14 +109,15 @@ int dil_ctx_set_mode(dil_ctx *ctx, int mode);
  *                   value is DIL_EINVAL; the ML-DSA levels are built for 4
  *                   only (a persistent Sign call or dil_persist_capacity at
  *                   level 44 / 65 / 87 with 1 or 2 is DIL_EINVAL);
- *   "timing"        1 = record HIP events around the persistent Sign's setup
- *                   kernels and its loop kernel (read with dil_sign_timing);
+ *   "timing"        1 = record HIP events around the setup and the loop of
+ *                   persistent-mode Sign calls (read with dil_sign_timing);
  *   "graph"         1 = capture the launch sequences of persistent-mode Sign's
  *                   setup stages and of Verify into hipGraphs, replayed when a
  *                   call repeats the same level, buffers, count and schedule
  *                   (up to 16 graphs per context, least recently used
- *                   evicted; dropped when the workspace grows); the Sign loop
- *                   kernel, a single launch, is always launched directly;
+ *                   evicted; dropped when the workspace grows); Sign's
+ *                   rounds (all but the first one's masks) and its loop
+ *                   kernel are always launched directly;
  *   "ntt.variant"   form of dil_ntt_mul_batch, for the optimisation ablation
  *                   of the NTT primitive (Sec. 3.2, Sec. 4.2); every form
  *                   returns the same words: 0 (default) levels merged in
@@ -120,7 +131,8 @@ int dil_ctx_set_mode(dil_ctx *ctx, int mode);
  *                   of the NTT(t0) stage of signing (Sec. 5, speedup
  *                   breakdown); every form returns the same words: 0
  *                   (default) unpacking merged into the NTT's registers,
- *                   padded LDS transpose (the Sign setup's code path), 1 the
+ *                   padded LDS transpose (Sign itself multiplies by t0 on
+ *                   the matrix cores, without this transform), 1 the
  *                   same unpadded, 2 one fused kernel that stores t0 in HBM
  *                   and reads it back, 3 an unpacking kernel then an NTT
  *                   kernel through HBM; other values are DIL_EINVAL;
@@ -137,8 +149,9 @@ int dil_ctx_set_mode(dil_ctx *ctx, int mode);
  *                   workgroup once the work queue has run dry (rounded up to a
  *                   multiple of 4, at most the batch's slots): shorter last
  *                   batches, fewer speculative candidates; -1 (default) the
- *                   level's setting (20 at levels 2 / 44, 12 at 3 / 65, full
- *                   batches at 5 / 87), 0 full batches, 1..64 that many; a
+ *                   level's setting when another knob selects the loop kernel
+ *                   (20 at levels 2 / 44, 12 at 3 / 65, full batches at
+ *                   5 / 87), 0 full batches, 1..64 that many; a
  *                   value above 0 with another "persist.waves" or
  *                   "persist.pad" = 0 fails the Sign call with DIL_EINVAL;
  *                   the signatures do not depend on it;
@@ -159,13 +172,14 @@ int dil_ctx_set_param(dil_ctx *ctx, const char *name, int64_t value);
  * largest batch they admit up front. */
 int dil_ctx_reserve(dil_ctx *ctx, int level, uint32_t count);
 /* As dil_ctx_reserve, for calls of one kind only: op (DIL_OP_*) at `level`,
- * against a resident key table (keyset != 0: A-hat and the NTT-domain secrets
+ * against a resident key table (keyset != 0: A-hat and the secrets' matrix tiles
  * come from the table and take no workspace) or not, in the context's current
  * Sign form and schedule knobs, with up to `count` tasks. */
 int dil_ctx_reserve_call(dil_ctx *ctx, int level, int op, int keyset, uint32_t count);
 /* Device bytes of workspace that one such call of exactly `count` tasks needs
- * (the same layout the call carves: per-task rows, plus the persistent Sign
- * kernel's per-workgroup scratch at the schedule that count gets).  Memory
+ * (the same layout the call carves: per-task rows, plus persistent-mode Sign's
+ * candidates of a round, or the loop kernel's per-workgroup scratch at the
+ * schedule that count gets).  Memory
  * budgets of serving loops are accounted with this figure.  The workspace is
  * allocated stream-ordered on the calling stream; growing it waits only for
  * this context's previous call. */
@@ -278,7 +292,7 @@ int dil_verify_keyset_noalloc(dil_ctx *ctx, const dil_keyset *ks, const uint32_t
  * context of its own; that needs more hardware queues than HIP's default of 4
  * per process, so the process should set GPU_MAX_HW_QUEUES (e.g. 16) before
  * HIP starts.  mode is DIL_MODE_STAGED or DIL_MODE_PERSISTENT for Sign; the
- * persistent Sign calls use four-wavefront workgroups ("persist.waves" = 4).
+ * persistent ones run in the automatic form (rounds).
  * mode | DIL_SERVER_MLDSA_INTERNAL: the requests of the ML-DSA levels carry
  * formatted messages M' ("mldsa.internal" = 1 on those groups: context
  * strings, pre-hashed messages); round-3 requests are unaffected.  Other mode
@@ -352,10 +366,11 @@ int dil_sign_stats(dil_ctx *ctx, uint64_t *evaluated, uint64_t *sequential);
  * slots per workgroup batch (W * (64 / l)), for schedule tuning. */
 int dil_persist_capacity(dil_ctx *ctx, int level, int *resident_groups, int *slots_per_batch);
 
-/* Event-measured durations (ms) of the most recent persistent dil_sign_batch
- * calls made since the "timing" parameter was set (at most 64 are kept):
- * setup kernels (mu, rho', ExpandA, secret NTTs) and the persistent
- * rejection-loop kernel, oldest first.  Fills at most max_calls entries of
+/* Event-measured durations (ms) of the most recent persistent-mode
+ * dil_sign_batch calls made since the "timing" parameter was set (at most 64
+ * are kept), oldest first: setup (mu, rho', ExpandA, the secrets' tiles and, in
+ * rounds, the masks of the first round) and loop (the other launches of the
+ * rounds, or the loop kernel).  Fills at most max_calls entries of
  * each caller-owned array (either may be NULL), stores the number filled in
  * *n_calls, and synchronises on the recorded events. */
 int dil_sign_timing(dil_ctx *ctx, float *setup_ms, float *loop_ms, int max_calls, int *n_calls);

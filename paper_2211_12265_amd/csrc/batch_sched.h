@@ -139,9 +139,11 @@ DIL_HD int sched_retire(int nh, uint32_t *h_task, uint32_t *h_next, const uint32
 // (n0 at the start of round 0), so that every kernel derives the round's
 // layout from the counts alone.  A round of few candidates takes as long as its
 // chains (five, then eight permutations), so it had better hold about as many as
-// run in that time anyway: 10,000 tasks at level 2 took 1314 / 1259 / 1228 us with
-// 4,096 / 8,192 / 16,384 (min 3), 2,503 at ML-DSA-65 917 / 938 / 908; a minimum of
-// 2 / 3 / 4 nonces gave 1389 / 1259 / 1190 us at level 2.
+// run in that time anyway.  Over 100 sizes from 20 to 20,000 tasks at levels 2, 3, 5
+// and 65, 4,096 take 2.4% longer than 8,192 in the geometric mean and 16,384 1.8%; by
+// level 4.4 / 2.6 / 0.1 / 2.4% and -0.8 / 1.9 / 3.6 / 2.6%, single sizes up to 15%
+// either way.  A minimum of 2 / 3 / 4 / 5 nonces: level 2, 10,000 tasks, 1389 / 1259 /
+// 1190 us with the kernels of that time, later 1156 / 1102 / 1127 for 3 / 4 / 5.
 constexpr uint32_t ROUND_NONCES_MIN = 4, ROUND_NONCES_MAX = 64, ROUND_KNEE = 8192;
 DIL_HD uint32_t round_nonces(uint32_t n) {
   if (n == 0) return 0;

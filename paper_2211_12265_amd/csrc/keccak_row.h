@@ -15,7 +15,7 @@
 //   chi    the next two sheets from lanes l + 2, l + 4.
 // After chi lanes 0 .. 11 are valid, after theta lanes 2 .. 11, which hold every
 // sheet once and are the ones whose words are kept; the read-back makes all 16
-// valid again.  32 VALU and 16 LDS instructions per round against 120 VALU on a
+// valid again.  34 VALU and 14 LDS instructions per round against 120 VALU on a
 // lane pair (keccak_pair.h): 3.4 times the issue slots per state, half the time
 // per permutation of a lone wavefront (3.1 against 6.8 us): the mu chains of 2,503
 // messages of up to 4 KB 328 -> 176 us.  4,096 states take 4.4 us per permutation,
@@ -399,7 +399,7 @@ __global__ void __launch_bounds__(64) vf_prep_coop_k(const uint8_t *sig, Ws ws, 
 // mu, the others sample the challenge and do the main part, a wavefront each.  In
 // one launch because the hash chain, 45 permutations for 6 KB, leaves the chip
 // nearly idle: 333 messages at ML-DSA-87 took 155 us with three launches
-// in series, 128 with one.
+// in series, 128 with one (one card; the call varies between 110 and 190).
 constexpr uint32_t FRONT_TASKS = WAVE_STATES / 2;  // above, the two would queue for LDS
 template <int LV, bool INTERNAL>
 __global__ void __launch_bounds__(64, 3)

@@ -1,7 +1,7 @@
 // Keccak-f[1600] with one state on a whole wavefront, for the smallest batches:
 // as the 16-lane form (keccak_row.h), but row y of the wavefront holds plane y
 // in one register and every row holds plane 4 in a second one, so that a round
-// is 27 VALU and 7 LDS instructions instead of 34 and 15.
+// is 24 VALU and 7 LDS instructions instead of 34 and 14.
 //   theta  column parity by two lane swaps across the rows; the rest as on a row;
 //   rho, pi  through LDS; plane 4 is written by row 0 only and read by all rows;
 //   chi    as on a row.

@@ -352,7 +352,9 @@ __device__ __forceinline__ void copy_sig_row(const uint32_t *src, uint8_t *dst, 
 // allocation (two wavefronts per SIMD with no spills at every level).
 // The bound of two wavefronts per SIMD keeps the accumulators of dev_check in
 // the same 256 registers (left alone, the compiler adds 64 AGPRs to them and
-// the kernel falls to one wavefront per SIMD); no form spills.
+// the kernel falls to one wavefront per SIMD).  At l = 7 the tail form and the
+// finishing launch spill 5 and 6 of them, the unpadded form at level 2 spills 4; the
+// others none.
 template <int LV, int NW, bool PAD = true, bool TAIL = false, bool RESUME = false>
 __global__ void __launch_bounds__(64 * NW, 2) sg_persistw_k(Ws ws, PScr sc, uint8_t *sig, uint32_t count,
                                                      uint32_t sched, uint32_t *stats, Resume rs) {

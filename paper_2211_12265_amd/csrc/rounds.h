@@ -12,7 +12,7 @@
 // to the next round's list and counted, and the next kernels read the count on
 // the device.  Tasks still unsigned after the last round (about one in 10^2
 // calls reaches that) are finished by the persistent kernel of persist.h,
-// started at the next nonce.
+// started at the next nonce (Resume).
 //
 // Against the persistent kernel, every stage gets the registers, the LDS and
 // the wavefronts it wants: the loop kernel holds two wavefronts per SIMD for
@@ -20,8 +20,8 @@
 // call, loop kernel / rounds: 10,000 tasks at level 2 1465 / 1199 us, at level 5
 // (32 to 4096-byte messages) 2844 / 2031 us; 2,503 hedged ML-DSA-65 1328 / 911
 // us; 613 tasks on resident level-2 keys 834 / 460 us, one on a level-3 key
-// 271 / 126 us.  With the kernels as they are now the rounds take 1052, 1870,
-// 810, 340 and 87 us.
+// 271 / 126 us.  With the kernels as they are now the rounds take 1043-1104, 1865-1889,
+// 834-874, 337-412 and 83-97 us (the ranges are of different cards).
 #pragma once
 #include <algorithm>
 
@@ -188,6 +188,9 @@ __global__ void __launch_bounds__(64) rd_chal_k(Ws ws, Group gr, int r) {
 // The checks.  Up to ROUND_SEQ nonces per task, each wavefront takes a task and
 // evaluates its candidates in order, so that none after the first passing one
 // is looked at; with more, the four wavefronts of a workgroup share a task.
+// Three wavefronts per SIMD (168 registers, of which l = 7 spills 9): with two, which
+// need no spills, levels 5 and 87 take 0-1% longer from 2,500 tasks on and 1-2% less
+// below 300.
 constexpr uint32_t ROUND_SEQ = 6;
 template <int LV>
 __global__ void __launch_bounds__(256, 3) rd_check_k(Ws ws, Group gr, uint8_t *sig, int r, uint32_t *stats) {
@@ -307,7 +310,8 @@ __global__ void __launch_bounds__(64 * Lv<LV>::L) rd_cand_k(Ws ws, Group gr, int
 // workgroup each: up to `most` nonces (at most FEW_TRIES), in order, until one passes.  A round in
 // four launches and a wait of the host took 83 us with a few tasks left, a nonce
 // here takes 50 (level 3; 1,000 tasks 3000 -> 2170 us).  Two wavefronts per SIMD:
-// with three dev_check spills (2,230 us; level 5 2,000 against 1,850).
+// with three dev_check spills at every level (2,230 us; level 5 2,000 against 1,850);
+// with two, 10 registers at l = 7 and none elsewhere.
 constexpr uint32_t FEW_TRIES = 64, FEW_STREAMS = WAVE_STATES;
 template <int LV>
 __global__ void __launch_bounds__(64 * Lv<LV>::L, 2) sg_few_k(Ws ws, uint8_t *sig, const uint32_t *active, uint32_t nactive,

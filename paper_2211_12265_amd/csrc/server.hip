@@ -474,9 +474,9 @@ int dil_server_create_tables(dil_server **out, int device, dil_keyset *const *ta
       ok = hipStreamCreateWithFlags(&ln.gst[gi], hipStreamNonBlocking) == hipSuccess &&
            hipEventCreateWithFlags(&ln.gev[gi], hipEventDisableTiming) == hipSuccess &&
            dil_ctx_create(&ln.gctx[gi], device, 0) == DIL_OK && dil_ctx_set_mode(ln.gctx[gi], ctx_mode) == DIL_OK &&
-           // a group call holds few tasks: four-wavefront workgroups give each
-           // task 4 x 64 / l nonces per batch, so almost every task passes in
-           // the first batch instead of needing a second or third
+           // the default, with which Sign runs in rounds; a loop kernel, too, would
+           // want four wavefronts for a group call's few tasks (4 x 64 / l nonces of
+           // each per batch)
            (gi % 2 == 1 || dil_ctx_set_param(ln.gctx[gi], "persist.waves", 4) == DIL_OK) &&
            // ML-DSA groups on formatted messages M' when asked (round-3 calls have no such form)
            (!mldsa_internal || kLevels[li] < 44 || dil_ctx_set_param(ln.gctx[gi], "mldsa.internal", 1) == DIL_OK);

@@ -110,7 +110,7 @@ class _Lane:
         self.stream = torch.cuda.Stream(device=device)
         self.ctx = dl.Context(device.index or 0, mode=dl.MODE_PERSISTENT if persistent else dl.MODE_STAGED)
         if persistent:
-            # few tasks per call: four-wavefront workgroups give each task 4 x 64 / l nonces per batch
+            # the default, with which Sign runs in rounds
             self.ctx.set_param("persist.waves", 4)
         pin = dict(pin_memory=True)
         self.h_msg = torch.empty(max_msg, dtype=torch.uint8, **pin)
