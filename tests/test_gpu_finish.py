@@ -1,6 +1,6 @@
 """The finishing launch of Sign in rounds with work to do: keys whose t0 makes most candidates fail leave many
-tasks after the last round, fewer than its workgroups, about as many, and more.  Signatures and statistics
-equal the oracle's."""
+tasks after the last round, fewer than its workgroups, about as many, and more, and in both groups of a call.
+Signatures and statistics equal the oracle's."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,8 @@ torch = pytest.importorskip("torch")
 T0 = {2: (4, 864), 3: (6, 1504), 5: (8, 1536)}   # k, offset of t0 in the secret key
 
 
-@pytest.mark.parametrize("level,frac,count", [(2, 0.6, 16), (2, 0.6, 700), (3, 1.0, 512), (5, 0.8, 40), (2, 0.5, 2600)])
+@pytest.mark.parametrize("level,frac,count", [(2, 0.6, 16), (2, 0.6, 700), (3, 1.0, 512), (5, 0.8, 40), (2, 0.5, 2600),
+                                              (2, 0.5, 16385)])   # two groups
 def test_tasks_left_after_the_rounds(level, frac, count):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
